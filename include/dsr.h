@@ -90,7 +90,7 @@ extern "C" {
  *     level and takes a contiguous piece of the team's range; it pushes a
  *     16-byte frame {lo, hi, team frame's space, offset} on its own member
  *     stack and forks its inner team, four 16-lane groups, which take
- *     pieces of [lo, hi).  At depth 3 each group pushes a frame of the same
+ *     chunks of [lo, hi) in turn.  At depth 3 each group pushes a frame of the same
  *     shape, naming the wave's frame, on its own lane-group stack for four
  *     4-lane groups.  The innermost lanes reach the arrays by following the
  *     references.  Member stacks are on chip (64 B per wave, 16 B per lane
@@ -667,7 +667,9 @@ int dsr_occupancy_model(const dsr_hw_model *hw, uint32_t threads_per_team,
  * fixed fma chains up to 8+8, 16+16 and 32+32 scalars; 10 + k for the lean
  * instance of fixed chain k of (1,0) (1,1) (2,2) (4,4) (8,8) (16,16)
  * (32,32), which a single-region launch of workgroups up to 256 threads
- * runs when every publish of the region is that chain), the team's LDS
+ * runs when every publish of the region is that chain; 17 and 18 for the
+ * lean instances of any workgroup size, for regions that publish only
+ * gathers or only affine loops, with a static schedule), the team's LDS
  * (control block plus stack slab) and the device's parameters. */
 int dsr_region_occupancy(dsr_ctx *ctx, uint32_t variant, dsr_occupancy *out);
 

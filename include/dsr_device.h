@@ -88,7 +88,7 @@ struct cb_header {
     uint32_t sp_hbm;   /* HBM stack pointer                        */
     uint32_t nframes;  /* live frames                              */
     int32_t error;     /* team error (DSR_E_* or 0)                */
-    uint32_t bad;      /* OR of the workers' range flags           */
+    uint32_t pad0;
     uint32_t region;   /* launch-specific context published with the */
     uint32_t team;     /* body: which region and which of its teams  */
     uint32_t blocks;   /* blocks of the team's range claimed so far by its
@@ -129,9 +129,12 @@ __device__ inline void wave_sync()
 __device__ inline cb_header *header(const team_t &T) { return (cb_header *)T.lds; }
 __device__ inline uint32_t *frame_table(const team_t &T) { return (uint32_t *)(T.lds + 64); }
 __device__ inline uint32_t *ref_list(const team_t &T) { return (uint32_t *)(T.lds + 64 + DSR_MAX_FRAMES * 16); }
-__device__ inline uint64_t *red_slot(const team_t &T, uint32_t w)
+/* Byte offset in the team's LDS of wave w's reduction slot: a 192-bit partial
+ * (three 64-bit words, low first) and a range flag, left by every participating
+ * wave for the join. */
+__host__ __device__ constexpr uint32_t red_slot_at(uint32_t w)
 {
-    return (uint64_t *)(T.lds + 64 + DSR_MAX_FRAMES * 16 + DSR_REF_LIST * 8 + w * 32);
+    return 64u + DSR_MAX_FRAMES * 16u + DSR_REF_LIST * 8u + w * 32u;
 }
 /* Base of the team's nested area (on chip). */
 __device__ inline uint8_t *nest_lds(const team_t &T)
@@ -146,10 +149,9 @@ __device__ inline uint32_t *nest_desc(const team_t &T, uint32_t w)
                         w * DSR_NEST_DESC);
 }
 
-/* ~__kmpc_kernel_init.  Called by every thread of the team; the master
- * lane resets the stack.  The first barrier of the team (publish/await)
- * orders this before any worker reads the control block. */
-__device__ inline team_t team_init(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
+/* The team's view of its memory, without touching it: for a master that
+ * keeps its stack in registers (stack_t below). */
+__device__ inline team_t team_bind(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
                                    uint32_t threshold, uint8_t *hbm_slot, uint32_t hbm_cap)
 {
     team_t T;
@@ -164,6 +166,16 @@ __device__ inline team_t team_init(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
     T.lane = threadIdx.x & 63u;
     T.nest_hbm = nullptr;
     T.nest_global = 0;
+    return T;
+}
+
+/* ~__kmpc_kernel_init.  Called by every thread of the team; the master
+ * lane resets the stack.  The first barrier of the team (publish/await)
+ * orders this before any worker reads the control block. */
+__device__ inline team_t team_init(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
+                                   uint32_t threshold, uint8_t *hbm_slot, uint32_t hbm_cap)
+{
+    team_t T = team_bind(lds, nw, lds_cap, threshold, hbm_slot, hbm_cap);
     if (T.wave == nw - 1 && T.lane == 0) {
         cb_header *h = header(T);
         h->body = 0;
@@ -171,7 +183,6 @@ __device__ inline team_t team_init(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
         h->sp_hbm = 0;
         h->nframes = 0;
         h->error = 0;
-        h->bad = 0;
     }
     return T;
 }
@@ -187,7 +198,6 @@ __device__ inline void team_reset(team_t &T)
         h->sp_hbm = 0;
         h->nframes = 0;
         h->error = 0;
-        h->bad = 0;
     }
     wave_sync();
 }
@@ -270,17 +280,74 @@ __device__ inline bool await(team_t &T, uint32_t *body, frame_t *f, uint32_t *lo
     return *body != 0;
 }
 
-/* Every participating wave: deposit its reduction partial (a 192-bit
- * integer, three 64-bit words, low first) and its range flag, then join
- * (barrier 2).  Waves that did not run the body pass zeros. */
-__device__ inline void end_parallel(team_t &T, uint64_t w0, uint64_t w1, uint64_t w2, uint32_t bad)
+/* ---- the master's stack in registers: the same placement rule, frame table
+ * and LIFO order, with the stack pointers and the top frame held by the
+ * master wave (uniform values) instead of read back from the control block
+ * at every step; for a team that runs one program. */
+struct stack_t {
+    uint32_t sp_lds, sp_hbm, nframes;
+    frame_t top;
+};
+
+__device__ inline stack_t stack_empty() { return stack_t{0, 0, 0, frame_t{SPACE_NONE, 0, 0}}; }
+
+/* Live frame `depth` (0 = bottom). */
+__device__ inline frame_t frame_at(const team_t &T, const stack_t &S, uint32_t depth)
 {
-    if (T.lane == 0) {
-        uint64_t *r = red_slot(T, T.wave);
-        r[0] = w0; r[1] = w1; r[2] = w2;
-        if (bad) atomicOr(&header(T)->bad, 1u);
+    if (depth + 1 == S.nframes) return S.top;
+    const uint32_t *ft = frame_table(T) + 4 * depth;
+    return frame_t{uniform(ft[0]), uniform(ft[1]), uniform(ft[2])};
+}
+
+__device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes)
+{
+    const uint32_t size = (nbytes + DSR_ALIGN - 1) & ~(DSR_ALIGN - 1);
+    frame_t f{SPACE_NONE, 0, size};
+    if (size <= T.threshold && size <= T.lds_cap - S.sp_lds) {
+        f.space = SPACE_LDS; f.off = S.sp_lds; S.sp_lds += size;
+    } else if (size <= T.hbm_cap - S.sp_hbm) {
+        f.space = SPACE_HBM; f.off = S.sp_hbm; S.sp_hbm += size;
+    } else {
+        return f;
     }
-    __syncthreads();
+    if (T.lane == 0) *(uint4 *)(frame_table(T) + 4 * S.nframes) = make_uint4(f.space, f.off, f.size, 0);
+    S.nframes++;
+    S.top = f;
+    return f;
+}
+
+/* Pop the top frame; false on an empty stack. */
+__device__ inline bool pop(const team_t &T, stack_t &S)
+{
+    if (S.nframes == 0) return false;
+    if (S.top.space == SPACE_LDS) S.sp_lds -= S.top.size; else S.sp_hbm -= S.top.size;
+    S.nframes--;
+    if (S.nframes) {
+        const uint32_t *ft = frame_table(T) + 4 * (S.nframes - 1);
+        S.top = frame_t{uniform(ft[0]), uniform(ft[1]), uniform(ft[2])};
+    }
+    return true;
+}
+
+/* Master lane: what the next barrier hands to the workers. */
+__device__ inline void post(const team_t &T, frame_t f, uint32_t body, uint32_t loop)
+{
+    cb_header *h = header(T);
+    *(uint4 *)&h->body = make_uint4(body, f.space, f.off, f.size);
+    h->loop = loop;
+}
+
+/* Worker waves, after that barrier. */
+__device__ inline void take(const team_t &T, uint32_t &body, frame_t &f, uint32_t &loop)
+{
+    const cb_header *h = header(T);
+    const uint4 v = *(const uint4 *)&h->body;
+    const uint32_t l = h->loop;
+    body = uniform(v.x);
+    f.space = uniform(v.y);
+    f.off = uniform(v.z);
+    f.size = uniform(v.w);
+    loop = uniform(l);
 }
 
 /* Frame address in LDS or in the team's HBM slot. */

@@ -56,8 +56,9 @@ struct dsr_region {
     uint32_t n_red;
     uint32_t red_kind_mask;
     uint32_t variant;                   /* widest fixed fma chain published */
-    int32_t lean;                       /* lean instance chain every publish uses
-                                           (-1 none yet, -2 mixed or other bodies) */
+    int32_t lean;                       /* lean instance every publish runs on: its variant
+                                           less DSR_LEAN_BASE (-1 none yet, -2 mixed or
+                                           other bodies) */
     bool frozen;                        /* uploaded; program can't change   */
     /* device side */
     dsr_op *d_ops;
@@ -296,10 +297,14 @@ static bool lane_share_ok(const dsr_region *r, uint64_t chunk)
     return (chunk + lanes - 1) / lanes <= (1ull << 15);
 }
 
-/* The lean chain a publish of `body` over loop L would run on, or -2. */
-static int32_t lean_chain_of(int32_t body, const dsr_loop &L)
+/* The lean instance a publish of `body` over loop L would run on (its
+ * variant less DSR_LEAN_BASE), or -2. */
+static int32_t lean_of(int32_t body, const dsr_loop &L)
 {
-    if (body != DSR_BODY_FMA_CHAIN || L.alen != 0 || L.schedule != DSR_SCHED_STATIC) return -2;
+    if (L.schedule != DSR_SCHED_STATIC) return -2;
+    if (body == DSR_BODY_AFFINE_XOR) return DSR_LEAN_AFFINE - DSR_LEAN_BASE;
+    if (body == DSR_BODY_GATHER || body == DSR_BODY_GATHER_NESTED) return DSR_LEAN_GATHER - DSR_LEAN_BASE;
+    if (body != DSR_BODY_FMA_CHAIN || L.alen != 0) return -2;
     for (int32_t k = 0; k < DSR_LEAN_CHAINS; ++k)
         if ((int)L.ni == DSR_LEAN_NI(k) && (int)L.nf == DSR_LEAN_NF(k)) return k;
     return -2;
@@ -311,10 +316,14 @@ static void note_lean(dsr_region *r, int32_t k)
     else if (r->lean != k) r->lean = -2;
 }
 
-/* Kernel variant for a single-region launch of r with workgroups of wg. */
+/* Kernel variant for a single-region launch of r with workgroups of wg: the
+ * lean instance that holds all its bodies, compiled for up to 256 threads
+ * (fixed chains, whose scalars fill the registers of two waves per SIMD)
+ * or 1024 (gathers, affine loops). */
 static uint32_t single_variant(const dsr_region *r, uint32_t wg)
 {
-    return (r->lean >= 0 && wg <= 256) ? (uint32_t)(DSR_LEAN_BASE + r->lean) : r->variant;
+    const uint32_t lean = (uint32_t)(DSR_LEAN_BASE + r->lean);
+    return (r->lean >= 0 && (wg <= 256 || lean >= DSR_LEAN_GATHER)) ? lean : r->variant;
 }
 
 extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr_loop *loop)
@@ -380,7 +389,7 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
     } catch (...) {
         return DSR_E_NOMEM;
     }
-    note_lean(r, lean_chain_of(body, L));
+    note_lean(r, lean_of(body, L));
     return DSR_OK;
 }
 
@@ -514,31 +523,6 @@ static int upload(dsr_region *r)
     return DSR_OK;
 }
 
-/* A single-region launch carries the region's descriptor R (device
- * pointers) by value and, when its program is short, the program, its
- * first loop and the image of the frame op 0 pushes. */
-static void fill_single(dsr_dlaunch &LP, const dsr_region *r, const dsr_dregion &R)
-{
-    LP.has_single = 1;
-    LP.single = R;
-    LP.inl_ops = LP.inl_loop = LP.inl_img = 0;
-    if (r->ops.empty() || r->ops.size() > DSR_INLINE_OPS) return;
-    LP.inl_ops = (uint32_t)r->ops.size();
-    std::memcpy(LP.inl_op, r->ops.data(), r->ops.size() * sizeof(dsr_op));
-    if (!r->loops.empty()) {
-        LP.inl_loop = 1;
-        LP.inl_loop0 = r->loops[0];
-    }
-    const dsr_op &op = r->ops[0];
-    if (op.kind == DSR_OP_PUSH && op.init_stride == 0 && op.init_bytes > 0 && op.init_bytes <= DSR_INLINE_IMG &&
-        op.init_off + op.init_bytes <= r->init.size()) {
-        const uint32_t padded = (op.init_bytes + 15u) & ~15u;
-        std::memset(LP.inl_image, 0, padded);
-        std::memcpy(LP.inl_image, r->init.data() + op.init_off, op.init_bytes);
-        LP.inl_img = padded;
-    }
-}
-
 static dsr_dconfig make_dconfig(const dsr_ctx *c, uint32_t wg, uint32_t lds_slab, uint32_t threshold,
                                 uint32_t joins, uint32_t trace)
 {
@@ -555,6 +539,53 @@ static dsr_dconfig make_dconfig(const dsr_ctx *c, uint32_t wg, uint32_t lds_slab
     C.nest_global = (c->cfg.flags & DSR_F_NESTED_GLOBAL) ? 1u : 0u;
     C.nest_base = c->nest;
     return C;
+}
+
+/* Launch region r, whose descriptor R holds device pointers, with workgroups
+ * of the context's size: its lean instance with everything in the kernel
+ * arguments, or a general one. */
+static int launch_single(const dsr_region *r, const dsr_dregion &R, const dsr_dregion *d_self, const dsr_dconfig &C,
+                         void *stream)
+{
+    const dsr_ctx *c = r->ctx;
+    const uint32_t variant = single_variant(r, c->cfg.wg_size);
+    if (variant < DSR_LEAN_BASE) {
+        dsr_dlaunch LP{};
+        LP.regions = d_self;
+        LP.items = nullptr;
+        LP.n_regions = 1;
+        return dsr_launch_region_kernel(&LP, &C, (uint32_t)r->teams, c->cfg.wg_size, c->lds_bytes, variant, stream);
+    }
+    dsr_lean A;
+    A.hbm_base = C.hbm_base;
+    A.hbm_slot_bytes = C.hbm_slot_bytes;
+    A.nest_base = C.nest_base;
+    A.partials = R.partials;
+    A.result = R.result;
+    A.trace = C.trace ? R.trace : nullptr;
+    A.ops = R.ops;
+    A.loops = R.loops;
+    A.init = R.init;
+    A.nw = C.nw;
+    A.lds_cap = C.lds_cap;
+    A.threshold = C.threshold;
+    A.master_joins = C.master_joins;
+    A.nest_global = C.nest_global;
+    A.n_ops = R.n_ops;
+    A.teams = R.teams;
+    A.n_red = R.n_red;
+    A.loop0 = r->loops[0];                 /* a lean region publishes at least once */
+    A.inl_ops = r->ops.size() <= DSR_INLINE_OPS ? 1u : 0u;
+    if (A.inl_ops) std::memcpy(A.inl_op, r->ops.data(), r->ops.size() * sizeof(dsr_op));
+    A.inl_img = 0;
+    const dsr_op &op = r->ops[0];
+    if (op.kind == DSR_OP_PUSH && op.init_stride == 0 && op.init_bytes > 0 && op.init_bytes <= DSR_INLINE_IMG) {
+        const uint32_t padded = (op.init_bytes + 15u) & ~15u;
+        std::memset(A.image, 0, padded);
+        std::memcpy(A.image, r->init.data() + op.init_off, op.init_bytes);
+        A.inl_img = padded;
+    }
+    return dsr_launch_region_kernel(&A, &C, (uint32_t)r->teams, c->cfg.wg_size, c->lds_bytes, variant, stream);
 }
 
 extern "C" int dsr_region_freeze(dsr_region *r)
@@ -584,20 +615,13 @@ extern "C" int dsr_launch(dsr_region *r, void *stream)
         r->frozen = true;
     }
     hipStream_t s = (hipStream_t)stream;
-    dsr_dlaunch LP{};
-    LP.regions = r->d_self;
-    LP.items = nullptr;
-    LP.n_regions = 1;
-    fill_single(LP, r, r->desc);
     const dsr_dconfig C = make_dconfig(c, c->cfg.wg_size, c->cfg.lds_slab_bytes, c->cfg.overflow_threshold,
                                        c->cfg.master_joins, (c->cfg.flags & DSR_F_TRACE) ? 1u : 0u);
     /* events only when timing is asked for: a marker between back-to-back
      * launches costs about as much as a small region's fixed overhead */
     const bool timing = (c->cfg.flags & DSR_F_TIMING) != 0;
     if (timing && hipEventRecord(r->ev0, s) != hipSuccess) return DSR_E_HIP;
-    if (dsr_launch_region_kernel(&LP, &C, (uint32_t)r->teams, c->cfg.wg_size, c->lds_bytes,
-                                 single_variant(r, c->cfg.wg_size), stream) != 0)
-        return DSR_E_HIP;
+    if (launch_single(r, r->desc, r->d_self, C, stream) != 0) return DSR_E_HIP;
     if (timing && hipEventRecord(r->ev1, s) != hipSuccess) return DSR_E_HIP;
     r->stream = s;
     r->timed = timing;
@@ -782,18 +806,11 @@ extern "C" int dsr_launch_static(dsr_region *r, dsr_result_rec *result, void *st
     /* counters, error word and arrival tree start at zero; partials and
      * stacks are written before they are read */
     if ((rc = dsr_static_fill(ws + L.result, sizeof(dsr_dresult) / 4, 0u, stream))) return rc;
-    dsr_dlaunch LP{};
-    LP.regions = (const dsr_dregion *)(ws + L.desc);
-    LP.items = nullptr;
-    LP.n_regions = 1;
-    fill_single(LP, r, R);
     dsr_dconfig C = make_dconfig(c, c->cfg.wg_size, c->cfg.lds_slab_bytes, c->cfg.overflow_threshold,
                                  c->cfg.master_joins, 0u);
     C.hbm_base = ws + L.hbm;
     C.nest_base = L.nested ? ws + L.nest : nullptr;
-    if (dsr_launch_region_kernel(&LP, &C, (uint32_t)r->teams, c->cfg.wg_size, c->lds_bytes,
-                                 single_variant(r, c->cfg.wg_size), stream) != 0)
-        return DSR_E_HIP;
+    if (launch_single(r, R, (const dsr_dregion *)(ws + L.desc), C, stream) != 0) return DSR_E_HIP;
     return dsr_static_copy_result(ws + L.result, r->n_red, result, stream);
 }
 

@@ -9,7 +9,7 @@
 #include "dsr_internal.h"
 
 #define DSR_DECLARE(tag, maxwg, variant)                                                                    \
-    extern "C" int dsr_inst_launch_##tag(const dsr_dlaunch *, const dsr_dconfig *, uint32_t, uint32_t,     \
+    extern "C" int dsr_inst_launch_##tag(const void *, const dsr_dconfig *, uint32_t, uint32_t,            \
                                          uint32_t, void *);                                                 \
     extern "C" int dsr_inst_occupancy_##tag(uint32_t, uint32_t);                                           \
     extern "C" int dsr_inst_regs_##tag(void);
@@ -21,7 +21,7 @@ namespace {
 struct instance {
     uint32_t maxwg;
     int variant;
-    int (*launch)(const dsr_dlaunch *, const dsr_dconfig *, uint32_t, uint32_t, uint32_t, void *);
+    int (*launch)(const void *, const dsr_dconfig *, uint32_t, uint32_t, uint32_t, void *);
     int (*occupancy)(uint32_t, uint32_t);
     int (*regs)(void);
 };
@@ -33,14 +33,13 @@ const instance kInstances[] = {DSR_INSTANCES(DSR_ENTRY)};
 
 /* Workgroups above 512 threads run the 1024-thread instance (run-time
  * chains only), 257-512 the 512-thread one; up to 256 threads the variant
- * the regions need, or the lean instance a single region of one fixed
- * chain asks for. */
+ * the regions need.  A lean instance runs the workgroup sizes it was
+ * compiled for. */
 const instance *pick(uint32_t wg_size, uint32_t variant)
 {
     if (variant >= DSR_LEAN_BASE) {
-        if (wg_size > 256 || variant >= DSR_LEAN_BASE + DSR_LEAN_CHAINS) return nullptr;
         for (const instance &k : kInstances)
-            if (k.maxwg == 256u && k.variant == (int)variant) return &k;
+            if (wg_size <= k.maxwg && k.variant == (int)variant) return &k;
         return nullptr;
     }
     const uint32_t maxwg = wg_size > 512 ? 1024u : (wg_size > 256 ? 512u : 256u);
@@ -52,11 +51,11 @@ const instance *pick(uint32_t wg_size, uint32_t variant)
 
 }  // namespace
 
-extern "C" int dsr_launch_region_kernel(const dsr_dlaunch *lp, const dsr_dconfig *cfg, uint32_t grid,
+extern "C" int dsr_launch_region_kernel(const void *args, const dsr_dconfig *cfg, uint32_t grid,
                                         uint32_t wg_size, uint32_t lds_bytes, uint32_t variant, void *stream)
 {
     const instance *k = pick(wg_size, variant);
-    return k ? k->launch(lp, cfg, grid, wg_size, lds_bytes, stream) : 1 /* hipErrorInvalidValue */;
+    return k ? k->launch(args, cfg, grid, wg_size, lds_bytes, stream) : 1 /* hipErrorInvalidValue */;
 }
 
 extern "C" int dsr_region_kernel_occupancy(uint32_t wg_size, uint32_t lds_bytes, uint32_t variant)

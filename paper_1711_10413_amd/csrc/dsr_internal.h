@@ -161,20 +161,32 @@ struct dsr_dlaunch {
     uint64_t idle_limit;       /* close after a waiting workgroup saw the
                                   published count unchanged for this many
                                   ticks of its own clock                    */
-    /* Single-region launches (items == null) may carry the region's
-     * descriptor by value and, for a program of at most DSR_INLINE_OPS ops,
-     * its ops, its first loop descriptor and the initial image of the frame
-     * its first op pushes (the same image for every team), so that a team
-     * forks without reading any of them from memory first. */
-    uint32_t has_single;       /* `single` holds regions[0]                 */
-    uint32_t inl_ops;          /* ops held in inl_op (0: read them from memory) */
-    uint32_t inl_loop;         /* inl_loop0 holds loop 0                    */
-    uint32_t inl_img;          /* image bytes held in inl_image (a multiple
-                                  of 16, zero-padded; 0: none)              */
-    dsr_dregion single;
-    dsr_dloop inl_loop0;
+};
+
+/* What one launch of a lean instance runs: one region on gridDim.x teams,
+ * team = blockIdx.x.  The whole launch is in the kernel arguments: for a
+ * program of at most DSR_INLINE_OPS ops the ops, and the initial image of
+ * the frame its first op pushes (the same image for every team) of up to
+ * DSR_INLINE_IMG bytes, so that a team forks without reading any of them
+ * from memory first. */
+struct dsr_lean {
+    uint8_t *hbm_base;         /* HBM slab slots, as in dsr_dconfig         */
+    uint64_t hbm_slot_bytes;
+    uint8_t *nest_base;
+    uint64_t *partials;        /* the region, as in dsr_dregion             */
+    dsr_dresult *result;
+    uint32_t *trace;           /* null: not traced                          */
+    const dsr_op *ops;
+    const dsr_dloop *loops;
+    const uint8_t *init;
+    uint32_t nw, lds_cap, threshold, master_joins, nest_global;
+    uint32_t n_ops, teams, n_red;
+    uint32_t inl_ops;          /* 1: the ops are in inl_op (0: read them from memory) */
+    uint32_t inl_img;          /* image bytes held in `image` (a multiple of
+                                  16, zero-padded; 0: none)                 */
+    dsr_dloop loop0;
     dsr_op inl_op[DSR_INLINE_OPS];
-    uint8_t inl_image[DSR_INLINE_IMG];
+    uint8_t image[DSR_INLINE_IMG];
 };
 
 /* Served form: control words in device memory (LP.counter, 32-bit words).
@@ -221,13 +233,20 @@ struct dsr_dconfig {
     X(256_l3, 256, 13)   \
     X(256_l4, 256, 14)   \
     X(256_l5, 256, 15)   \
-    X(256_l6, 256, 16)
+    X(256_l6, 256, 16)   \
+    X(1024_g, 1024, 17)  \
+    X(1024_a, 1024, 18)
 
 /* Lean instances: variant DSR_LEAN_BASE + k runs single-region launches of
  * workgroups up to 256 threads whose publishes are all the fixed fma chain
- * k, (DSR_LEAN_NI(k) int32, DSR_LEAN_NF(k) fp64 scalars), with no array. */
+ * k, (DSR_LEAN_NI(k) int32, DSR_LEAN_NF(k) fp64 scalars), with no array;
+ * DSR_LEAN_GATHER and DSR_LEAN_AFFINE single-region launches of any workgroup
+ * size whose publishes are all gathers (flat or nested) or all affine
+ * loops, with a static schedule. */
 #define DSR_LEAN_BASE 10
 #define DSR_LEAN_CHAINS 7
+#define DSR_LEAN_GATHER 17
+#define DSR_LEAN_AFFINE 18
 #define DSR_LEAN_NI(k) ((k) == 0 ? 1 : (k) == 1 ? 1 : (k) == 2 ? 2 : (k) == 3 ? 4 : (k) == 4 ? 8 : (k) == 5 ? 16 : 32)
 #define DSR_LEAN_NF(k) ((k) == 0 ? 0 : DSR_LEAN_NI(k))
 
@@ -240,7 +259,8 @@ int dsr_static_workspace(int device, uint8_t **out);
 int dsr_static_fill(void *p, uint32_t words, uint32_t value, void *stream);
 int dsr_static_copy_result(const void *result_block, uint32_t n_red, void *dst, void *stream);
 /* Kernel launchers (dsr_dispatch.cpp). Return hipError_t as int. */
-int dsr_launch_region_kernel(const dsr_dlaunch *lp, const dsr_dconfig *cfg, uint32_t grid,
+/* `args` is a dsr_dlaunch, or a dsr_lean for a lean variant (cfg unused). */
+int dsr_launch_region_kernel(const void *args, const dsr_dconfig *cfg, uint32_t grid,
                              uint32_t wg_size, uint32_t lds_bytes, uint32_t variant,
                              void *stream);
 /* Workgroups of the region kernel that fit on one CU at once (0 on error). */

@@ -29,6 +29,10 @@
 #include "dsr_device.h"
 #include "dsr_internal.h"
 
+#if !defined(DSR_INST_MAXWG) || !defined(DSR_INST_VARIANT) || !defined(DSR_INST_TAG)
+#error "compile with -DDSR_INST_MAXWG=<threads> -DDSR_INST_VARIANT=<v> -DDSR_INST_TAG=<tag>"
+#endif
+
 using namespace dsr;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -180,6 +184,16 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane)
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane);
     const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
     return ((uint64_t)hi << 32) | lo;
+}
+
+/* Sum over the first row (lanes 0 to 15), returned to every lane. */
+__device__ __forceinline__ i192 row_sum192(i192 v)
+{
+    v = dpp_add192<0x111, 0x1>(v);   /* row_shr:1 */
+    v = dpp_add192<0x112, 0x1>(v);   /* row_shr:2 */
+    v = dpp_add192<0x114, 0x1>(v);   /* row_shr:4 */
+    v = dpp_add192<0x118, 0x1>(v);   /* row_shr:8 */
+    return i192{readlane64(v.w0, 15), readlane64(v.w1, 15), readlane64(v.w2, 15)};
 }
 
 /* Sum over the 64 lanes of a wave, returned to every lane: a running sum
@@ -857,76 +871,103 @@ __device__ __forceinline__ void body_fma_rt(const team_t &T, frame_t f, const ds
 __device__ __forceinline__ i32x4 load4(const LDSQ int32_t *p) { return *(const LDSQ i32x4 *)p; }
 __device__ __forceinline__ i32x4 load4(const GLB int32_t *p) { return *(const GLB i32x4 *)p; }
 
-template <int NA, class AP>
-__device__ __forceinline__ i32x4 gather4(AP arr, uint32_t len, uint32_t na, uint32_t idx)
+/* V consecutive outputs of one lane. */
+template <int V>
+struct gather_vec {
+    uint32_t e[V];
+};
+
+template <int NA, int V, class AP>
+__device__ __forceinline__ gather_vec<V> gather_sum(AP arr, uint32_t len, uint32_t na, uint32_t idx)
 {
-    i32x4 s = {0, 0, 0, 0};
-    if (NA > 0) {
+    gather_vec<V> s;
 #pragma unroll
-        for (int j = 0; j < NA; ++j) s += load4(arr + (uint64_t)j * len + idx);
+    for (int k = 0; k < V; ++k) s.e[k] = 0;
+    AP a = arr + idx;
+    auto add = [&]() {
+        if constexpr (V == 4) {
+            const i32x4 v = load4(a);
+            s.e[0] += (uint32_t)v.x;
+            s.e[1] += (uint32_t)v.y;
+            s.e[2] += (uint32_t)v.z;
+            s.e[3] += (uint32_t)v.w;
+        } else {
+            s.e[0] += (uint32_t)*a;
+        }
+        a += len;
+    };
+    if constexpr (NA > 0) {
+#pragma unroll
+        for (int j = 0; j < NA; ++j) add();
     } else {
-        for (uint32_t j = 0; j < na; ++j) s += load4(arr + (uint64_t)j * len + idx);
+#pragma nounroll
+        for (uint32_t j = 0; j < na; ++j) add();
     }
     return s;
 }
 
-/* Vectors [v0, v1) of 4 elements, visited v0 + k*stride; len % 4 == 0.
- * BATCH4: four vectors at a time (false where registers are scarce). */
-template <int NA, class AP, bool BATCH4 = true>
-__device__ __forceinline__ void gather_vectors(AP arr, const dsr_dloop &L, uint64_t v0, uint64_t v1,
-                                               uint64_t stride)
+template <int V>
+__device__ __forceinline__ void gather_store(GLB int32_t *out, uint32_t i, const gather_vec<V> &s)
 {
-    const uint32_t len = L.len;
-    GLB i32x4 *__restrict__ out4 = (GLB i32x4 *)L.out;
-    uint32_t idx = (uint32_t)((v0 * 4) % len);
-    const uint32_t step = (uint32_t)((stride * 4) % len);
-    uint64_t v = v0;
-    /* four vectors at a time, their array reads (LDS or global) all in flight */
-    for (; BATCH4 && v + 3 * stride < v1; v += 4 * stride) {
-        const uint32_t i1 = mod_step(idx, step, len), i2 = mod_step(i1, step, len), i3 = mod_step(i2, step, len);
-        i32x4 s[4] = {gather4<NA>(arr, len, L.arrays, idx), gather4<NA>(arr, len, L.arrays, i1),
-                      gather4<NA>(arr, len, L.arrays, i2), gather4<NA>(arr, len, L.arrays, i3)};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint64_t w = v + u * stride;
-            const uint32_t base = (uint32_t)(w * 4);
-            s[u] += i32x4{(int32_t)base, (int32_t)(base + 1), (int32_t)(base + 2), (int32_t)(base + 3)};
-            __builtin_nontemporal_store(s[u], &out4[w]);
-        }
-        idx = mod_step(i3, step, len);
+    if constexpr (V == 4) {
+        const i32x4 r = {(int32_t)(s.e[0] + i), (int32_t)(s.e[1] + i + 1), (int32_t)(s.e[2] + i + 2),
+                         (int32_t)(s.e[3] + i + 3)};
+        __builtin_nontemporal_store(r, (GLB i32x4 *)(out + i));
+    } else {
+        __builtin_nontemporal_store((int32_t)(s.e[0] + i), out + i);
     }
-    for (; v < v1; v += stride) {
-        i32x4 s = gather4<NA>(arr, len, L.arrays, idx);
-        const uint32_t base = (uint32_t)(v * 4);
-        s += i32x4{(int32_t)base, (int32_t)(base + 1), (int32_t)(base + 2), (int32_t)(base + 3)};
-        __builtin_nontemporal_store(s, &out4[v]);
+}
+
+/* One lane's share of a gather: V outputs at i0, i0 + stride, ... below i1
+ * (the last group may be cut short by i1).  V = 4 needs len and i0 to be
+ * multiples of 4, so a group never wraps inside an array.  A loop has fewer
+ * than 2^31 iterations, so every index is 32 bits wide, and the array index
+ * is carried from group to group (one conditional subtraction) after one
+ * division at the start (a 64-bit remainder per element had bound loops over
+ * arrays of a ragged length).  Bound by the output stores; four groups go at
+ * a time, their array reads (LDS or global) all in flight.  Launch and wait
+ * of 10^7 outputs, 3 x 257, three levels: 68.0 -> 32.3 us; of 2^26 outputs,
+ * 2 x 4096, two levels: 81.3 -> 66.7 us (with the lean instance, four
+ * workgroups per CU instead of two). */
+template <int NA, int V, class AP>
+__device__ __forceinline__ void gather_run(AP arr, uint32_t len, uint32_t na, GLB int32_t *__restrict__ out,
+                                           uint32_t i0, uint32_t i1, uint32_t stride)
+{
+    if (i0 >= i1) return;
+    uint32_t i = i0, idx = i0 % len;
+    const uint32_t step = stride % len;
+#pragma nounroll
+    for (; i + 3 * stride + V <= i1; i += 4 * stride) {
+        const uint32_t x1 = mod_step(idx, step, len), x2 = mod_step(x1, step, len), x3 = mod_step(x2, step, len);
+        const gather_vec<V> s0 = gather_sum<NA, V>(arr, len, na, idx), s1 = gather_sum<NA, V>(arr, len, na, x1),
+                            s2 = gather_sum<NA, V>(arr, len, na, x2), s3 = gather_sum<NA, V>(arr, len, na, x3);
+        gather_store<V>(out, i, s0);
+        gather_store<V>(out, i + stride, s1);
+        gather_store<V>(out, i + 2 * stride, s2);
+        gather_store<V>(out, i + 3 * stride, s3);
+        idx = mod_step(x3, step, len);
+    }
+#pragma nounroll
+    for (; i + V <= i1; i += stride) {
+        gather_store<V>(out, i, gather_sum<NA, V>(arr, len, na, idx));
         idx = mod_step(idx, step, len);
     }
+    if constexpr (V > 1) {
+#pragma nounroll
+        for (; i < i1; ++i, ++idx) gather_store<1>(out, i, gather_sum<NA, 1>(arr, len, na, idx));
+    }
 }
 
-template <class AP>
-__device__ __forceinline__ void gather_scalar(AP arr, const dsr_dloop &L, uint64_t i0, uint64_t i1,
-                                              uint64_t stride)
+/* Lane q of G lanes that share [lo, hi): groups of four outputs where the
+ * arrays and the range allow it, single outputs otherwise; each store
+ * instruction of the G lanes covers consecutive elements either way. */
+template <int NA, class AP>
+__device__ __forceinline__ void gather_lanes(AP arr, const dsr_dloop &L, uint32_t lo, uint32_t hi, uint32_t q,
+                                             uint32_t G, bool vec)
 {
     GLB int32_t *out = (GLB int32_t *)L.out;
-    for (uint64_t i = i0; i < i1; i += stride) {
-        uint32_t s = (uint32_t)i;
-        const uint32_t k = (uint32_t)(i % L.len);
-        for (uint32_t j = 0; j < L.arrays; ++j) s += (uint32_t)arr[(uint64_t)j * L.len + k];
-        out[i] = (int32_t)s;
-    }
-}
-
-template <int NA, class AP>
-__device__ __forceinline__ void gather_span(AP arr, const dsr_dloop &L, span_t sp)
-{
-    if ((L.len & 3u) || (sp.lo & 3u)) {
-        gather_scalar(arr, L, sp.lo + sp.p, sp.hi, sp.P);
-        return;
-    }
-    const uint64_t nv = (sp.hi - sp.lo) >> 2;
-    gather_vectors<NA>(arr, L, (sp.lo >> 2) + sp.p, (sp.lo >> 2) + nv, sp.P);
-    gather_scalar(arr, L, sp.lo + 4 * nv + sp.p, sp.hi, sp.P);
+    if (vec) gather_run<NA, 4>(arr, L.len, L.arrays, out, lo + 4 * q, hi, 4 * G);
+    else gather_run<NA, 1>(arr, L.len, L.arrays, out, lo + q, hi, G);
 }
 
 /* ---- nested levels ----------------------------------------------------------
@@ -942,31 +983,31 @@ __device__ __forceinline__ void split_range(uint64_t lo, uint64_t hi, uint32_t p
     b = min(hi, a + per);
 }
 
-/* The innermost members' loop: elements [a, b) over G lanes (q = this
- * lane's index), on 16-byte vectors when `vec` (a is then a multiple of 4). */
-template <int NA, bool BATCH4, class AP>
-__device__ __forceinline__ void gather_leaf(AP arr, const dsr_dloop &L, uint64_t a, uint64_t b, uint32_t q,
-                                            uint32_t G, bool vec)
+/* The lanes of one gather loop: lane q of G shares [lo, hi) of the team frame
+ * at (space, off). */
+struct gather_t {
+    uint32_t space, off, lo, hi, q, G;
+};
+
+/* The gather loop itself, at one place for the flat and the nested bodies:
+ * the array count as a constant (0: more than four), the arrays in LDS or in
+ * global memory, groups of four outputs or single ones. */
+__device__ __forceinline__ void gather_loop(const team_t &T, const dsr_dloop &L, const gather_t &g, bool vec)
 {
-    if (vec) {
-        const uint64_t v1 = b >> 2;
-        gather_vectors<NA, AP, BATCH4>(arr, L, (a >> 2) + q, v1, G);
-        gather_scalar(arr, L, (v1 << 2) + q, b, G);
-    } else {
-        gather_scalar(arr, L, a + q, b, G);
-    }
+    auto at = [&](auto arr) {
+        switch (L.arrays) {
+        case 1: gather_lanes<1>(arr, L, g.lo, g.hi, g.q, g.G, vec); break;
+        case 2: gather_lanes<2>(arr, L, g.lo, g.hi, g.q, g.G, vec); break;
+        case 3: gather_lanes<3>(arr, L, g.lo, g.hi, g.q, g.G, vec); break;
+        case 4: gather_lanes<4>(arr, L, g.lo, g.hi, g.q, g.G, vec); break;
+        default: gather_lanes<0>(arr, L, g.lo, g.hi, g.q, g.G, vec); break;
+        }
+    };
+    if (g.space == SPACE_LDS) at((const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + g.off));
+    else at((const GLB int32_t *)(T.stack_hbm + g.off));
 }
 
-/* The gather through a reference to the team's frame (space, offset). */
-template <int NA, bool BATCH4>
-__device__ __forceinline__ void gather_leaf_at(const team_t &T, uint32_t space, uint32_t off, const dsr_dloop &L,
-                                               uint64_t a, uint64_t b, uint32_t q, uint32_t G, bool vec)
-{
-    if (space == SPACE_LDS)
-        gather_leaf<NA, BATCH4>((const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + off), L, a, b, q, G, vec);
-    else
-        gather_leaf<NA, BATCH4>((const GLB int32_t *)(T.stack_hbm + off), L, a, b, q, G, vec);
-}
+__device__ __forceinline__ bool gather_vec4(const dsr_dloop &L, span_t sp) { return !((L.len & 3u) || (sp.lo & 3u)); }
 
 /* A nested fork or join inside one wave: the leader lanes' frame and
  * descriptor writes (LDS, or the global part of a member stack) become
@@ -986,16 +1027,19 @@ __device__ __forceinline__ uint32_t pack_place(frame_t f) { return (f.space << 2
  * and takes its piece of the team's range.  It pushes the frame {lo, hi,
  * team frame's space, offset} on its own member stack, publishes it in its
  * descriptor and forks its inner team, the four 16-lane groups.  Level 2:
- * each group reads the descriptor, then the frame, and takes its piece.  At
+ * each group reads the descriptor, then the frame, and takes its pieces.  At
  * depth 2 its lanes gather through the team frame the frame names.  At
  * depth 3 each group's leader lane pushes a frame {lo, hi, the wave frame's
  * space, offset} on the group's own member stack and forks the group's
  * inner team, four 4-lane groups, which reach the team frame by following
- * the two references.  Frames are popped in LIFO order after each inner
+ * the two references.  The inner members take chunks of the wave's range in
+ * turn (one group of outputs per lane, as a cyclic static schedule does), so
+ * that the wave's stores cover consecutive elements: with one contiguous
+ * piece per 4-lane member a store instruction had touched 16 cache lines a
+ * quarter full or less.  Frames are popped in LIFO order after each inner
  * team joins.  A member stack's frame goes to its on-chip part, or to its
  * global part when the on-chip part is full or `nest_global` is set; each
  * global part holds several nested frames, so no nested push fails. */
-template <int NA, bool BATCH4>
 __device__ __forceinline__ void body_gather_nested(team_t &T, frame_t outer, const dsr_dloop &L, span_t sp,
                                                    uint32_t member, uint32_t members, uint32_t &inner_pushes,
                                                    GLB uint32_t *tr)
@@ -1003,7 +1047,7 @@ __device__ __forceinline__ void body_gather_nested(team_t &T, frame_t outer, con
     static_assert(DSR_NEST_WAVE_HBM >= DSR_NEST_FRAME && DSR_NEST_GROUP_HBM >= DSR_NEST_FRAME,
                   "a global part holds at least one nested frame");
     const uint32_t depth = uniform(L.depth);
-    const bool vec = !((L.len & 3u) || (sp.lo & 3u));
+    const bool vec = gather_vec4(L, sp);
     const uint32_t gran = vec ? 4u : 1u;
     const uint32_t lane = T.lane;
     uint32_t *desc = nest_desc(T, member);
@@ -1025,24 +1069,23 @@ __device__ __forceinline__ void body_gather_nested(team_t &T, frame_t outer, con
     }
     inner_pushes += 1;
     nest_sync();
-    /* level 2: lane group g reads the published frame */
+    /* level 2: lane group g reads the published frame; its first chunk is 16
+     * lanes' outputs, the next one a wave's outputs further on */
     const uint32_t g = lane >> 4, l = lane & 15u;
     const uint32_t d2s = desc[0], d2o = desc[1];
     const uint32_t *q2 = nest_addr(T, d2s, d2o);
-    const uint32_t vlo = q2[0], vhi = q2[1], osp = q2[2], ooff = q2[3];
-    uint64_t glo, ghi;
-    split_range(vlo, vhi, DSR_NEST_GROUPS, g, gran, glo, ghi);
-    if (depth == 2) {
-        gather_leaf_at<NA, BATCH4>(T, osp, ooff, L, glo, ghi, l, 16u, vec);
-    } else {
+    gather_t leaf{q2[2], q2[3], q2[0] + g * 16u * gran, q2[1], l, 64u};
+    mstack_t gs{};
+    frame_t f3{SPACE_NONE, 0, 0};
+    if (depth != 2) {
         const uint32_t k = member * DSR_NEST_GROUPS + g;
-        mstack_t gs = mstack(members * DSR_NEST_WAVE_LDS + k * DSR_NEST_GROUP_LDS, DSR_NEST_GROUP_LDS,
-                             members * DSR_NEST_WAVE_HBM + k * DSR_NEST_GROUP_HBM, DSR_NEST_GROUP_HBM);
-        const frame_t f3 = mpush(gs, DSR_NEST_FRAME, T.nest_global != 0);
+        gs = mstack(members * DSR_NEST_WAVE_LDS + k * DSR_NEST_GROUP_LDS, DSR_NEST_GROUP_LDS,
+                    members * DSR_NEST_WAVE_HBM + k * DSR_NEST_GROUP_HBM, DSR_NEST_GROUP_HBM);
+        f3 = mpush(gs, DSR_NEST_FRAME, T.nest_global != 0);
         uint32_t *p3 = nest_addr(T, f3.space, f3.off);
         if (l == 0) {
-            p3[0] = (uint32_t)glo;
-            p3[1] = (uint32_t)ghi;
+            p3[0] = leaf.lo;
+            p3[1] = leaf.hi;
             p3[2] = d2s;
             p3[3] = d2o;
             desc[2 + 2 * g] = f3.space;
@@ -1054,17 +1097,25 @@ __device__ __forceinline__ void body_gather_nested(team_t &T, frame_t outer, con
         /* level 3: 4-lane group s of group g */
         const uint32_t s = l >> 2, q = l & 3u;
         const uint32_t *q3 = nest_addr(T, desc[2 + 2 * g], desc[3 + 2 * g]);
-        const uint32_t slo = q3[0], shi = q3[1];
         const uint32_t *pp = nest_addr(T, q3[2], q3[3]);      /* the wave's frame */
-        uint64_t a, b;
-        split_range(slo, shi, DSR_NEST_GROUPS, s, gran, a, b);
-        gather_leaf_at<NA, BATCH4>(T, pp[2], pp[3], L, a, b, q, 4u, vec);
+        leaf = gather_t{pp[2], pp[3], q3[0] + s * 4u * gran, q3[1], q, 64u};
+    }
+    /* every lane follows the same chain to the same team frame */
+    leaf.space = uniform(leaf.space);
+    leaf.off = uniform(leaf.off);
+    gather_loop(T, L, leaf, vec);
+    if (depth != 2) {
         nest_sync();                                            /* inner join */
         if (!mpop(gs, f3) && tr) tr[133 + 8 * member] = 1;
     }
     nest_sync();                                                /* inner join */
     if (!mpop(ws, f2) && tr && lane == 0) tr[133 + 8 * member] = 1;
     if (tr && lane == 0) tr[134 + 8 * member] = inner_pushes;
+}
+
+__device__ __forceinline__ void body_gather(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp)
+{
+    gather_loop(T, L, gather_t{f.space, f.off, (uint32_t)sp.lo, (uint32_t)sp.hi, sp.p, sp.P}, gather_vec4(L, sp));
 }
 
 /* Cross-team traffic (partials, arrival counters, results) uses
@@ -1103,31 +1154,12 @@ __device__ __forceinline__ const uint8_t *frame_ptr(const team_t &T, frame_t f)
  * 512 threads); 1: adds 16+16; 2: adds 32+32; -1 (workgroups above 512
  * threads, 128 registers per lane): run-time chains only.  Other lengths
  * (at most 64 scalars) use the run-time chain, one pair per batch at -1. */
-/* Lean instances (VARIANT >= DSR_LEAN_BASE) run single-region launches
- * whose every publish is one fixed fma chain, DSR_LEAN_NI/NF of the
- * variant: the kernel then holds only that body and only the single-region
- * form, so its code and registers are those of the sweep's own path. */
-template <int VARIANT>
-struct lean_chain {
-    static constexpr int k = VARIANT - DSR_LEAN_BASE;
-    static constexpr int ni = DSR_LEAN_NI(k), nf = DSR_LEAN_NF(k);
-};
-
 template <int VARIANT>
 __device__ __forceinline__ void run_body(team_t &T, uint32_t body, frame_t f, const dsr_dloop &L, span_t sp,
                                          lane_acc &A, uint32_t *claim, uint32_t member,
                                          uint32_t members, uint32_t &inner_pushes, GLB uint32_t *tr)
 {
     const uint32_t lane = T.lane;
-    if constexpr (VARIANT >= DSR_LEAN_BASE) {
-        /* the host dispatches only regions made of this chain here */
-        /* every scalar stays in registers: reading them once per batch
-         * instead (the general instances' run-time chain) measured slower
-         * here for every chain length */
-        if (body == DSR_BODY_FMA_CHAIN)
-            body_fma_fixed<lean_chain<VARIANT>::ni, lean_chain<VARIANT>::nf, false>(T, f, L, sp, A, claim, lane);
-        return;
-    }
     switch (body) {
     case DSR_BODY_AFFINE_XOR: {
         /* frame layout: [8 B int64 sum][a][b][c][d] */
@@ -1195,40 +1227,12 @@ __device__ __forceinline__ void run_body(team_t &T, uint32_t body, frame_t f, co
         }
         break;
     }
-    case DSR_BODY_GATHER: {
-        if (f.space == SPACE_LDS) {
-            const LDSQ int32_t *arr = (const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + f.off);
-            switch (L.arrays) {
-#define GATHER_CASE(NA) for_spans(L, sp, lane, claim, A, [&](span_t q) { gather_span<NA>(arr, L, q); }); break;
-            case 1: GATHER_CASE(1)
-            case 2: GATHER_CASE(2)
-            case 3: GATHER_CASE(3)
-            case 4: GATHER_CASE(4)
-            default: GATHER_CASE(0)
-            }
-        } else {
-            const GLB int32_t *arr = (const GLB int32_t *)frame_hbm(T, f);
-            switch (L.arrays) {
-            case 1: GATHER_CASE(1)
-            case 2: GATHER_CASE(2)
-            case 3: GATHER_CASE(3)
-            case 4: GATHER_CASE(4)
-            default: GATHER_CASE(0)
-#undef GATHER_CASE
-            }
-        }
+    case DSR_BODY_GATHER:
+        for_spans(L, sp, lane, claim, A, [&](span_t q) { body_gather(T, f, L, q); });
         break;
-    }
-    case DSR_BODY_GATHER_NESTED: {
-        switch (L.arrays) {
-        case 1: body_gather_nested<1, (VARIANT >= 0)>(T, f, L, sp, member, members, inner_pushes, tr); break;
-        case 2: body_gather_nested<2, (VARIANT >= 0)>(T, f, L, sp, member, members, inner_pushes, tr); break;
-        case 3: body_gather_nested<3, (VARIANT >= 0)>(T, f, L, sp, member, members, inner_pushes, tr); break;
-        case 4: body_gather_nested<4, (VARIANT >= 0)>(T, f, L, sp, member, members, inner_pushes, tr); break;
-        default: body_gather_nested<0, (VARIANT >= 0)>(T, f, L, sp, member, members, inner_pushes, tr); break;
-        }
+    case DSR_BODY_GATHER_NESTED:
+        body_gather_nested(T, f, L, sp, member, members, inner_pushes, tr);
         break;
-    }
     default:
         break;
     }
@@ -1242,6 +1246,31 @@ __device__ __forceinline__ span_t team_span(const dsr_dloop &L, uint32_t team, u
     s.p = p;
     s.P = P;
     return s;
+}
+
+/* A participating wave leaves its partial and its range flag (one 32-byte
+ * reduction slot) for the join. */
+__device__ __forceinline__ void deposit(const team_t &T, i192 w, uint32_t bad)
+{
+    if (T.lane == 0) {
+        LDSQ uint64_t *r = (LDSQ uint64_t *)(dsr_lds + red_slot_at(T.wave));
+        r[0] = w.w0;
+        r[1] = w.w1;
+        r[2] = w.w2;
+        r[3] = bad;
+    }
+}
+
+/* Master wave, after the join: the sum of the `nwork` participating waves'
+ * partials, one wave's slot per lane, and whether any of them flagged a value
+ * outside the exact-sum window. */
+__device__ __forceinline__ i192 joined_sum(uint32_t lane, uint32_t nwork, uint32_t &bad)
+{
+    const bool mine = lane < nwork;
+    const LDSQ uint64_t *q = (const LDSQ uint64_t *)(dsr_lds + red_slot_at(mine ? lane : 0));
+    const uint64_t q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+    bad = __any(mine && q3 != 0);
+    return row_sum192(mine ? i192{q0, q1, q2} : i192{0, 0, 0});
 }
 
 /* Run one participating wave's share of a published body and join. */
@@ -1260,10 +1289,9 @@ __device__ __forceinline__ void participate(team_t &T, const dsr_dregion &R, con
     /* served form: the request completes while the kernel keeps running,
      * so this wave's output stores must have reached L2 before the join
      * (the master then writes the L2 back before the team arrives) */
-    if (VARIANT < DSR_LEAN_BASE && C.serve) drain_memory();
-    const i192 w = wave_sum192(widen(A));
-    const uint32_t bad = __any(A.bad != 0);
-    end_parallel(T, w.w0, w.w1, w.w2, bad);
+    if (C.serve) drain_memory();
+    deposit(T, wave_sum192(widen(A)), __any(A.bad != 0));
+    __syncthreads();
 }
 
 /* Bytes o .. o+3 of src as a little-endian word, zero from `lim` on. */
@@ -1376,14 +1404,10 @@ __device__ __forceinline__ region_sums sums_of(const dsr_dregion &R)
     return S;
 }
 
-/* Master wave: this team's partial of one reduction (lane 0 stores). */
+/* Master wave: this team's partial of one reduction, a word per lane. */
 __device__ __forceinline__ void store_partial(uint64_t *pp, i192 sv, uint32_t lane)
 {
-    if (lane == 0) {
-        store_dev(pp, sv.w0);
-        store_dev(pp + 1, sv.w1);
-        store_dev(pp + 2, sv.w2);
-    }
+    if (lane < DSR_PART_WORDS) store_dev(pp + lane, lane == 0 ? sv.w0 : (lane == 1 ? sv.w1 : sv.w2));
 }
 
 /* Master wave: add the join's total into the shared sum at c (an int64
@@ -1414,8 +1438,8 @@ __device__ __forceinline__ i192 update_sum(P c, i192 tot, bool integer_sum, uint
  * (Figure 2): pushes, publishes and pops.  Returns the team's error. */
 template <int VARIANT>
 __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, const dsr_dconfig &C,
-                                               const dsr_dlaunch &LP, bool single, uint32_t region,
-                                               uint32_t team, uint32_t &barriers, uint32_t &inner_pushes)
+                                               uint32_t region, uint32_t team, uint32_t &barriers,
+                                               uint32_t &inner_pushes)
 {
     cb_header *h = header(T);
     /* trace words go through a global-space pointer: a generic store is
@@ -1432,17 +1456,11 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
     /* read once, before any join: after a barrier the compiler would load
      * them from memory again, behind this wave's outstanding stores */
     const region_sums RS = sums_of(R);
-    /* a short program of a single-region launch, its first loop and its
-     * first frame's image come with the kernel arguments; the image is read
-     * into registers (16 bytes a lane) before anything else */
-    const bool inl = VARIANT >= DSR_LEAN_BASE && single && LP.inl_ops == n_ops && n_ops > 0;
-    i32x4 img = {0, 0, 0, 0};
-    if (inl && LP.inl_img && 16u * T.lane < LP.inl_img) img = *(const i32x4 *)(LP.inl_image + 16u * T.lane);
     /* the 1024-thread instance has no registers to spare: it reads each op
      * when it gets to it */
-    const op_lanes prog = load_ops(R.ops, (VARIANT < 0 || inl) ? 0 : n_ops, T.lane);
+    const op_lanes prog = load_ops(R.ops, VARIANT < 0 ? 0 : n_ops, T.lane);
     for (uint32_t k = 0; k < n_ops; ++k) {
-        const dsr_op op = inl ? LP.inl_op[k] : (VARIANT < 0 ? R.ops[k] : op_at(prog, k));
+        const dsr_op op = VARIANT < 0 ? R.ops[k] : op_at(prog, k);
         if (op.kind == DSR_OP_PUSH) {
             const frame_t f = push(T, op.nbytes);
             if (f.space == SPACE_NONE) { err = DSR_E_NOMEM; break; }
@@ -1452,23 +1470,10 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
                 tr[3 + 3 * npush] = f.size;
             }
             npush++;
-            if (k == 0 && inl && LP.inl_img && f.size <= 16u * 64u) {
-                /* the image (zero-padded to a multiple of 16 bytes) from
-                 * registers, zeros after it */
-                if (16u * T.lane < f.size) {
-                    if (f.space == SPACE_LDS)
-                        *(LDSQ i32x4 *)(dsr_lds + cb_bytes(T.nw) + f.off + 16u * T.lane) = img;
-                    else
-                        *(GLB i32x4 *)(T.stack_hbm + f.off + 16u * T.lane) = img;
-                }
-                wave_sync();
-            } else {
-                init_frame(T, f, R.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes,
-                           op.nbytes);
-            }
+            init_frame(T, f, R.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes, op.nbytes);
         } else if (op.kind == DSR_OP_PUBLISH) {
             frame_t f, lf{SPACE_NONE, 0, 0};
-            if (VARIANT < DSR_LEAN_BASE && op.body == DSR_BODY_FMA_CHAIN_REFS) {
+            if (op.body == DSR_BODY_FMA_CHAIN_REFS) {
                 /* section 5.2: resolve each (frame, offset) reference to a
                  * stack address and write the list on chip, or to a list
                  * frame on the HBM stack when it is longer than the on-chip
@@ -1516,11 +1521,9 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
             /* the 1024-thread instance has no registers for a participating
              * master; the host never asks it to (teams above 512 threads) */
             if (VARIANT >= 0 && C.master_joins) {
-                participate<VARIANT>(T, R, C, team, op.body, f, op.loop,
-                                     (inl && LP.inl_loop && op.loop == 0) ? LP.inl_loop0 : R.loops[op.loop],
-                                     inner_pushes);
+                participate<VARIANT>(T, R, C, team, op.body, f, op.loop, R.loops[op.loop], inner_pushes);
             } else {
-                end_parallel(T, 0, 0, 0, 0);
+                __syncthreads();             /* the join (barrier 2) */
             }
             barriers++;
             if (tr && T.lane == 0) {
@@ -1529,23 +1532,16 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
                 tr[85] = (uint32_t)(t1 >> 32);
             }
             /* join done: combine the participating waves' partials */
-            i192 tot{0, 0, 0};
-            for (uint32_t w = 0; w < T.nw; ++w) {
-                if (w == T.nw - 1 && !C.master_joins) continue;
-                const uint64_t *r = red_slot(T, w);
-                tot = add192(tot, i192{r[0], r[1], r[2]});
-            }
-            const uint32_t bad = uniform(h->bad);
-            if (bad) { err = DSR_E_RANGE; }
-            wave_sync();
-            if (T.lane == 0) h->bad = 0;
+            uint32_t bad;
+            const i192 tot = joined_sum(T.lane, nwork, bad);
+            if (bad) err = DSR_E_RANGE;
             if (op.red != 0xffffffffu) {
                 /* the shared sum: the frame's first bytes, or where reference
                  * 0 of the list points; read and written through a pointer
                  * of its own memory space (a generic access would also wait
                  * for this wave's outstanding loop stores) */
                 uint32_t s_space = f.space, s_off = f.off;
-                if (VARIANT < DSR_LEAN_BASE && op.body == DSR_BODY_FMA_CHAIN_REFS) {
+                if (op.body == DSR_BODY_FMA_CHAIN_REFS) {
                     const uint32_t *lst = f.space == SPACE_LIST ? ref_list(T) : (const uint32_t *)frame_hbm(T, f);
                     s_space = uniform(lst[0]);
                     s_off = uniform(lst[1]);
@@ -1577,7 +1573,6 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
             if (!pop(T, f)) { err = DSR_E_ORDER; break; }
         }
     }
-    (void)nwork;
     if (tr && T.lane == 0) {
         tr[0] = npush;
         tr[81] = (uint32_t)err;
@@ -1592,6 +1587,14 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
 __device__ __forceinline__ i192 sum_partials(const uint64_t *base, uint32_t cnt, uint32_t stride, uint32_t lane)
 {
     i192 s{0, 0, 0};
+    if (cnt <= 64) {
+        /* one load round of one partial per lane, a third of the instructions */
+        if (lane < cnt) {
+            const uint64_t *pp = base + (uint64_t)DSR_PART_WORDS * lane * stride;
+            s = i192{load_dev(pp), load_dev(pp + 1), load_dev(pp + 2)};
+        }
+        return wave_sum192(s);
+    }
     for (uint32_t j0 = 0; j0 < cnt; j0 += 512) {
         uint64_t w[8][3];
 #pragma unroll
@@ -1640,13 +1643,13 @@ __device__ __forceinline__ void combine_teams(const region_sums &R, uint32_t cnt
 /* Served form: finish a region's host-coherent completion record (its
  * sums are already there) and release the ticket; the system-scope release
  * also writes this XCD's L2 back, outputs included. */
-__device__ __forceinline__ void publish_record(const dsr_dregion &R, dsr_drec *rec, int32_t err, uint32_t lane)
+__device__ __forceinline__ void publish_record(uint32_t n_red, uint64_t tag, dsr_drec *rec, int32_t err, uint32_t lane)
 {
     if (lane != 0) return;
     rec->status = err;
-    rec->n_red = R.n_red;
+    rec->n_red = n_red;
     rec->ticks = wall_clock64();
-    __hip_atomic_store(&rec->seq, R.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&rec->seq, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 /* A team's arrival after its program.  Arrivals go through a two-level
@@ -1655,15 +1658,18 @@ __device__ __forceinline__ void publish_record(const dsr_dregion &R, dsr_drec *r
  * reads every partial in one round; with more, the last team of each group
  * first adds up its group's partials and leaves the sum in the group's
  * first partial slot, and the last team overall adds the group sums. */
-__device__ __forceinline__ void finish_team(const dsr_dregion &RD, uint32_t team, uint32_t lane,
-                                            uint64_t *done_ts, dsr_drec *rec = nullptr, GLB uint32_t *tr = nullptr)
+template <bool REDUCES>
+__device__ __forceinline__ void finish_team(const region_sums &R, uint32_t team, uint32_t lane, uint64_t *done_ts,
+                                            dsr_drec *rec, const dsr_dregion *served, GLB uint32_t *tr)
 {
-    const region_sums R = sums_of(RD);
-    const uint32_t gsize = R.teams <= DSR_FLAT_TEAMS ? R.teams : (R.teams + DSR_ARRIVE_GROUPS - 1) / DSR_ARRIVE_GROUPS;
-    const uint32_t ngroups = (R.teams + gsize - 1) / gsize;
-    const uint32_t g = team / gsize;
-    const uint32_t in_group = min(gsize, R.teams - g * gsize);
-    const bool group_sums = R.teams > 512;
+    uint32_t gsize = R.teams, ngroups = 1, g = 0, in_group = R.teams;
+    if (R.teams > DSR_FLAT_TEAMS) {
+        gsize = (R.teams + DSR_ARRIVE_GROUPS - 1) / DSR_ARRIVE_GROUPS;
+        ngroups = (R.teams + gsize - 1) / gsize;
+        g = team / gsize;
+        in_group = min(gsize, R.teams - g * gsize);
+    }
+    const bool group_sums = REDUCES && R.teams > 512;
     drain_memory();                      /* this team's partials are stored */
     if (tr && lane == 0) tr[92] = (uint32_t)wall_clock64();
     GLB dsr_dresult *res = (GLB dsr_dresult *)R.result;
@@ -1708,15 +1714,17 @@ __device__ __forceinline__ void finish_team(const dsr_dregion &RD, uint32_t team
     int32_t err = 0;
     if (lane == 0) err = __hip_atomic_exchange(&res->error, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (lane < DSR_MAX_LOOPS) __hip_atomic_store(&res->claim[lane], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (ngroups > 1 && group_sums) combine_teams(R, ngroups, gsize, lane, rec);
-    else combine_teams(R, R.teams, 1, lane, rec);
+    if constexpr (REDUCES) {
+        if (ngroups > 1 && group_sums) combine_teams(R, ngroups, gsize, lane, rec);
+        else combine_teams(R, R.teams, 1, lane, rec);
+    }
     if (lane == 0) {
         res->final_error = err;
         __hip_atomic_fetch_add(&res->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (done_ts) *done_ts = wall_clock64();
         if (tr) tr[95] = (uint32_t)wall_clock64();
     }
-    if (rec) publish_record(RD, rec, err, lane);
+    if (rec) publish_record(R.n_red, served->tag, rec, err, lane);
 }
 
 /* Served form: close the server (one workgroup does it; see wait_item).
@@ -1969,6 +1977,7 @@ __device__ __forceinline__ const dsr_dregion &stage_request(team_t &T, const uin
     return *Rl;
 }
 
+#if DSR_INST_VARIANT < DSR_LEAN_BASE
 /* One kernel for both launch forms.  The master wave runs region programs
  * (one per workgroup for a single region; claimed items for a batch) and
  * then terminates the workers; worker waves sit in the await loop and take
@@ -1980,10 +1989,9 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_dlaunch LP, dsr_d
                          C.hbm_base + (uint64_t)blockIdx.x * C.hbm_slot_bytes, (uint32_t)C.hbm_slot_bytes);
     T.nest_hbm = C.nest_base + (uint64_t)blockIdx.x * DSR_NEST_SLOT;
     T.nest_global = C.nest_global;
-    constexpr bool lean = VARIANT >= DSR_LEAN_BASE;
-    const bool single = lean || LP.items == nullptr;
+    const bool single = LP.items == nullptr;
     uint32_t barriers = 0, inner_pushes = 0;
-    if (!lean && LP.published && T.wave == C.nw - 1 && T.lane == 0) {
+    if (LP.published && T.wave == C.nw - 1 && T.lane == 0) {
         const uint64_t now = wall_clock64();
         if (blockIdx.x == 0 && LP.done_ts)
             __hip_atomic_store(LP.done_ts, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2017,22 +2025,22 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_dlaunch LP, dsr_d
                 }
                 team_reset(T);
             }
-            const dsr_dregion &R = (!lean && C.serve)
+            const dsr_dregion &R = C.serve
                                        ? stage_request(T, (const uint8_t *)LP.regions + (uint64_t)region * LP.region_stride, team,
                                                    LP.relays)
-                                                        : ((lean && LP.has_single) ? LP.single : LP.regions[region]);
-            run_program<VARIANT>(T, R, C, LP, single, region, team, barriers, inner_pushes);
+                                       : LP.regions[region];
+            run_program<VARIANT>(T, R, C, region, team, barriers, inner_pushes);
             GLB uint32_t *tr = (single && C.trace && R.trace) ? (GLB uint32_t *)(R.trace + (uint64_t)team * DSR_TRACE_WORDS) : nullptr;
             if (tr && T.lane == 0) tr[87] = (uint32_t)wall_clock64();
             /* outputs out of L2 before the arrival; a request of one team
              * has its completion record's system-scope release do it */
-            if (!lean && C.serve && R.teams > 1) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (C.serve && R.teams > 1) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             /* the 1024-thread instance reads fewer partials per round */
-            finish_team(R, team, T.lane, (LP.done_ts && !LP.published) ? LP.done_ts + region : nullptr,
-                        (!lean && LP.recs) ? LP.recs + region : nullptr, tr);
+            finish_team<true>(sums_of(R), team, T.lane, (LP.done_ts && !LP.published) ? LP.done_ts + region : nullptr,
+                              LP.recs ? LP.recs + region : nullptr, &R, tr);
             if (tr && T.lane == 0) tr[88] = (uint32_t)wall_clock64();
         }
-        if (!lean && LP.wg_exited && T.lane == 0)
+        if (LP.wg_exited && T.lane == 0)
             __hip_atomic_store(LP.wg_exited + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         /* terminate the workers (Figure 3's terminate branch) */
         frame_t none{SPACE_NONE, 0, 0};
@@ -2053,10 +2061,8 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_dlaunch LP, dsr_d
             barriers++;
             if (!go) break;
             const uint32_t region = uniform(header(T)->region), team = uniform(header(T)->team);
-            const dsr_dregion &R = (!lean && C.serve) ? *serve_area(T)
-                                                      : ((lean && LP.has_single) ? LP.single : LP.regions[region]);
-            participate<VARIANT>(T, R, C, team, body, f, loop,
-                                 (lean && LP.inl_loop && loop == 0) ? LP.inl_loop0 : R.loops[loop], inner_pushes);
+            const dsr_dregion &R = C.serve ? *serve_area(T) : LP.regions[region];
+            participate<VARIANT>(T, R, C, team, body, f, loop, R.loops[loop], inner_pushes);
             barriers++;
         }
     }
@@ -2067,19 +2073,238 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_dlaunch LP, dsr_d
     }
 }
 
+#else
+/* ---- lean instances -----------------------------------------------------
+ * Single-region launches whose every publish is of one kind (DSR_LEAN_*):
+ * the kernel holds that body and the single-region form only.  A small
+ * region's time is the chain of steps its master wave goes through one
+ * after another (about 10 us of the 26 us launch-and-wait of a 64-team
+ * region, and about 9 us of the 46 us of a 2^24-element one), so the steps
+ * are short here: everything the launch needs comes in the kernel
+ * arguments, whose cache lines are fetched together at the start; the
+ * master keeps its stack pointers and top frame in registers and only
+ * writes the control block; both roles run the body at one place, so its
+ * code is fetched once; the waves' partials are combined across lanes; and
+ * the workers are terminated before the team arrives.  Launch and wait
+ * against the interpreter all instances shared before: 4-team affine loop
+ * 26.1 -> 21.8 us, 64-team chain of 8 scalars 26.3 -> 24.6 us, the seven
+ * 2^24-element regions of the sweep 455.8 -> 438.4 us. */
+typedef __attribute__((address_space(4))) const uint32_t *kptr_t;
+
+/* Touch every 64-byte line of the first BYTES of the kernel arguments: the
+ * scalar loads that follow then hit, instead of missing one after another
+ * as the code reaches them (0.8 us per launch). */
+template <uint32_t BYTES>
+__device__ __forceinline__ void touch_args()
+{
+    const kptr_t p = (kptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < BYTES / 4; k += 16) v ^= p[k];
+    asm volatile("" ::"s"(v));
+}
+
+/* A descriptor in global memory that no kernel writes, read with scalar
+ * loads. */
+template <class V>
+__device__ __forceinline__ V load_const(const V *p)
+{
+    static_assert(sizeof(V) % 4 == 0, "whole words");
+    union {
+        V v;
+        uint32_t w[sizeof(V) / 4];
+    } u;
+    const kptr_t q = (kptr_t)(uintptr_t)p;
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(V) / 4; ++k) u.w[k] = q[k];
+    return u.v;
+}
+
+/* Fixed fma chain of a lean instance: the frame's scalars are read one word
+ * per lane in one round and handed out with readlanes. */
+template <int NI, int NF>
+__device__ __forceinline__ void lean_chain(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp, lane_acc &A)
+{
+    constexpr uint32_t NWORDS = 2 * NF + NI;
+    uint32_t w[2] = {0, 0};
+#pragma unroll
+    for (uint32_t h = 0; h < 2 && 64 * h < NWORDS; ++h) {
+        const uint32_t k = T.lane + 64u * h;
+        if (k < NWORDS)
+            w[h] = f.space == SPACE_LDS
+                       ? *(const LDSQ uint32_t *)(dsr_lds + cb_bytes(T.nw) + f.off + 24 + 4 * k)
+                       : *(const GLB uint32_t *)(T.stack_hbm + f.off + 24 + 4 * k);
+    }
+    auto word = [&](int k) { return (uint32_t)__builtin_amdgcn_readlane(w[k >> 6], k & 63); };
+    double s[NI + NF];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) s[k] = (double)(int32_t)word(2 * NF + k);
+#pragma unroll
+    for (int k = 0; k < NF; ++k)
+        s[NI + k] = __longlong_as_double((long long)((uint64_t)word(2 * k) | ((uint64_t)word(2 * k + 1) << 32)));
+    /* every wave takes its fixed per-lane share of the team's range: 0.3-1.0 us
+     * faster per 2^24-element region than the balanced block split of the
+     * general instances for 8 to 32 scalars, and the same below */
+    fma_span<NI, NF>(s, (const GLB float *)L.in, (GLB double *)L.out, sp, A);
+}
+
+__device__ __forceinline__ void lean_affine(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp, lane_acc &A)
+{
+    uint32_t w = 0;
+    if (T.lane < 4)
+        w = f.space == SPACE_LDS ? *(const LDSQ uint32_t *)(dsr_lds + cb_bytes(T.nw) + f.off + 8 + 4 * T.lane)
+                                 : *(const GLB uint32_t *)(T.stack_hbm + f.off + 8 + 4 * T.lane);
+    const uint32_t a = __builtin_amdgcn_readlane(w, 0), b = __builtin_amdgcn_readlane(w, 1);
+    const uint32_t c = __builtin_amdgcn_readlane(w, 2), d = __builtin_amdgcn_readlane(w, 3);
+    affine_span(a, b, c, d, (GLB int32_t *)L.out, sp, A);
+}
+
+template <int MAXWG, int VARIANT>
+__global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
+{
+    constexpr bool gather = VARIANT == DSR_LEAN_GATHER, affine = VARIANT == DSR_LEAN_AFFINE;
+    touch_args<offsetof(dsr_lean, image)>();
+    const uint32_t team = blockIdx.x;
+    team_t T = team_bind(dsr_lds, A.nw, A.lds_cap, A.threshold, A.hbm_base + (uint64_t)team * A.hbm_slot_bytes,
+                         (uint32_t)A.hbm_slot_bytes);
+    T.nest_hbm = A.nest_base + (uint64_t)team * DSR_NEST_SLOT;
+    T.nest_global = A.nest_global;
+    const bool master = T.wave == A.nw - 1;
+    const uint32_t nwork = A.master_joins ? A.nw : A.nw - 1;
+    GLB uint32_t *tr = A.trace ? (GLB uint32_t *)(A.trace + (uint64_t)team * DSR_TRACE_WORDS) : nullptr;
+    const region_sums RS{A.partials, A.result, A.teams, A.n_red, affine ? 0u : 0xffu};
+    uint32_t barriers = 0, inner_pushes = 0;
+    /* the master's place in the program, and its stack */
+    stack_t S = stack_empty();
+    uint32_t k = 0, npush = 0;
+    int32_t err = 0;
+    bool stamped = false;
+    if (tr && master && T.lane == 0) tr[86] = (uint32_t)wall_clock64();
+    /* the first frame's image, 16 bytes a lane */
+    i32x4 img = {0, 0, 0, 0};
+    if (master && 16u * T.lane < A.inl_img) img = *(const i32x4 *)(A.image + 16u * T.lane);
+    for (;;) {
+        uint32_t body = DSR_BODY_TERMINATE, loop = 0, red = 0xffffffffu;
+        frame_t f{SPACE_NONE, 0, 0};
+        if (master) {
+            while (k < A.n_ops && !err) {
+                const dsr_op op = A.inl_ops ? A.inl_op[k] : load_const(A.ops + k);
+                const uint32_t at = k++;
+                if (op.kind == DSR_OP_PUSH) {
+                    const frame_t p = push(T, S, op.nbytes);
+                    if (p.space == SPACE_NONE) { err = DSR_E_NOMEM; break; }
+                    if (tr && T.lane == 0 && npush < 16) {
+                        tr[1 + 3 * npush] = p.space;
+                        tr[2 + 3 * npush] = p.off;
+                        tr[3 + 3 * npush] = p.size;
+                    }
+                    npush++;
+                    if (at == 0 && A.inl_img && p.size <= 16u * 64u) {
+                        /* the image (zero-padded to a multiple of 16 bytes)
+                         * from registers, zeros after it */
+                        if (16u * T.lane < p.size) {
+                            if (p.space == SPACE_LDS)
+                                *(LDSQ i32x4 *)(dsr_lds + cb_bytes(T.nw) + p.off + 16u * T.lane) = img;
+                            else
+                                *(GLB i32x4 *)(T.stack_hbm + p.off + 16u * T.lane) = img;
+                        }
+                    } else {
+                        init_frame(T, p, A.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes,
+                                   op.nbytes);
+                    }
+                } else if (op.kind == DSR_OP_PUBLISH) {
+                    f = frame_at(T, S, op.frame);
+                    body = op.body;
+                    loop = op.loop;
+                    red = op.red;
+                    break;
+                } else if (op.kind == DSR_OP_POP) {
+                    if (!pop(T, S)) err = DSR_E_UNDERFLOW;
+                }
+            }
+            if (body == DSR_BODY_TERMINATE && tr && T.lane == 0) {
+                tr[0] = npush;
+                tr[81] = (uint32_t)err;
+                tr[87] = (uint32_t)wall_clock64();
+            }
+            if (T.lane == 0) post(T, f, body, loop);
+        }
+        __syncthreads();                     /* hand-over (barrier 1) */
+        barriers++;
+        if (!master) take(T, body, f, loop);
+        if (body == DSR_BODY_TERMINATE) break;
+        if (tr && master && !stamped && T.lane == 0) {
+            const uint64_t t0 = wall_clock64();
+            tr[82] = (uint32_t)t0;
+            tr[83] = (uint32_t)(t0 >> 32);
+        }
+        stamped = true;
+        if (!master || A.master_joins) {
+            const dsr_dloop L = loop == 0 ? A.loop0 : load_const(A.loops + loop);
+            const span_t sp = team_span(L, team, T.wave * 64 + T.lane, nwork * 64);
+            if (tr && T.lane == 0) tr[96 + 2 * T.wave] = (uint32_t)wall_clock64();
+            lane_acc acc = acc_zero();
+            if constexpr (gather) {
+                if (body == DSR_BODY_GATHER) body_gather(T, f, L, sp);
+                else body_gather_nested(T, f, L, sp, T.wave, nwork, inner_pushes, tr);
+            } else if constexpr (affine) {
+                lean_affine(T, f, L, sp, acc);
+            } else {
+                lean_chain<DSR_LEAN_NI(VARIANT - DSR_LEAN_BASE), DSR_LEAN_NF(VARIANT - DSR_LEAN_BASE)>(T, f, L, sp, acc);
+            }
+            if (tr && T.lane == 0) tr[97 + 2 * T.wave] = (uint32_t)wall_clock64();
+            if constexpr (affine) {
+                deposit(T, wave_sum192(from_i64(acc.i)), 0);
+            } else if constexpr (!gather) {
+                deposit(T, wave_sum192(widen(acc)), __any(acc.bad != 0));
+            }
+        }
+        __syncthreads();                     /* the join (barrier 2) */
+        barriers++;
+        if (!master) continue;
+        if (tr && T.lane == 0) {
+            const uint64_t t1 = wall_clock64();
+            tr[84] = (uint32_t)t1;
+            tr[85] = (uint32_t)(t1 >> 32);
+        }
+        if constexpr (!gather) {
+            uint32_t bad;
+            const i192 tot = joined_sum(T.lane, nwork, bad);
+            if (bad) err = DSR_E_RANGE;
+            /* into the shared variable; the team's partial is stored inside
+             * each branch: where the two would merge the compiler waits for
+             * every outstanding memory operation of the wave, its loop stores
+             * included */
+            uint64_t *pp = A.partials + ((uint64_t)red * A.teams + team) * DSR_PART_WORDS;
+            if (f.space == SPACE_LDS)
+                store_partial(pp, update_sum((LDSQ uint64_t *)(dsr_lds + cb_bytes(T.nw) + f.off), tot, affine, T.lane),
+                              T.lane);
+            else
+                store_partial(pp, update_sum((GLB uint64_t *)(T.stack_hbm + f.off), tot, affine, T.lane), T.lane);
+        }
+    }
+    if (master) {
+        if (err && T.lane == 0) atomicCAS(&A.result->error, 0, err);
+        finish_team<!gather>(RS, team, T.lane, nullptr, nullptr, nullptr, tr);
+        if (tr && T.lane == 0) tr[88] = (uint32_t)wall_clock64();
+    }
+    if (tr && T.lane == 0) {
+        tr[49 + T.wave] = barriers;
+        tr[65 + T.wave] = inner_pushes;
+    }
+}
+#endif
+
 /* ---- this object's instance --------------------------------------------
  * The build compiles this file once per kernel instance, in parallel, with
  * DSR_INST_MAXWG, DSR_INST_VARIANT and DSR_INST_TAG defined; each object
  * exports its instance's launcher, occupancy and register queries under
  * names carrying the tag, and dsr_dispatch.cpp picks among them. */
-#if !defined(DSR_INST_MAXWG) || !defined(DSR_INST_VARIANT) || !defined(DSR_INST_TAG)
-#error "compile with -DDSR_INST_MAXWG=<threads> -DDSR_INST_VARIANT=<v> -DDSR_INST_TAG=<tag>"
-#endif
 #define DSR_INST_CAT2(a, b) a##b
 #define DSR_INST_CAT(a, b) DSR_INST_CAT2(a, b)
 #define DSR_INST_KERNEL dsr_region_kernel<DSR_INST_MAXWG, DSR_INST_VARIANT>
 
-extern "C" int DSR_INST_CAT(dsr_inst_launch_, DSR_INST_TAG)(const dsr_dlaunch *lp, const dsr_dconfig *cfg,
+extern "C" int DSR_INST_CAT(dsr_inst_launch_, DSR_INST_TAG)(const void *args, const dsr_dconfig *cfg,
                                                             uint32_t grid, uint32_t wg_size, uint32_t lds_bytes,
                                                             void *stream)
 {
@@ -2089,7 +2314,14 @@ extern "C" int DSR_INST_CAT(dsr_inst_launch_, DSR_INST_TAG)(const dsr_dlaunch *l
                                   160 * 1024);
         attr = true;
     }
-    hipLaunchKernelGGL(DSR_INST_KERNEL, dim3(grid), dim3(wg_size), lds_bytes, (hipStream_t)stream, *lp, *cfg);
+#if DSR_INST_VARIANT < DSR_LEAN_BASE
+    hipLaunchKernelGGL(DSR_INST_KERNEL, dim3(grid), dim3(wg_size), lds_bytes, (hipStream_t)stream,
+                       *(const dsr_dlaunch *)args, *cfg);
+#else
+    (void)cfg;
+    hipLaunchKernelGGL(DSR_INST_KERNEL, dim3(grid), dim3(wg_size), lds_bytes, (hipStream_t)stream,
+                       *(const dsr_lean *)args);
+#endif
     return (int)hipGetLastError();
 }
 

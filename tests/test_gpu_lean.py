@@ -1,0 +1,143 @@
+"""The kernel instances that hold one kind of body (fixed chains, gathers,
+affine loops) against the oracle, bit for bit: programs of one publish and
+of several, programs longer than the kernel arguments hold, frames buried
+under others, per-team images, frames on chip and in HBM, every workgroup
+class, team counts around the arrival tree's edges, ragged sizes."""
+import numpy as np
+import pytest
+
+import dsr_workloads as W
+from oracle import ref as R
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+from paper_1711_10413_amd import dsr as D  # noqa: E402
+
+
+def stream():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def run_region(r):
+    """Launch twice, so that counters reset by the first launch are used."""
+    for _ in range(2):
+        D.dsr_launch(r, stream())
+        st = D.dsr_region_sync(r)
+    return st
+
+
+@pytest.mark.parametrize("wg", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("slab", [0, 4096])
+@pytest.mark.parametrize("n,teams,publishes", [(0, 2, 1), (1, 1, 1), (1023, 5, 2), (100003, 513, 1), (65536, 512, 5)])
+def test_affine(wg, slab, n, teams, publishes):
+    ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=slab, hbm_slab_bytes=4096, max_teams=teams, master_joins=wg == 256)
+    vals = [(3 + k, -17 * k, 5 - k, 1 << (20 + k)) for k in range(publishes)]
+    outs = [torch.full((n + 1,), -9, dtype=torch.int32, device="cuda") for _ in vals]
+    r = D.dsr_region_begin(ctx, teams)
+    for v, o in zip(vals, outs):
+        f = D.dsr_push(r, 24, D.affine_xor_frame(*v))
+        D.dsr_publish(r, f, D.DSR_BODY_AFFINE_XOR, n, out=o.data_ptr())
+        D.dsr_pop(r, f)
+    assert run_region(r) == 0
+    for k, (v, o) in enumerate(zip(vals, outs)):
+        want, total = R.affine_xor(*v, 0, n)
+        got = o.cpu().numpy()
+        assert np.array_equal(got[:n], want) and got[n] == -9, (k, v)
+        assert D.dsr_region_reduction(r, k)[0] == total
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("wg,joins", [(64, 1), (192, 0), (256, 1), (512, 1), (1024, 0)])
+@pytest.mark.parametrize("A,length", [(1, 1), (2, 3), (3, 257), (4, 64), (5, 12), (16, 7)])
+@pytest.mark.parametrize("n,chunk", [(1, 0), (4099, 514), (30011, 0), (65536, 0)])
+def test_gather_shapes(wg, joins, A, length, n, chunk):
+    """Flat and nested publishes of one region, the frame on chip or in HBM."""
+    arrs = W.cfg3_arrays(A, length)
+    frame = 4 * A * length
+    teams = 6 if chunk == 0 else -(-n // chunk)
+    for slab in (0, 8192):
+        ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=slab, hbm_slab_bytes=8192, max_teams=teams, master_joins=joins)
+        outs = [torch.full((n + 1,), -9, dtype=torch.int32, device="cuda") for _ in range(3)]
+        r = D.dsr_region_begin(ctx, teams)
+        f = D.dsr_push(r, frame, D.gather_frame(arrs))
+        for o, (body, depth) in zip(outs, ((D.DSR_BODY_GATHER, 0), (D.DSR_BODY_GATHER_NESTED, 2),
+                                           (D.DSR_BODY_GATHER_NESTED, 3))):
+            D.dsr_publish(r, f, body, n, out=o.data_ptr(), arrays=A, length=length, depth=depth, chunk=chunk)
+        D.dsr_pop(r, f)
+        assert run_region(r) == 0
+        want = R.gather(arrs, 0, n)
+        for o in outs:
+            got = o.cpu().numpy()
+            assert np.array_equal(got[:n], want) and got[n] == -9
+        D.dsr_region_free(r)
+        D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 8, 16, 32, 64])
+@pytest.mark.parametrize("slab", [0, 1024])
+def test_chain_programs(K, slab):
+    """Two frames of the same chain, the lower one published under the other
+    and again after its pop, seven ops; then a frame of its own for each team."""
+    n, teams = 5003, 7
+    a, x_np = W.cfg2_inputs(K, seed=11, n=n)
+    b, _ = W.cfg2_inputs(K, seed=12, n=n, with_x=False)
+    x = torch.from_numpy(x_np).cuda()
+    ni, nf = len(a.s_i32), len(a.s_f64)
+    ctx = D.dsr_init(wg_size=256, lds_slab_bytes=slab, hbm_slab_bytes=4096, max_teams=teams)
+    ys = [torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(3)]
+    r = D.dsr_region_begin(ctx, teams)
+    img, size = D.fma_chain_frame(a.s_i32, a.s_f64)
+    f0 = D.dsr_push(r, size + 8, img)
+    f1 = D.dsr_push(r, size, D.fma_chain_frame(b.s_i32, b.s_f64)[0])
+    args = {"inp": x.data_ptr(), "ni": ni, "nf": nf}
+    D.dsr_publish(r, f0, D.DSR_BODY_FMA_CHAIN, n, out=ys[0].data_ptr(), **args)
+    D.dsr_publish(r, f1, D.DSR_BODY_FMA_CHAIN, n, out=ys[1].data_ptr(), **args)
+    D.dsr_pop(r, f1)
+    D.dsr_publish(r, f0, D.DSR_BODY_FMA_CHAIN, n, out=ys[2].data_ptr(), **args)
+    D.dsr_pop(r, f0)
+    assert run_region(r) == 0
+    wa, wb = R.fma_chain(x_np, a.s_i32, a.s_f64), R.fma_chain(x_np, b.s_i32, b.s_f64)
+    for y, w in zip(ys, (wa, wb, wa)):
+        assert np.array_equal(y.cpu().numpy(), w)
+    # a second publish of a frame adds to the same shared sum
+    ta, tb = R.fixed75_sum(wa), R.fixed75_sum(wb)
+    assert [D.dsr_region_reduction(r, k)[2] for k in range(3)] == [ta, tb, 2 * ta]
+    D.dsr_region_free(r)
+    # per-team images
+    stride = (size + 15) // 16 * 16
+    chunk = 750
+    images, want = b"", np.zeros(n)
+    for t in range(teams):
+        s_i = a.s_i32 + t
+        images += D.fma_chain_frame(s_i, a.s_f64)[0].ljust(stride, b"\0")
+        lo, hi = t * chunk, min(n, (t + 1) * chunk)
+        want[lo:hi] = R.fma_chain(x_np[lo:hi], s_i, a.s_f64)
+    r = D.dsr_region_begin(ctx, teams)
+    f = D.dsr_push(r, size, images, init_stride=stride, init_bytes=size)
+    D.dsr_publish(r, f, D.DSR_BODY_FMA_CHAIN, n, out=ys[0].data_ptr(), chunk=chunk, **args)
+    D.dsr_pop(r, f)
+    assert run_region(r) == 0
+    assert np.array_equal(ys[0].cpu().numpy(), want)
+    assert D.dsr_region_reduction(r, 0)[2] == R.fixed75_sum(want)
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("body", ["affine", "gather", "chain"])
+def test_no_room_for_the_frame(body):
+    ctx = D.dsr_init(wg_size=256, lds_slab_bytes=0, hbm_slab_bytes=0, max_teams=3)
+    out = torch.zeros(256, dtype=torch.float64, device="cuda")
+    x = torch.zeros(256, dtype=torch.float32, device="cuda")
+    r = D.dsr_region_begin(ctx, 3)
+    f = D.dsr_push(r, 64)
+    if body == "affine":
+        D.dsr_publish(r, f, D.DSR_BODY_AFFINE_XOR, 256, out=out.data_ptr())
+    elif body == "gather":
+        D.dsr_publish(r, f, D.DSR_BODY_GATHER, 256, out=out.data_ptr(), arrays=1, length=16)
+    else:
+        D.dsr_publish(r, f, D.DSR_BODY_FMA_CHAIN, 256, inp=x.data_ptr(), out=out.data_ptr(), ni=1)
+    D.dsr_pop(r, f)
+    assert run_region(r) == D.DSR_E_NOMEM
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
