@@ -67,9 +67,11 @@ namespace dsr {
 
 /* SPACE_LIST names the on-chip reference list (a published list only);
  * SPACE_NEST_LDS / SPACE_NEST_HBM the on-chip and global parts of the
- * nested members' stacks. */
+ * nested members' stacks.  A published frame in SPACE_IMAGE has its place on
+ * the HBM stack, but nothing in its region writes to it and its bytes are
+ * read where its initial image lies (`off` from team_t::image). */
 enum : uint32_t { SPACE_LDS = 0, SPACE_HBM = 1, SPACE_NONE = 2, SPACE_LIST = 3, SPACE_NEST_LDS = 4,
-                  SPACE_NEST_HBM = 5 };
+                  SPACE_NEST_HBM = 5, SPACE_IMAGE = 6 };
 
 struct frame_t {
     uint32_t space;
@@ -114,6 +116,7 @@ struct team_t {
     uint32_t lane;
     uint8_t *nest_hbm;   /* this team's slot of the nested members' global stacks */
     uint32_t nest_global; /* 1: nested frames skip the on-chip stacks      */
+    const uint8_t *image; /* the region's initial images (SPACE_IMAGE)      */
 };
 
 __device__ inline uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -166,6 +169,7 @@ __device__ inline team_t team_bind(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
     T.lane = threadIdx.x & 63u;
     T.nest_hbm = nullptr;
     T.nest_global = 0;
+    T.image = nullptr;
     return T;
 }
 
@@ -287,16 +291,35 @@ __device__ inline bool await(team_t &T, uint32_t *body, frame_t *f, uint32_t *lo
 struct stack_t {
     uint32_t sp_lds, sp_hbm, nframes;
     frame_t top;
+    uint32_t top_image;  /* 1 + offset / 16 of the image the top frame is read
+                            from (SPACE_IMAGE), 0: the frame holds its bytes */
 };
 
-__device__ inline stack_t stack_empty() { return stack_t{0, 0, 0, frame_t{SPACE_NONE, 0, 0}}; }
+__device__ inline stack_t stack_empty() { return stack_t{0, 0, 0, frame_t{SPACE_NONE, 0, 0}, 0}; }
 
-/* Live frame `depth` (0 = bottom). */
+/* Live frame `depth` (0 = bottom), as it is published. */
 __device__ inline frame_t frame_at(const team_t &T, const stack_t &S, uint32_t depth)
 {
-    if (depth + 1 == S.nframes) return S.top;
-    const uint32_t *ft = frame_table(T) + 4 * depth;
-    return frame_t{uniform(ft[0]), uniform(ft[1]), uniform(ft[2])};
+    frame_t f = S.top;
+    uint32_t image = S.top_image;
+    if (depth + 1 != S.nframes) {
+        const uint32_t *ft = frame_table(T) + 4 * depth;
+        f = frame_t{uniform(ft[0]), uniform(ft[1]), uniform(ft[2])};
+        image = uniform(ft[3]);
+    }
+    if (image) {
+        f.space = SPACE_IMAGE;
+        f.off = (image - 1) * DSR_ALIGN;
+    }
+    return f;
+}
+
+/* Master wave: the top frame, on the HBM stack and never written, is read from
+ * its image at `off` (a multiple of 16 below 2^32) from here on. */
+__device__ inline void read_in_place(const team_t &T, stack_t &S, uint32_t off)
+{
+    S.top_image = 1 + off / DSR_ALIGN;
+    if (T.lane == 0) frame_table(T)[4 * (S.nframes - 1) + 3] = S.top_image;
 }
 
 __device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes)
@@ -313,6 +336,7 @@ __device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes)
     if (T.lane == 0) *(uint4 *)(frame_table(T) + 4 * S.nframes) = make_uint4(f.space, f.off, f.size, 0);
     S.nframes++;
     S.top = f;
+    S.top_image = 0;
     return f;
 }
 
@@ -325,6 +349,7 @@ __device__ inline bool pop(const team_t &T, stack_t &S)
     if (S.nframes) {
         const uint32_t *ft = frame_table(T) + 4 * (S.nframes - 1);
         S.top = frame_t{uniform(ft[0]), uniform(ft[1]), uniform(ft[2])};
+        S.top_image = uniform(ft[3]);
     }
     return true;
 }

@@ -578,6 +578,8 @@ static int launch_single(const dsr_region *r, const dsr_dregion &R, const dsr_dr
     A.inl_ops = r->ops.size() <= DSR_INLINE_OPS ? 1u : 0u;
     if (A.inl_ops) std::memcpy(A.inl_op, r->ops.data(), r->ops.size() * sizeof(dsr_op));
     A.inl_img = 0;
+    A.init_in_place = r->init.size() <= 0xFFFFFFFFull ? 1u : 0u;
+    A.pad = 0;
     const dsr_op &op = r->ops[0];
     if (op.kind == DSR_OP_PUSH && op.init_stride == 0 && op.init_bytes > 0 && op.init_bytes <= DSR_INLINE_IMG) {
         const uint32_t padded = (op.init_bytes + 15u) & ~15u;

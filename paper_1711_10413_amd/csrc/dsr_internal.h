@@ -184,6 +184,8 @@ struct dsr_lean {
     uint32_t inl_ops;          /* 1: the ops are in inl_op (0: read them from memory) */
     uint32_t inl_img;          /* image bytes held in `image` (a multiple of
                                   16, zero-padded; 0: none)                 */
+    uint32_t init_in_place;    /* 1: the images lie within 2^32 bytes of `init` */
+    uint32_t pad;
     dsr_dloop loop0;
     dsr_op inl_op[DSR_INLINE_OPS];
     uint8_t image[DSR_INLINE_IMG];

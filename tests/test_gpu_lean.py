@@ -141,3 +141,42 @@ def test_no_room_for_the_frame(body):
     assert run_region(r) == D.DSR_E_NOMEM
     D.dsr_region_free(r)
     D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("depth", [0, 2, 3])
+@pytest.mark.parametrize("A,length", [(1, 300), (2, 1001), (3, 4096)])
+def test_gather_frames_read_in_place(depth, A, length):
+    """HBM frames whose image covers them are read where the image lies: one
+    image for all teams, one per team, under another frame and after its pop;
+    a frame longer than its image still reads as zeros past it."""
+    n, teams, chunk = 20011, 5, 4004
+    arrs = W.cfg3_arrays(A, length)
+    frame = 4 * A * length
+    stride = (frame + 15) // 16 * 16
+    body = D.DSR_BODY_GATHER_NESTED if depth else D.DSR_BODY_GATHER
+    ctx = D.dsr_init(wg_size=256, lds_slab_bytes=0, hbm_slab_bytes=4 * stride, max_teams=teams, flags=D.DSR_F_TRACE)
+    outs = [torch.full((n,), -9, dtype=torch.int32, device="cuda") for _ in range(4)]
+    per_team = [[a + 7 * t for a in arrs] for t in range(teams)]
+    cut = [np.concatenate([arrs[0]] + arrs[1:]).copy()]
+    cut[0][A * length - length // 2:] = 0
+    args = {"arrays": A, "length": length, "depth": depth, "chunk": chunk}
+    r = D.dsr_region_begin(ctx, teams)
+    f0 = D.dsr_push(r, frame, D.gather_frame(arrs))
+    f1 = D.dsr_push(r, frame, b"".join(D.gather_frame(p).ljust(stride, b"\0") for p in per_team), init_stride=stride,
+                    init_bytes=frame)
+    f2 = D.dsr_push(r, frame, D.gather_frame(arrs)[:frame - 4 * (length // 2)])
+    for f, o in ((f1, outs[0]), (f2, outs[1]), (f0, outs[2])):
+        D.dsr_publish(r, f, body, n, out=o.data_ptr(), **args)
+    D.dsr_pop(r, f2)
+    D.dsr_pop(r, f1)
+    D.dsr_publish(r, f0, body, n, out=outs[3].data_ptr(), **args)
+    D.dsr_pop(r, f0)
+    assert run_region(r) == 0
+    whole = R.gather(arrs, 0, n)
+    own = np.concatenate([R.gather(per_team[t], t * chunk, min(n, (t + 1) * chunk)) for t in range(teams)])
+    short = R.gather([cut[0][j * length:(j + 1) * length] for j in range(A)], 0, n)
+    for o, want in zip(outs, (own, short, whole, whole)):
+        assert np.array_equal(o.cpu().numpy(), want)
+    assert D.dsr_region_trace(r, 1)["placements"] == [("hbm", k * stride, stride) for k in range(3)]
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
