@@ -511,9 +511,7 @@ typedef struct dsr_done {
 } dsr_done;
 
 /* Launch the server kernel on its own stream (not in the paper).  Regions submitted later must
- * belong to `ctx` and use one of the bodies compiled into the server (all
- * bodies; fixed-length fma chains up to 8+8 scalars, longer ones through the
- * run-time loop).  The server's kernel stays resident until it closes, and
+ * belong to `ctx` (every body may be used).  The server's kernel stays resident until it closes, and
  * other device work shares the CUs with it: the runtime's copies
  * (host<->device, staged or not) and fills run as kernels, so a grid that
  * holds every workgroup slot of the device (an explicit grid at the
@@ -663,13 +661,13 @@ int dsr_occupancy_model(const dsr_hw_model *hw, uint32_t threads_per_team,
 
 /* The model for this runtime's region kernel on the context's device: the
  * kernel's registers per thread (compiled variant `variant` of the
- * context's workgroup size: 0..2 for the general instances, which hold
- * fixed fma chains up to 8+8, 16+16 and 32+32 scalars; 10 + k for the lean
- * instance of fixed chain k of (1,0) (1,1) (2,2) (4,4) (8,8) (16,16)
- * (32,32), which a single-region launch of workgroups up to 256 threads
- * runs when every publish of the region is that chain; 17 and 18 for the
- * lean instances of any workgroup size, for regions that publish only
- * gathers or only affine loops, with a static schedule), the team's LDS
+ * context's workgroup size: 0, 1 or 2 for the general instance, which runs
+ * every body; 10 + k for the lean instance of the fixed fma chain k of (1,0)
+ * (1,1) (2,2) (4,4) (8,8) (16,16) (32,32), which a single-region launch of
+ * workgroups up to 256 threads runs when every publish of the region is that
+ * chain; 17 and 18 for those of regions that publish only gathers or only
+ * affine loops, of any workgroup size; 19, up to 512 threads, for any other
+ * mix of fma chains; all with a static schedule), the team's LDS
  * (control block plus stack slab) and the device's parameters. */
 int dsr_region_occupancy(dsr_ctx *ctx, uint32_t variant, dsr_occupancy *out);
 

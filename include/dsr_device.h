@@ -322,11 +322,11 @@ __device__ inline void read_in_place(const team_t &T, stack_t &S, uint32_t off)
     if (T.lane == 0) frame_table(T)[4 * (S.nframes - 1) + 3] = S.top_image;
 }
 
-__device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes)
+__device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes, bool global_only = false)
 {
     const uint32_t size = (nbytes + DSR_ALIGN - 1) & ~(DSR_ALIGN - 1);
     frame_t f{SPACE_NONE, 0, size};
-    if (size <= T.threshold && size <= T.lds_cap - S.sp_lds) {
+    if (!global_only && size <= T.threshold && size <= T.lds_cap - S.sp_lds) {
         f.space = SPACE_LDS; f.off = S.sp_lds; S.sp_lds += size;
     } else if (size <= T.hbm_cap - S.sp_hbm) {
         f.space = SPACE_HBM; f.off = S.sp_hbm; S.sp_hbm += size;

@@ -55,7 +55,6 @@ struct dsr_region {
     std::vector<uint8_t> dead;          /* handle popped                    */
     uint32_t n_red;
     uint32_t red_kind_mask;
-    uint32_t variant;                   /* widest fixed fma chain published */
     int32_t lean;                       /* lean instance every publish runs on: its variant
                                            less DSR_LEAN_BASE (-1 none yet, -2 mixed or
                                            other bodies) */
@@ -171,7 +170,6 @@ extern "C" int dsr_region_begin(dsr_ctx *ctx, int32_t teams, dsr_region **out)
     r->teams = teams;
     r->n_red = 0;
     r->red_kind_mask = 0;
-    r->variant = 0;
     r->lean = -1;
     r->frozen = false;
     r->d_ops = nullptr;
@@ -304,26 +302,30 @@ static int32_t lean_of(int32_t body, const dsr_loop &L)
     if (L.schedule != DSR_SCHED_STATIC) return -2;
     if (body == DSR_BODY_AFFINE_XOR) return DSR_LEAN_AFFINE - DSR_LEAN_BASE;
     if (body == DSR_BODY_GATHER || body == DSR_BODY_GATHER_NESTED) return DSR_LEAN_GATHER - DSR_LEAN_BASE;
-    if (body != DSR_BODY_FMA_CHAIN || L.alen != 0) return -2;
-    for (int32_t k = 0; k < DSR_LEAN_CHAINS; ++k)
-        if ((int)L.ni == DSR_LEAN_NI(k) && (int)L.nf == DSR_LEAN_NF(k)) return k;
-    return -2;
+    if (body == DSR_BODY_FMA_CHAIN && L.alen == 0)
+        for (int32_t k = 0; k < DSR_LEAN_CHAINS; ++k)
+            if ((int)L.ni == DSR_LEAN_NI(k) && (int)L.nf == DSR_LEAN_NF(k)) return k;
+    return DSR_LEAN_ANY_CHAIN - DSR_LEAN_BASE;
 }
 
 static void note_lean(dsr_region *r, int32_t k)
 {
+    const int32_t any = DSR_LEAN_ANY_CHAIN - DSR_LEAN_BASE;
+    const auto chain = [any](int32_t v) { return v == any || (v >= 0 && v < DSR_LEAN_CHAINS); };
     if (r->lean == -1) r->lean = k;
-    else if (r->lean != k) r->lean = -2;
+    else if (r->lean != k) r->lean = chain(r->lean) && chain(k) ? any : -2;
 }
 
 /* Kernel variant for a single-region launch of r with workgroups of wg: the
- * lean instance that holds all its bodies, compiled for up to 256 threads
- * (fixed chains, whose scalars fill the registers of two waves per SIMD)
- * or 1024 (gathers, affine loops). */
+ * lean instance that holds all its bodies (a fixed chain in a workgroup above
+ * 256 threads runs as any chain), else the general one. */
 static uint32_t single_variant(const dsr_region *r, uint32_t wg)
 {
+    if (r->lean < 0) return 0;
     const uint32_t lean = (uint32_t)(DSR_LEAN_BASE + r->lean);
-    return (r->lean >= 0 && (wg <= 256 || lean >= DSR_LEAN_GATHER)) ? lean : r->variant;
+    if (lean == DSR_LEAN_GATHER || lean == DSR_LEAN_AFFINE) return lean;
+    if (wg > 512) return 0;
+    return wg > 256 ? (uint32_t)DSR_LEAN_ANY_CHAIN : lean;
 }
 
 extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr_loop *loop)
@@ -353,8 +355,6 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
         if (L.alen) need = ((need + 15) & ~15ull) + 4ull * L.alen;
         if (nb < need) return DSR_E_INVAL;
         if (!lane_share_ok(r, chunk)) return DSR_E_INVAL;
-        if (L.alen == 0 && L.ni == 16 && L.nf == 16 && r->variant < 1) r->variant = 1;
-        if (L.alen == 0 && L.ni == 32 && L.nf == 32) r->variant = 2;
         reduces = true;
         break;
     }
@@ -440,7 +440,7 @@ extern "C" int dsr_publish_list(dsr_region *r, const dsr_ref *refs, int32_t n, i
     } catch (...) {
         return DSR_E_NOMEM;
     }
-    note_lean(r, -2);
+    note_lean(r, lean_of(body, L));
     r->red_kind_mask |= 1u << r->n_red;
     r->n_red++;
     return DSR_OK;
@@ -579,7 +579,7 @@ static int launch_single(const dsr_region *r, const dsr_dregion &R, const dsr_dr
     if (A.inl_ops) std::memcpy(A.inl_op, r->ops.data(), r->ops.size() * sizeof(dsr_op));
     A.inl_img = 0;
     A.init_in_place = r->init.size() <= 0xFFFFFFFFull ? 1u : 0u;
-    A.pad = 0;
+    A.global_lists = C.global_lists;
     const dsr_op &op = r->ops[0];
     if (op.kind == DSR_OP_PUSH && op.init_stride == 0 && op.init_bytes > 0 && op.init_bytes <= DSR_INLINE_IMG) {
         const uint32_t padded = (op.init_bytes + 15u) & ~15u;
@@ -834,7 +834,6 @@ struct dsr_batch {
     std::vector<dsr_dresult> h_results;
     uint8_t *h_pin;                     /* pinned: n leading host parts of the results */
     bool have_results;
-    uint32_t variant;
     dsr_tune tune;
     uint32_t grid;
     uint32_t lds_bytes;
@@ -911,7 +910,6 @@ extern "C" int dsr_batch_create(dsr_ctx *ctx, dsr_region *const *regions, int32_
     b->last = 0;
     b->have_results = false;
     b->h_pin = nullptr;
-    b->variant = 0;
     std::vector<uint8_t> stage;
     try {
         stage.assign(sz, 0);
@@ -950,7 +948,6 @@ extern "C" int dsr_batch_create(dsr_ctx *ctx, dsr_region *const *regions, int32_
         b->teams[i] = r->teams;
         b->n_red[i] = r->n_red;
         b->loops[i] = r->loops;
-        b->variant = std::max(b->variant, r->variant);
         uint64_t lp = 0, hp = 0;
         (void)stack_peaks(r, 0xFFFFFFFFu, 0xFFFFFFFFu, ~0ull, &lp, &hp);
         b->stack_peak[i] = (uint32_t)std::min<uint64_t>(lp + hp, 0xFFFFFFFFull);
@@ -1013,10 +1010,9 @@ extern "C" int dsr_batch_tune(dsr_batch *b, const dsr_tune *tune)
     for (int32_t i = 0; i < b->n; ++i)
         for (const dsr_dloop &L : b->loops[i])
             if ((L.chunk + lanes - 1) / lanes > (1ull << 15)) return DSR_E_INVAL;
-    const uint32_t variant = t.wg_size > 256 ? 0 : b->variant;
     uint32_t grid = t.grid;
     if (grid == 0) {
-        const int occ = dsr_region_kernel_occupancy(t.wg_size, (uint32_t)lds, variant);
+        const int occ = dsr_region_kernel_occupancy(t.wg_size, (uint32_t)lds, 0);
         if (occ <= 0) return DSR_E_LDS;
         grid = (uint32_t)occ * (b->cus ? b->cus : 1);
         grid = std::min(grid, b->ctx->cfg.max_teams);
@@ -1049,7 +1045,7 @@ static int batch_kernel(dsr_batch *b, hipStream_t s)
     LP.done_ts = b->d_done;
     const dsr_dconfig C = make_dconfig(b->ctx, b->tune.wg_size, b->tune.lds_slab_bytes,
                                        b->tune.overflow_threshold, b->tune.master_joins, 0);
-    return dsr_launch_region_kernel(&LP, &C, b->grid, b->tune.wg_size, b->lds_bytes, b->variant, s) ? DSR_E_HIP
+    return dsr_launch_region_kernel(&LP, &C, b->grid, b->tune.wg_size, b->lds_bytes, 0, s) ? DSR_E_HIP
                                                                                                      : DSR_OK;
 }
 
@@ -1098,7 +1094,6 @@ extern "C" int dsr_batch_launch_each(dsr_batch *b, void *stream)
     hipStream_t s = (hipStream_t)stream;
     const dsr_dconfig C = make_dconfig(b->ctx, b->tune.wg_size, b->tune.lds_slab_bytes,
                                        b->tune.overflow_threshold, b->tune.master_joins, 0);
-    const uint32_t variant = b->tune.wg_size > 256 ? 0 : b->variant;
     if (hipEventRecord(b->ev0, s) != hipSuccess) return DSR_E_HIP;
     for (int32_t i = 0; i < b->n; ++i) {
         dsr_dlaunch LP{};
@@ -1107,7 +1102,7 @@ extern "C" int dsr_batch_launch_each(dsr_batch *b, void *stream)
         LP.n_regions = 1;
         LP.done_ts = b->d_done + i;                  /* region i's completion */
         LP.start_ts = i == 0 ? b->d_done + b->n : nullptr;
-        if (dsr_launch_region_kernel(&LP, &C, (uint32_t)b->teams[i], b->tune.wg_size, b->lds_bytes, variant, s))
+        if (dsr_launch_region_kernel(&LP, &C, (uint32_t)b->teams[i], b->tune.wg_size, b->lds_bytes, 0, s))
             return DSR_E_HIP;
     }
     if (hipEventRecord(b->ev1, s) != hipSuccess) return DSR_E_HIP;
@@ -1229,8 +1224,7 @@ extern "C" int dsr_autotune_plan(dsr_batch *b, dsr_tune *out, int32_t max, int32
     std::vector<cand> keep;
     for (uint32_t wg : {64u, 128u, 256u, 512u, 1024u}) {
         const uint32_t nw = wg / 64;
-        const uint32_t variant = wg > 256 ? 0 : b->variant;
-        const int regs = dsr_region_kernel_regs(wg, variant);
+        const int regs = dsr_region_kernel_regs(wg, 0);
         if (regs <= 0) continue;
         /* per occupancy the largest slab: it keeps more frames on chip at
          * no cost in resident teams */
@@ -1394,7 +1388,6 @@ struct dsr_server {
     std::vector<serve_class> cls;
     uint64_t next_ticket;
     uint64_t hbm_budget, hbm_used;
-    uint32_t variant;
     dsr_tune tune;
     uint32_t in_flight;
 };
@@ -1466,7 +1459,6 @@ extern "C" int dsr_serve_start(dsr_ctx *ctx, const dsr_serve_cfg *cfg, dsr_serve
         lds_max = (uint32_t)v;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, ctx->device) == hipSuccess && v > 0)
         cus = (uint32_t)v;
-    const uint32_t variant = 0;
     /* the classes: one of the tune's slab and grid, or those given */
     const uint32_t n_cls = c.n_classes ? c.n_classes : 1u;
     std::vector<serve_class> cls(n_cls);
@@ -1488,7 +1480,7 @@ extern "C" int dsr_serve_start(dsr_ctx *ctx, const dsr_serve_cfg *cfg, dsr_serve
              * any stream, waits until the server closes (measured: a
              * device-to-host copy blocked for the whole idle limit at full
              * occupancy and took 0.6 ms with one slot per CU free). */
-            const int occ = dsr_region_kernel_occupancy(t.wg_size, K.lds_bytes, variant);
+            const int occ = dsr_region_kernel_occupancy(t.wg_size, K.lds_bytes, 0);
             if (occ <= 0) return DSR_E_LDS;
             const uint32_t slots_all = (uint32_t)occ * cus;
             const uint32_t spare = occ >= 2 ? cus : std::max(1u, cus / 32);
@@ -1506,7 +1498,6 @@ extern "C" int dsr_serve_start(dsr_ctx *ctx, const dsr_serve_cfg *cfg, dsr_serve
     S->ctx = ctx;
     S->cfg = c;
     S->tune = t;
-    S->variant = variant;
     S->next_ticket = 1;
     S->in_flight = 0;
     S->hbm_used = 0;
@@ -1616,7 +1607,7 @@ extern "C" int dsr_serve_start(dsr_ctx *ctx, const dsr_serve_cfg *cfg, dsr_serve
         /* each class's teams take their own HBM stack and nested slots */
         C.hbm_base = ctx->hbm + (uint64_t)K.first_wg * ctx->cfg.hbm_slab_bytes;
         C.nest_base = ctx->nest + (uint64_t)K.first_wg * DSR_NEST_SLOT;
-        if (dsr_launch_region_kernel(&LP, &C, K.grid, t.wg_size, K.lds_bytes, variant, K.stream) != 0) {
+        if (dsr_launch_region_kernel(&LP, &C, K.grid, t.wg_size, K.lds_bytes, 0, K.stream) != 0) {
             __atomic_store_n(S->stop, 1u, __ATOMIC_RELEASE);
             for (uint32_t j = 0; j < k; ++j) (void)hipStreamSynchronize(S->cls[j].stream);
             serve_free(S);
@@ -1649,7 +1640,6 @@ extern "C" int dsr_serve_submit(dsr_server *S, dsr_region *r, void *const *outs,
     if (r->ops.size() > DSR_SERVE_MAX_OPS || r->loops.size() > DSR_SERVE_MAX_LOOPS) return DSR_E_INVAL;
     if ((uint32_t)r->teams > S->cfg.max_teams || r->init.size() > S->cfg.slot_bytes) return DSR_E_INVAL;
     if ((size_t)n_outs > r->loops.size() || (n_outs && !outs)) return DSR_E_INVAL;
-    /* fixed-length chains beyond 8+8 run through the run-time loop here */
     const uint64_t lanes = 64ull * (S->tune.master_joins ? S->tune.wg_size / 64 : S->tune.wg_size / 64 - 1);
     for (const dsr_dloop &L : r->loops)
         if ((L.chunk + lanes - 1) / lanes > (1ull << 15)) return DSR_E_INVAL;
@@ -1923,7 +1913,6 @@ extern "C" int dsr_batch_replay_serial(dsr_batch *b, const int32_t *prog, const 
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) return DSR_E_HIP;
     const dsr_dconfig C = make_dconfig(b->ctx, b->tune.wg_size, b->tune.lds_slab_bytes,
                                        b->tune.overflow_threshold, b->tune.master_joins, 0);
-    const uint32_t variant = b->tune.wg_size > 256 ? 0 : b->variant;
     const double t0 = now_s();
     int rc = DSR_OK;
     for (int32_t q = 0; q < n && rc == DSR_OK; ++q) {
@@ -1935,7 +1924,7 @@ extern "C" int dsr_batch_replay_serial(dsr_batch *b, const int32_t *prog, const 
         LP.regions = b->d_regions + i;
         LP.items = nullptr;
         LP.n_regions = 1;
-        if (dsr_launch_region_kernel(&LP, &C, (uint32_t)b->teams[i], b->tune.wg_size, b->lds_bytes, variant, s) ||
+        if (dsr_launch_region_kernel(&LP, &C, (uint32_t)b->teams[i], b->tune.wg_size, b->lds_bytes, 0, s) ||
             hipStreamSynchronize(s) != hipSuccess)
             rc = DSR_E_HIP;
         latency_us[q] = (now_s() - t0 - arrival_s[q]) * 1e6;
@@ -1990,9 +1979,11 @@ extern "C" int dsr_occupancy_model(const dsr_hw_model *hw, uint32_t threads, uin
 extern "C" int dsr_region_occupancy(dsr_ctx *ctx, uint32_t variant, dsr_occupancy *out)
 {
     if (!ctx || !out) return DSR_E_INVAL;
-    if (variant > 2 && (variant < DSR_LEAN_BASE || variant >= DSR_LEAN_BASE + DSR_LEAN_CHAINS ||
-                        ctx->cfg.wg_size > 256))
-        return DSR_E_INVAL;
+    if (variant > 2) {
+        const uint32_t most = variant < DSR_LEAN_BASE ? 0u : variant < DSR_LEAN_GATHER ? 256u
+                              : variant <= DSR_LEAN_AFFINE ? 1024u : variant == DSR_LEAN_ANY_CHAIN ? 512u : 0u;
+        if (ctx->cfg.wg_size > most) return DSR_E_INVAL;
+    }
     if (ctx->device < 0) return DSR_E_STATE;
     hipDeviceProp_t p{};
     if (hipGetDeviceProperties(&p, ctx->device) != hipSuccess) return DSR_E_HIP;

@@ -31,10 +31,9 @@ struct instance {
 const instance kInstances[] = {DSR_INSTANCES(DSR_ENTRY)};
 #undef DSR_ENTRY
 
-/* Workgroups above 512 threads run the 1024-thread instance (run-time
- * chains only), 257-512 the 512-thread one; up to 256 threads the variant
- * the regions need.  A lean instance runs the workgroup sizes it was
- * compiled for. */
+/* Workgroups above 512 threads run the 1024-thread general instance, 257-512
+ * the 512-thread one, smaller ones the 256-thread one.  A lean instance runs
+ * the workgroup sizes it was compiled for. */
 const instance *pick(uint32_t wg_size, uint32_t variant)
 {
     if (variant >= DSR_LEAN_BASE) {
@@ -43,7 +42,7 @@ const instance *pick(uint32_t wg_size, uint32_t variant)
         return nullptr;
     }
     const uint32_t maxwg = wg_size > 512 ? 1024u : (wg_size > 256 ? 512u : 256u);
-    const int want = maxwg == 1024 ? -1 : (maxwg == 512 ? 0 : (int)(variant > 2 ? 2 : variant));
+    const int want = maxwg == 1024 ? -1 : 0;
     for (const instance &k : kInstances)
         if (k.maxwg == maxwg && k.variant == want) return &k;
     return nullptr;

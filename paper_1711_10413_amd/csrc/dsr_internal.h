@@ -185,7 +185,7 @@ struct dsr_lean {
     uint32_t inl_img;          /* image bytes held in `image` (a multiple of
                                   16, zero-padded; 0: none)                 */
     uint32_t init_in_place;    /* 1: the images lie within 2^32 bytes of `init` */
-    uint32_t pad;
+    uint32_t global_lists;
     dsr_dloop loop0;
     dsr_op inl_op[DSR_INLINE_OPS];
     uint8_t image[DSR_INLINE_IMG];
@@ -225,8 +225,6 @@ struct dsr_dconfig {
  * dsr_dispatch.cpp routes each launch to one of them. */
 #define DSR_INSTANCES(X) \
     X(256_0, 256, 0)     \
-    X(256_1, 256, 1)     \
-    X(256_2, 256, 2)     \
     X(512_0, 512, 0)     \
     X(1024_m1, 1024, -1) \
     X(256_l0, 256, 10)   \
@@ -237,18 +235,22 @@ struct dsr_dconfig {
     X(256_l5, 256, 15)   \
     X(256_l6, 256, 16)   \
     X(1024_g, 1024, 17)  \
-    X(1024_a, 1024, 18)
+    X(1024_a, 1024, 18)  \
+    X(512_c, 512, 19)
 
 /* Lean instances: variant DSR_LEAN_BASE + k runs single-region launches of
  * workgroups up to 256 threads whose publishes are all the fixed fma chain
  * k, (DSR_LEAN_NI(k) int32, DSR_LEAN_NF(k) fp64 scalars), with no array;
  * DSR_LEAN_GATHER and DSR_LEAN_AFFINE single-region launches of any workgroup
  * size whose publishes are all gathers (flat or nested) or all affine
- * loops, with a static schedule. */
+ * loops, and DSR_LEAN_ANY_CHAIN those of workgroups up to 512 threads whose
+ * publishes are all fma chains, of any counts, with or without an array,
+ * through frames or lists; all with a static schedule. */
 #define DSR_LEAN_BASE 10
 #define DSR_LEAN_CHAINS 7
 #define DSR_LEAN_GATHER 17
 #define DSR_LEAN_AFFINE 18
+#define DSR_LEAN_ANY_CHAIN 19
 #define DSR_LEAN_NI(k) ((k) == 0 ? 1 : (k) == 1 ? 1 : (k) == 2 ? 2 : (k) == 3 ? 4 : (k) == 4 ? 8 : (k) == 5 ? 16 : 32)
 #define DSR_LEAN_NF(k) ((k) == 0 ? 0 : DSR_LEAN_NI(k))
 

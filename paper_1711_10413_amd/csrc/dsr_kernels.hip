@@ -39,15 +39,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-
-/* Element pairs per lane and batch in the run-time fma chain (256- and
- * 512-thread instances), and in the fixed chains of up to four scalars. */
-#ifndef DSR_FIXED_U_LIGHT
-#define DSR_FIXED_U_LIGHT 8
-#endif
-#ifndef DSR_RT_PAIRS
-#define DSR_RT_PAIRS 8
-#endif
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 
 extern __shared__ __align__(16) uint8_t dsr_lds[];
 
@@ -116,7 +108,8 @@ __device__ __forceinline__ void acc_add_i64(lane_acc &a, int64_t v)
 
 /* Split y exactly into y = t1 + t2 + r2 with t1 on the 2^-5 grid, t2 on
  * the 2^-40 grid and |r2| <= 2^-41, and add the parts to the bins.  r2 must
- * itself be on the 2^-75 grid (checked by rounding it there). */
+ * itself be on the 2^-75 grid (checked by rounding it there); the caller has
+ * checked |y| < 2^32. */
 __device__ __forceinline__ void acc_add_f64(lane_acc &a, double y)
 {
     const double C1 = 0x1.8p47, C2 = 0x1.8p12, C3 = 0x1.8p-23;
@@ -125,7 +118,7 @@ __device__ __forceinline__ void acc_add_f64(lane_acc &a, double y)
     const double t2 = (r1 + C2) - C2;
     const double r2 = r1 - t2;
     const double t3 = (r2 + C3) - C3;
-    a.bad |= (uint32_t)((t3 != r2) | !(__builtin_fabs(y) < 0x1p32));
+    a.bad |= (uint32_t)(t3 != r2);
     a.b1 += t1;
     a.b2 += t2;
     a.b3 += r2;
@@ -281,15 +274,6 @@ struct span_t {
  * device counter (the next claim is issued before the current block runs,
  * so its latency overlaps the work).  Claimed blocks are shared by the 64
  * lanes of the claiming wave. */
-/* Balanced split of a team's static range among its waves: the range is
- * cut into blocks of DSR_TEAM_BLOCK iterations that the waves claim from a
- * counter in the team's LDS control block.  A wave then streams contiguous
- * 8 KiB stretches of x (one batch of eight pairs per lane), and a wave on a
- * SIMD it shares with fewer others takes more blocks: with three worker
- * waves per team and two teams per CU some SIMDs hold two worker waves and
- * some one.  Measured on the fma chains against the fixed per-lane share:
- * 2.2-2.7 us faster per 2^24-element region for up to 16 scalars, 0.5-1.2 us
- * for 32 and 64; 2048-, 4096- and 8192-iteration blocks were slower. */
 /* teams up to this many arrive at one counter (no group level) */
 #ifndef DSR_FLAT_TEAMS
 #define DSR_FLAT_TEAMS 512
@@ -297,47 +281,10 @@ struct span_t {
 #ifndef DSR_ARRIVE_FENCE
 #define DSR_ARRIVE_FENCE 1
 #endif
-#ifndef DSR_TEAM_BLOCK
-#define DSR_TEAM_BLOCK 1024u
-#endif
-/* chains of at least this many scalars take the balanced split (all) */
-#ifndef DSR_BALANCE_MIN
-#define DSR_BALANCE_MIN 1
-#endif
-/* fixed chains stream their balanced blocks pipelined across blocks */
-#ifndef DSR_STREAM_BLOCKS
-#define DSR_STREAM_BLOCKS 1
-#endif
-
-template <class F>
-__device__ __forceinline__ void team_blocks(span_t sp, uint32_t lane, lane_acc &A, F &&f)
-{
-    LDSQ uint32_t *ctr = (LDSQ uint32_t *)(dsr_lds + offsetof(cb_header, blocks));
-    const uint64_t lo = sp.lo;
-    const uint32_t nblk = sp.hi > lo ? (uint32_t)((sp.hi - lo + DSR_TEAM_BLOCK - 1) / DSR_TEAM_BLOCK) : 0u;
-    uint32_t c = 0;
-    if (lane == 0) c = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    c = uniform((uint32_t)__shfl((int)c, 0, 64));
-    uint32_t since = 0;
-    while (c < nblk) {
-        uint32_t cn = 0;
-        if (lane == 0) cn = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        const uint64_t b = lo + (uint64_t)c * DSR_TEAM_BLOCK;
-        f(span_t{b, min(sp.hi, b + DSR_TEAM_BLOCK), lane, 64u});
-        /* a block adds 32 values per lane: flush well before 2^16 */
-        if (++since == 256) { acc_flush(A); since = 0; }
-        c = uniform((uint32_t)__shfl((int)cn, 0, 64));
-    }
-}
-
 template <class F>
 __device__ __forceinline__ void for_spans(const dsr_dloop &L, span_t sp, uint32_t lane,
-                                          uint32_t *claim, lane_acc &A, F &&f, bool balanced = false)
+                                          uint32_t *claim, lane_acc &A, F &&f)
 {
-    if (balanced && L.schedule == DSR_SCHED_STATIC) {
-        team_blocks(sp, lane, A, f);
-        return;
-    }
     f(sp);
     if (L.schedule != DSR_SCHED_DYNAMIC_TAIL) return;
     uint32_t c = 0;
@@ -369,288 +316,32 @@ __device__ __forceinline__ void affine_span(uint32_t a, uint32_t b, uint32_t c, 
     acc_add_i64(A, s);
 }
 
-/* fma chain with the scalar counts known at compile time. */
-template <int NI, int NF>
-__device__ __forceinline__ double chain(const double (&s)[NI + NF], double xd)
-{
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < NI + NF; ++k) acc = __builtin_fma(s[k], xd, acc);
-    return acc;
-}
-
-/* Lane-to-element mapping of the streaming loop: a lane takes element
- * pairs (8 B of x, 16 B of y), so every load instruction of a wave covers
- * 512 contiguous bytes of x and every store 1 KB of y; consecutive batches
- * of U pairs per lane are software-pipelined (the next batch's loads are in
- * flight while the current batch computes). */
-template <int NI, int NF>
-__device__ __forceinline__ void fma_span(const double (&s)[NI + NF], const GLB float *__restrict__ x,
-                                         GLB double *__restrict__ y, span_t sp, lane_acc &A)
-{
-    /* head element when the range starts on an odd index */
-    const uint64_t plo = min(sp.hi, (sp.lo + 1) & ~1ull);
-    const uint64_t phi = max(plo, sp.hi & ~1ull);
-    if (sp.lo < plo && sp.p == 0) {
-        const double v = chain<NI, NF>(s, (double)x[sp.lo]);
-        y[sp.lo] = v;
-        acc_add_f64(A, v);
-    }
-    lane_acc Ac[2] = {acc_zero(), acc_zero()};
-    const GLB f32x2 *__restrict__ x2 = (const GLB f32x2 *)x;
-    GLB f64x2 *__restrict__ y2 = (GLB f64x2 *)y;
-    const uint64_t nv1 = phi >> 1;
-    constexpr int U = (NI + NF >= 64) ? 4 : (NI + NF <= 4 ? DSR_FIXED_U_LIGHT : 8);
-    /* the 64-scalar chain computes a batch for as long as the memory takes
-     * to return one, so it keeps two batches in flight ahead of the one it
-     * computes: 1.3 us faster per 2^24-element region on the lean instance */
-    constexpr bool DEEP = NI + NF >= 64;
-    const uint64_t step = (uint64_t)U * sp.P;
-    uint64_t v = (plo >> 1) + sp.p;
-    if (DEEP && v + (uint64_t)(U - 1) * sp.P < nv1) {
-        /* two batches in flight ahead of the one being computed */
-        f32x2 b0[U], b1[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) b0[u] = __builtin_nontemporal_load(&x2[v + (uint64_t)u * sp.P]);
-        bool m1 = v + step + (uint64_t)(U - 1) * sp.P < nv1;
-        if (m1) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) b1[u] = __builtin_nontemporal_load(&x2[v + step + (uint64_t)u * sp.P]);
-        }
-        for (;;) {
-            const uint64_t v2 = v + 2 * step;
-            const bool m2 = m1 && v2 + (uint64_t)(U - 1) * sp.P < nv1;
-            f32x2 b2[U];
-            if (m2) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) b2[u] = __builtin_nontemporal_load(&x2[v2 + (uint64_t)u * sp.P]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                f64x2 r;
-                r.x = chain<NI, NF>(s, (double)b0[u].x);
-                r.y = chain<NI, NF>(s, (double)b0[u].y);
-                __builtin_nontemporal_store(r, &y2[v + (uint64_t)u * sp.P]);
-                acc_add_f64(Ac[0], r.x);
-                acc_add_f64(Ac[1], r.y);
-            }
-            v += step;
-            if (!m1) break;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                b0[u] = b1[u];
-                b1[u] = b2[u];
-            }
-            m1 = m2;
-        }
-    } else if (v + (uint64_t)(U - 1) * sp.P < nv1) {
-        f32x2 cur[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) cur[u] = __builtin_nontemporal_load(&x2[v + (uint64_t)u * sp.P]);
-        for (;;) {
-            const uint64_t vn = v + step;
-            const bool more = vn + (uint64_t)(U - 1) * sp.P < nv1;
-            f32x2 nxt[U];
-            if (more) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) nxt[u] = __builtin_nontemporal_load(&x2[vn + (uint64_t)u * sp.P]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                f64x2 r;
-                r.x = chain<NI, NF>(s, (double)cur[u].x);
-                r.y = chain<NI, NF>(s, (double)cur[u].y);
-                __builtin_nontemporal_store(r, &y2[v + (uint64_t)u * sp.P]);
-                acc_add_f64(Ac[0], r.x);
-                acc_add_f64(Ac[1], r.y);
-            }
-            v = vn;
-            if (!more) break;
-#pragma unroll
-            for (int u = 0; u < U; ++u) cur[u] = nxt[u];
-        }
-    }
-    for (; v < nv1; v += sp.P) {
-        const f32x2 xv = __builtin_nontemporal_load(&x2[v]);
-        f64x2 r;
-        r.x = chain<NI, NF>(s, (double)xv.x);
-        r.y = chain<NI, NF>(s, (double)xv.y);
-        __builtin_nontemporal_store(r, &y2[v]);
-        acc_add_f64(Ac[0], r.x);
-        acc_add_f64(Ac[1], r.y);
-    }
-    if (phi < sp.hi && sp.p == 0) {
-        const double r = chain<NI, NF>(s, (double)x[phi]);
-        y[phi] = r;
-        acc_add_f64(A, r);
-    }
-    acc_merge(A, Ac[0]);
-    acc_merge(A, Ac[1]);
-}
-
-/* Shared scalars are wave-uniform: read them once as uniform values, so
- * they live in scalar registers and no frame load is still in flight when
- * the streaming loop starts (an outstanding frame load would make every
- * iteration wait for all memory operations). */
-__device__ __forceinline__ uint32_t uniform_u32(const uint8_t *p)
-{
-    return uniform(*(const uint32_t *)p);
-}
-
-__device__ __forceinline__ double uniform_f64(const uint8_t *p)
-{
-    const uint64_t lo = uniform_u32(p), hi = uniform_u32(p + 4);
-    return __longlong_as_double((long long)(lo | (hi << 32)));
-}
-
-/* The balanced split for a fixed chain, pipelined across blocks: a block is
- * one batch (U pairs per lane, 128·U elements); a wave claims its next
- * block and issues that block's loads before it computes the current one,
- * so two batches stay in flight however the blocks fall.  A partial last
- * block of the range goes through fma_span.  Measured 0.2-0.8 us faster
- * per 2^24-element region than one fma_span per claimed block for up to 32
- * scalars, 0.8 us slower for 64 (whose batches are half as long), which
- * keeps the per-block spans. */
-template <int NI, int NF>
-__device__ __forceinline__ void fma_blocks(const double (&s)[NI + NF], const GLB float *__restrict__ x,
-                                           GLB double *__restrict__ y, span_t sp, uint32_t lane, lane_acc &A)
-{
-    constexpr int U = (NI + NF >= 64) ? 4 : (NI + NF <= 4 ? DSR_FIXED_U_LIGHT : 8);
-    constexpr uint32_t BLK = 128u * U;
-    LDSQ uint32_t *ctr = (LDSQ uint32_t *)(dsr_lds + offsetof(cb_header, blocks));
-    const uint64_t lo = sp.lo;
-    const uint32_t nfull = sp.hi > lo ? (uint32_t)((sp.hi - lo) / BLK) : 0u;
-    const bool tail = sp.hi > lo + (uint64_t)nfull * BLK;
-    const GLB f32x2 *__restrict__ x2 = (const GLB f32x2 *)x;
-    GLB f64x2 *__restrict__ y2 = (GLB f64x2 *)y;
-    lane_acc Ac[2] = {acc_zero(), acc_zero()};
-    uint32_t c = 0;
-    if (lane == 0) c = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    c = uniform((uint32_t)__shfl((int)c, 0, 64));
-    f32x2 cur[U];
-    if (c < nfull) {
-        const uint64_t v = (lo >> 1) + (uint64_t)c * (BLK / 2) + lane;
-#pragma unroll
-        for (int u = 0; u < U; ++u) cur[u] = __builtin_nontemporal_load(&x2[v + 64u * u]);
-    }
-    uint32_t since = 0;
-    while (c < nfull) {
-        uint32_t cn = 0;
-        if (lane == 0) cn = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        cn = uniform((uint32_t)__shfl((int)cn, 0, 64));
-        f32x2 nxt[U];
-        if (cn < nfull) {
-            const uint64_t vn = (lo >> 1) + (uint64_t)cn * (BLK / 2) + lane;
-#pragma unroll
-            for (int u = 0; u < U; ++u) nxt[u] = __builtin_nontemporal_load(&x2[vn + 64u * u]);
-        }
-        const uint64_t v = (lo >> 1) + (uint64_t)c * (BLK / 2) + lane;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            f64x2 r;
-            r.x = chain<NI, NF>(s, (double)cur[u].x);
-            r.y = chain<NI, NF>(s, (double)cur[u].y);
-            __builtin_nontemporal_store(r, &y2[v + 64u * u]);
-            acc_add_f64(Ac[0], r.x);
-            acc_add_f64(Ac[1], r.y);
-        }
-        /* a block adds U values to each of the two bins: flush well before 2^16 */
-        if (++since == 2048) {
-            acc_merge(A, Ac[0]);
-            acc_merge(A, Ac[1]);
-            Ac[0] = acc_zero();
-            Ac[1] = acc_zero();
-            acc_flush(A);
-            since = 0;
-        }
-        c = cn;
-#pragma unroll
-        for (int u = 0; u < U; ++u) cur[u] = nxt[u];
-    }
-    acc_merge(A, Ac[0]);
-    acc_merge(A, Ac[1]);
-    /* the claim that went past the full blocks takes the partial block */
-    if (c == nfull && tail) fma_span<NI, NF>(s, x, y, span_t{lo + (uint64_t)nfull * BLK, sp.hi, lane, 64u}, A);
-}
-
-/* BLOCKS: the static schedule streams the balanced block split (general
- * instances); without it every participating wave takes its fixed per-lane
- * share of the team's range.  On the lean instances the fixed share
- * measured 0.3-1.0 us faster per 2^24-element region for 8 to 32 scalars
- * and the same below (both builds timed interleaved on one GPU). */
-template <int NI, int NF, bool BLOCKS = true>
-__device__ __forceinline__ void fma_fixed_spans(const double (&s)[NI + NF], const dsr_dloop &L, span_t sp,
-                                                lane_acc &A, uint32_t *claim, uint32_t lane)
-{
-    const GLB float *x = (const GLB float *)L.in;
-    GLB double *y = (GLB double *)L.out;
-    if (!BLOCKS && L.schedule == DSR_SCHED_STATIC) {
-        fma_span<NI, NF>(s, x, y, sp, A);
-        return;
-    }
-    /* (a team range starting on an odd element keeps the per-span path) */
-    if (DSR_STREAM_BLOCKS && NI + NF < 64 && L.schedule == DSR_SCHED_STATIC && !(uniform((uint32_t)sp.lo) & 1u)) {
-        fma_blocks<NI, NF>(s, x, y, sp, lane, A);
-        return;
-    }
-    for_spans(L, sp, lane, claim, A, [&](span_t q) { fma_span<NI, NF>(s, x, y, q, A); }, NI + NF >= DSR_BALANCE_MIN);
-}
-
-template <int NI, int NF, bool BLOCKS = true>
-__device__ __forceinline__ void body_fma_fixed(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp,
-                                               lane_acc &A, uint32_t *claim, uint32_t lane)
-{
-    /* frame layout: [24 B exact sum][NF fp64][NI int32] */
-    double s[NI + NF];
-#pragma unroll
-    for (int k = 0; k < NI; ++k)
-        s[k] = (double)(int32_t)uniform_u32((const uint8_t *)slot<int32_t>(T, f, 24 + 8 * NF + 4 * k));
-#pragma unroll
-    for (int k = 0; k < NF; ++k) s[NI + k] = uniform_f64((const uint8_t *)slot<double>(T, f, 24 + 8 * k));
-    fma_fixed_spans<NI, NF, BLOCKS>(s, L, sp, A, claim, lane);
-}
-
-/* The same chain with its scalars held one per lane (lane k: scalar k). */
-template <int NI, int NF>
-__device__ __forceinline__ void lanes_fma_fixed(double sv, const dsr_dloop &L, span_t sp, lane_acc &A,
-                                                uint32_t *claim, uint32_t lane);
-
-/* fma chain with a run-time scalar count (at most 64) and an optional
- * shared int32 array (the chain then starts from the array element).  The
- * scalars come from one of two sources:
- *   lds_scalars   the frame is in LDS: each chain step reads its scalar with
- *                 a wave-uniform LDS load (a broadcast) shared by every
- *                 element of the batch; int32 scalars are read in pairs.
- *   lane_scalars  the frame is in HBM: lane k holds scalar k as a double
- *                 (loaded once per body) and each step takes it with two
- *                 readlanes.
- * The array index i mod alen is carried from element to element (one
- * conditional subtraction per step) instead of divided.  The element
- * layout, batching and software pipelining are those of fma_span. */
-typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
-
+/* ---- fma chains ----------------------------------------------------------
+ * The chain y = a + s_0 x + s_1 x + ... rounds once per step, so its steps
+ * run in order; what can be saved is steps that do not round.  The int32
+ * scalars come first.  Let S_k be the sum of the first k of them.  While
+ * a + S_k x is exact in fp64 for every k, each step's result is that value,
+ * and one step with S = S_ni gives the same bits as ni steps:
+ *   without an array (a = +0): x has 24 significant bits, so |S_k| <= 2^29
+ *     suffices for every finite x, whatever its exponent;
+ *   with an array element a: if x is a multiple of 2^-24, so is a + S_k x,
+ *     and |a| + max|S_k| |x| < 2^29 bounds it to 53 bits.
+ * Signed zeros agree as well: the chain starts at +0 or an integer, and an
+ * exact sum that cancels is +0.  The first condition is checked once per body
+ * (a scan over the scalars, one per lane), the second once per batch over the
+ * batch's largest |x| and |a|; a non-finite x shows as a y outside the
+ * exact-sum window.  A batch that fails runs every step.  Half of a 64-scalar
+ * chain's steps and two thirds of a mixed region's fall away: 2^24 elements,
+ * 512 teams x 256, 64 scalars 62.3 -> 49.7 us per launch (fp64-bound before,
+ * HBM-bound like the short chains now), 38 scalars in a frame 57.8 -> 48.9 us;
+ * launch and wait of 2^20 elements, 48 scalars and an 8128-element array on
+ * 16 teams 108.7 -> 79.6 us; 10,000 mixed regions 3.79 -> 3.42 ms. */
 __device__ __forceinline__ double readlane_f64(double v, uint32_t k)
 {
     const uint64_t b = (uint64_t)__double_as_longlong(v);
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, k);
     const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), k);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-template <int NI, int NF>
-__device__ __forceinline__ void lanes_fma_fixed(double sv, const dsr_dloop &L, span_t sp, lane_acc &A,
-                                                uint32_t *claim, uint32_t lane)
-{
-    double s[NI + NF];
-#pragma unroll
-    for (int k = 0; k < NI + NF; ++k) s[k] = readlane_f64(sv, k);
-    fma_fixed_spans<NI, NF>(s, L, sp, A, claim, lane);
-}
-
-__device__ __forceinline__ uint32_t mod_step(uint32_t j, uint32_t d, uint32_t m)
-{
-    j += d;
-    return j >= m ? j - m : j;
 }
 
 template <int E>
@@ -660,37 +351,138 @@ __device__ __forceinline__ void fma_all(double s, double (&acc)[E], const double
     for (int e = 0; e < E; ++e) acc[e] = __builtin_fma(s, xd[e], acc[e]);
 }
 
-struct lds_scalars {
-    const LDSQ int32_t *si;   /* ni int32 scalars (8-byte aligned) */
-    const LDSQ double *sf;    /* nf fp64 scalars                   */
-    uint32_t ni, nf;
+/* Whether any of a lane's values lies outside the exact-sum window. */
+template <int E>
+__device__ __forceinline__ bool outside(const double (&y)[E])
+{
+    bool w = false;
+#pragma unroll
+    for (int e = 0; e < E; ++e) w |= !(__builtin_fabs(y[e]) < 0x1p32);
+    return w;
+}
+
+/* A chain with run-time counts: lane k holds scalar k as a double (at most
+ * 64), and each step takes it with two readlanes shared by every element of
+ * the batch.  Four steps at a time, so a batch of 16 elements issues 64
+ * independent-enough fmas between reads. */
+struct rt_chain {
+    double sv;                /* lane k: scalar k                             */
+    uint32_t ni, n;
+    double S;                 /* sum of the int32 scalars                     */
+    float M;                  /* largest partial sum in magnitude             */
+    bool sum;                 /* the int32 steps may be taken as one          */
 
     template <int E>
-    __device__ __forceinline__ void chain(double (&acc)[E], const double (&xd)[E]) const
+    __device__ __forceinline__ void steps(double (&acc)[E], const double (&xd)[E], uint32_t k) const
     {
-        uint32_t k = 0;
-#pragma unroll 2
-        for (; k + 2 <= ni; k += 2) {
-            const i32x2 q = *(const LDSQ i32x2 *)(si + k);
-            fma_all<E>((double)q.x, acc, xd);
-            fma_all<E>((double)q.y, acc, xd);
+#pragma nounroll
+        for (; k + 4 <= n; k += 4) {
+            const double s0 = readlane_f64(sv, k), s1 = readlane_f64(sv, k + 1);
+            const double s2 = readlane_f64(sv, k + 2), s3 = readlane_f64(sv, k + 3);
+            fma_all<E>(s0, acc, xd);
+            fma_all<E>(s1, acc, xd);
+            fma_all<E>(s2, acc, xd);
+            fma_all<E>(s3, acc, xd);
         }
-        if (k < ni) fma_all<E>((double)si[k], acc, xd);
-#pragma unroll 4
-        for (uint32_t f = 0; f < nf; ++f) fma_all<E>(sf[f], acc, xd);
+#pragma nounroll
+        for (; k < n; ++k) fma_all<E>(readlane_f64(sv, k), acc, xd);
     }
-};
 
-struct lane_scalars {
-    double sv;                /* lane k: scalar k */
-    uint32_t n;
-
-    template <int E>
-    __device__ __forceinline__ void chain(double (&acc)[E], const double (&xd)[E]) const
+    /* acc comes in as the chain's start; returns whether a value of this lane
+     * is outside the window.  Every lane of the wave takes part. */
+    template <bool ARR, int E>
+    __device__ __forceinline__ bool eval(double (&acc)[E], const double (&xd)[E], const float (&xf)[E],
+                                         const int32_t (&a)[E]) const
     {
-        for (uint32_t k = 0; k < n; ++k) fma_all<E>(readlane_f64(sv, k), acc, xd);
+        bool one = sum;
+        if (ARR && sum) {
+            uint32_t mx = 0, frac = 0;
+            int32_t hi = 0, lo = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                mx = max(mx, __float_as_uint(xf[e]) & 0x7FFFFFFFu);
+                frac |= __float_as_uint(__builtin_amdgcn_fractf(xf[e] * 0x1p24f));
+                hi = max(hi, a[e]);
+                lo = min(lo, a[e]);
+            }
+            const float ma = (float)hi - (float)lo;
+            /* (2^28 for 2^29: the bound itself is rounded) */
+            one = __all(frac == 0 && __builtin_fmaf(__uint_as_float(mx), M, ma) < 0x1p28f);
+        }
+        if (one) fma_all<E>(S, acc, xd);
+        for (uint32_t k = one ? ni : 0;; k = 0) {
+            steps<E>(acc, xd, k);
+            const bool w = outside<E>(acc);
+            if (ARR || !one || !__any(w)) return w;
+            /* all the steps of a batch with a value outside the window */
+            one = false;
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = 0.0;
+        }
     }
 };
+
+/* A chain with its counts known at compile time, its fp64 scalars in
+ * registers; `all` holds the int32 ones too, for what cannot be summed. */
+template <int NI, int NF>
+struct fixed_chain {
+    double s[NF > 0 ? NF : 1];
+    rt_chain all;
+
+    template <bool ARR, int E>
+    __device__ __forceinline__ bool eval(double (&acc)[E], const double (&xd)[E], const float (&)[E],
+                                         const int32_t (&)[E]) const
+    {
+        static_assert(!ARR, "fixed chains have no array");
+        if (NI == 1 || all.sum) {
+            fma_all<E>(all.S, acc, xd);
+#pragma unroll
+            for (int k = 0; k < NF; ++k) fma_all<E>(s[k], acc, xd);
+            const bool w = outside<E>(acc);
+            if (NI == 1 || !__any(w)) return w;
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = 0.0;
+        }
+        all.template steps<E>(acc, xd, 0);
+        return outside<E>(acc);
+    }
+};
+
+/* One DPP step of a wave scan over doubles (zero where the source lane lies
+ * outside the row). */
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_f64(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, true);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ __forceinline__ rt_chain make_chain(double sv, uint32_t ni, uint32_t nf, uint32_t lane)
+{
+    rt_chain c{sv, ni, ni + nf, ni ? readlane_f64(sv, 0) : 0.0, 0.0f, false};
+    if (ni > 1) {
+        /* partial sums of the int32 scalars: exact (at most 64 of 32 bits) */
+        double p = lane < ni ? sv : 0.0;
+        p = dpp_add_f64<0x111, 0xf>(p);
+        p = dpp_add_f64<0x112, 0xf>(p);
+        p = dpp_add_f64<0x114, 0xf>(p);
+        p = dpp_add_f64<0x118, 0xf>(p);
+        p = dpp_add_f64<0x142, 0xa>(p);
+        p = dpp_add_f64<0x143, 0xc>(p);
+        c.S = readlane_f64(p, 63);
+        c.sum = __all(__builtin_fabs(p) <= 0x1p29);
+        /* the largest magnitude, rounded up to a power of two: the highest
+         * bit set in any lane */
+        uint32_t m = c.sum ? (uint32_t)__builtin_fabs(p) : 0u;
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) m |= (uint32_t)__shfl_xor((int)m, d, 64);
+        m = uniform(m);
+        c.M = m ? (float)(1ull << (32 - __builtin_clz(m))) : 0.0f;
+    }
+    return c;
+}
 
 /* The scalars read through the published reference list on every batch:
  * each chain step reads reference 1 + k (a space and an offset), then the
@@ -699,13 +491,14 @@ struct lane_scalars {
  * list is on chip or in a list frame on the HBM stack, the variables on
  * either stack; all of it is read through generic pointers, as the outlined
  * function receives them. */
-struct list_scalars {
+struct list_chain {
     const uint32_t *lst;
     const uint8_t *stack_lds, *stack_hbm;
     uint32_t ni, nf;
 
-    template <int E>
-    __device__ __forceinline__ void chain(double (&acc)[E], const double (&xd)[E]) const
+    template <bool ARR, int E>
+    __device__ __forceinline__ bool eval(double (&acc)[E], const double (&xd)[E], const float (&)[E],
+                                         const int32_t (&)[E]) const
     {
         for (uint32_t k = 0; k < ni + nf; ++k) {
             const uint32_t sp = uniform(lst[2 * (1 + k)]), off = uniform(lst[2 * (1 + k) + 1]);
@@ -713,157 +506,325 @@ struct list_scalars {
             const double v = k < ni ? (double)*(const int32_t *)p : *(const double *)p;
             fma_all<E>(v, acc, xd);
         }
+        return outside<E>(acc);
     }
 };
 
-template <bool ARR, class AP, class SC>
-__device__ __forceinline__ double rt_one(const SC &sc, AP arr, uint32_t alen, double xd, uint64_t i)
+__device__ __forceinline__ uint32_t mod_step(uint32_t j, uint32_t d, uint32_t m)
 {
-    double acc[1] = {0.0};
-    const double x1[1] = {xd};
-    if constexpr (ARR) acc[0] = (double)arr[(uint32_t)(i % alen)];
-    sc.template chain<1>(acc, x1);
-    return acc[0];
+    j += d;
+    return j >= m ? j - m : j;
 }
 
-template <int U, bool ARR, class AP, class SC>
-__device__ __forceinline__ void fma_rt_span(const SC &sc, AP arr, uint32_t alen,
-                                            const GLB float *__restrict__ x, GLB double *__restrict__ y,
-                                            span_t sp, lane_acc &A)
-{
-    const uint64_t plo = min(sp.hi, (sp.lo + 1) & ~1ull);
-    const uint64_t phi = max(plo, sp.hi & ~1ull);
-    if (sp.lo < plo && sp.p == 0) {
-        const double v = rt_one<ARR>(sc, arr, alen, (double)x[sp.lo], sp.lo);
-        y[sp.lo] = v;
-        acc_add_f64(A, v);
-    }
-    lane_acc Ac[2] = {acc_zero(), acc_zero()};
-    const GLB f32x2 *__restrict__ x2 = (const GLB f32x2 *)x;
-    GLB f64x2 *__restrict__ y2 = (GLB f64x2 *)y;
-    const uint64_t nv1 = phi >> 1;
-    const uint64_t step = (uint64_t)U * sp.P;
-    uint64_t v = (plo >> 1) + sp.p;
-    /* array index of element 2v and its advance per pair stride */
-    uint32_t j = 0, dj = 0;
-    if constexpr (ARR) {
-        j = (uint32_t)((2 * v) % alen);
-        dj = (uint32_t)((2ull * sp.P) % alen);
-    }
-    if (v + (uint64_t)(U - 1) * sp.P < nv1) {
-        f32x2 cur[U];
-        int32_t ca[2 * U];
+/* How a body's array is read.  In an array of even length a pair of loop
+ * iterations that starts on an even one never wraps inside the pair. */
+enum { ARR_NONE = 0, ARR_EVEN = 1, ARR_ODD = 2 };
+
+/* U element pairs of one lane: x, and the array elements they start from. */
+template <int U, int ARR>
+struct batch_t {
+    f32x2 x[U];
+    int32_t a[2 * U];
+};
+
+/* Streams the pairs of a range through a chain.  Pair b + lane + u * st of a
+ * wave's batch at b (u < U) is the lane's u-th; a lane takes element pairs
+ * (8 B of x, 16 B of y), so every load instruction of a wave covers 512
+ * contiguous bytes of x and every store 1 KB of y.  The batch's place is
+ * wave-uniform and the lane's offset inside it is fixed, so the addresses
+ * cost the lanes nothing; the next batch's loads are in flight while the
+ * current one computes.  What is left at the end, less than a batch for the
+ * wave, is loaded in one round as well. */
+template <int U, int ARR, class AP, class CH>
+struct stream_t {
+    const CH &ch;
+    AP arr;
+    uint32_t alen;
+    const GLB char *xb;       /* pair 0 of the range                          */
+    GLB char *yb;
+    uint32_t nv;              /* pairs in the range                           */
+    uint32_t first;           /* array index of pair 0's first element        */
+    uint32_t inv;             /* floor((2^32 - 1) / alen)                     */
+    uint32_t st, dj;          /* pair stride of a lane, as an array step      */
+    uint32_t lane;
+    lane_acc &A;
+    lane_acc Ac[2];
+
+    template <int N, bool MASK>
+    __device__ __forceinline__ void load(batch_t<U, ARR> &B, uint32_t b) const
+    {
+        uint32_t j = 0;
+        if constexpr (ARR != ARR_NONE) {
+            /* (first + 2 (b + lane)) mod alen; the quotient from the
+             * reciprocal is at most one short */
+            const uint32_t k = first + 2u * (b + lane);
+            j = k - __umulhi(k, inv) * alen;
+            j = j >= alen ? j - alen : j;
+        }
 #pragma unroll
-        for (int u = 0; u < U; ++u) cur[u] = __builtin_nontemporal_load(&x2[v + (uint64_t)u * sp.P]);
-        if constexpr (ARR) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                ca[2 * u] = arr[j];
-                ca[2 * u + 1] = arr[j + 1 == alen ? 0 : j + 1];
+        for (int u = 0; u < N; ++u) {
+            const GLB char *base = xb + 8ull * (b + (uint32_t)u * st);
+            uint32_t off = 8u * lane;
+            if constexpr (MASK) {
+                /* pairs past the end load the last one (their results are
+                 * dropped) */
+                const uint32_t v = b + (uint32_t)u * st;
+                base = xb;
+                off = 8u * min(v + lane, nv - 1);
+            }
+            B.x[u] = __builtin_nontemporal_load((const GLB f32x2 *)(base + off));
+            if constexpr (ARR == ARR_EVEN) {
+                const i32x2 q = *(const typename AP::pair)(arr.p + j);
+                B.a[2 * u] = q.x;
+                B.a[2 * u + 1] = q.y;
+                j = mod_step(j, dj, alen);
+            } else if constexpr (ARR == ARR_ODD) {
+                B.a[2 * u] = arr.p[j];
+                B.a[2 * u + 1] = arr.p[j + 1 == alen ? 0 : j + 1];
                 j = mod_step(j, dj, alen);
             }
         }
-        for (;;) {
-            const uint64_t vn = v + step;
-            const bool more = vn + (uint64_t)(U - 1) * sp.P < nv1;
-            f32x2 nxt[U];
-            int32_t na[2 * U];
-            if (more) {
+    }
+
+    template <int N, bool MASK>
+    __device__ __forceinline__ void compute(const batch_t<U, ARR> &B, uint32_t b)
+    {
+        double xd[2 * N], acc[2 * N];
+        float xf[2 * N];
+        int32_t a[2 * N];
 #pragma unroll
-                for (int u = 0; u < U; ++u) nxt[u] = __builtin_nontemporal_load(&x2[vn + (uint64_t)u * sp.P]);
-                if constexpr (ARR) {
+        for (int e = 0; e < 2 * N; ++e) {
+            xf[e] = (e & 1) ? B.x[e / 2].y : B.x[e / 2].x;
+            xd[e] = (double)xf[e];
+            a[e] = ARR != ARR_NONE ? B.a[e] : 0;
+            acc[e] = ARR != ARR_NONE ? (double)a[e] : 0.0;
+        }
+        const bool w = ch.template eval<ARR != ARR_NONE, 2 * N>(acc, xd, xf, a);
+        A.bad |= (uint32_t)w;
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        na[2 * u] = arr[j];
-                        na[2 * u + 1] = arr[j + 1 == alen ? 0 : j + 1];
-                        j = mod_step(j, dj, alen);
-                    }
-                }
+        for (int u = 0; u < N; ++u) {
+            f64x2 r = {acc[2 * u], acc[2 * u + 1]};
+            const uint32_t v = b + (uint32_t)u * st;
+            if constexpr (MASK) {
+                const bool in = v + lane < nv;
+                if (in) __builtin_nontemporal_store(r, (GLB f64x2 *)(yb + 16ull * (v + lane)));
+                r.x = in ? r.x : 0.0;
+                r.y = in ? r.y : 0.0;
+            } else {
+                __builtin_nontemporal_store(r, (GLB f64x2 *)(yb + 16ull * v + 16u * lane));
             }
-            double xd[2 * U], acc[2 * U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                xd[2 * u] = (double)cur[u].x;
-                xd[2 * u + 1] = (double)cur[u].y;
-                acc[2 * u] = ARR ? (double)ca[2 * u] : 0.0;
-                acc[2 * u + 1] = ARR ? (double)ca[2 * u + 1] : 0.0;
-            }
-            sc.template chain<2 * U>(acc, xd);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                f64x2 r;
-                r.x = acc[2 * u];
-                r.y = acc[2 * u + 1];
-                __builtin_nontemporal_store(r, &y2[v + (uint64_t)u * sp.P]);
-                acc_add_f64(Ac[0], r.x);
-                acc_add_f64(Ac[1], r.y);
-            }
-            v = vn;
-            if (!more) break;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                cur[u] = nxt[u];
-                if constexpr (ARR) {
-                    ca[2 * u] = na[2 * u];
-                    ca[2 * u + 1] = na[2 * u + 1];
-                }
-            }
+            acc_add_f64(Ac[0], r.x);
+            acc_add_f64(Ac[1], r.y);
         }
     }
-    for (; v < nv1; v += sp.P) {
-        const f32x2 xv = __builtin_nontemporal_load(&x2[v]);
-        f64x2 r;
-        r.x = rt_one<ARR>(sc, arr, alen, (double)xv.x, 2 * v);
-        r.y = rt_one<ARR>(sc, arr, alen, (double)xv.y, 2 * v + 1);
-        __builtin_nontemporal_store(r, &y2[v]);
-        acc_add_f64(Ac[0], r.x);
-        acc_add_f64(Ac[1], r.y);
+
+    template <int N>
+    __device__ __forceinline__ void rest(uint32_t b)
+    {
+        batch_t<U, ARR> B;
+        load<N, true>(B, b);
+        compute<N, true>(B, b);
     }
-    if (phi < sp.hi && sp.p == 0) {
-        const double r = rt_one<ARR>(sc, arr, alen, (double)x[phi], phi);
-        y[phi] = r;
-        acc_add_f64(A, r);
+
+    /* next(b): the wave's batch after the one at b. */
+    template <class NEXT>
+    __device__ __forceinline__ void run(uint32_t b, NEXT &&next)
+    {
+        auto full = [&](uint32_t q) { return (uint64_t)q + 63u + (uint64_t)(U - 1) * st < nv; };
+        Ac[0] = Ac[1] = acc_zero();
+        bool have = full(b);
+        if (have) {
+            batch_t<U, ARR> cur;
+            load<U, false>(cur, b);
+            uint32_t since = 0;
+            while (have) {
+                const uint32_t bn = next(b);
+                const bool more = full(bn);
+                batch_t<U, ARR> nxt;
+                if (more) load<U, false>(nxt, bn);
+                compute<U, false>(cur, b);
+                /* a batch adds U values to each bin: flush well before 2^16 */
+                if (++since == 2048) {
+                    acc_merge(A, Ac[0]);
+                    acc_merge(A, Ac[1]);
+                    acc_flush(A);
+                    Ac[0] = Ac[1] = acc_zero();
+                    since = 0;
+                }
+                b = bn;
+                have = more;
+                cur = nxt;
+            }
+        }
+        if (b < nv) {
+            const uint32_t left = min((uint32_t)U, (nv - b + st - 1) / st);
+            if (U >= 8 && left > 4) rest<U>(b);
+            else if (U >= 4 && left > 2) rest<U < 4 ? U : 4>(b);
+            else rest<U < 2 ? U : 2>(b);
+        }
+        acc_merge(A, Ac[0]);
+        acc_merge(A, Ac[1]);
     }
-    acc_merge(A, Ac[0]);
-    acc_merge(A, Ac[1]);
+};
+
+/* A pointer to a body's array, and the type of a pair of its elements. */
+struct lds_array {
+    typedef const LDSQ i32x2 *pair;
+    const LDSQ int32_t *p;
+};
+struct glb_array {
+    typedef const GLB i32x2 *pair;
+    const GLB int32_t *p;
+};
+
+/* The next block of the team's range, claimed by this wave from the counter
+ * in the team's control block. */
+__device__ __forceinline__ uint32_t claim_block(uint32_t lane)
+{
+    LDSQ uint32_t *ctr = (LDSQ uint32_t *)(dsr_lds + offsetof(cb_header, blocks));
+    uint32_t c = 0;
+    if (lane == 0) c = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return c;
 }
 
-template <int U, class AP, class SC>
-__device__ __forceinline__ void rt_spans(const SC &sc, AP arr, const dsr_dloop &L, uint32_t alen, span_t sp,
-                                         lane_acc &A, uint32_t *claim, uint32_t lane)
+/* One range [sp.lo, sp.hi) of the loop through a chain.  BLOCKS: the team's
+ * waves claim batches of 64 * U pairs from the team's counter, so a wave on a
+ * SIMD it shares with fewer others takes more of them (three worker waves per
+ * team and two teams per CU leave some SIMDs two worker waves and some one);
+ * a claim is taken one batch ahead.  Else lane sp.p of sp.P takes every
+ * sp.P-th pair.  An odd first element and an odd last one go to lanes 0 and 1
+ * of the range. */
+template <int U, int ARR, bool BLOCKS, class AP, class CH>
+__device__ __forceinline__ void chain_range(const CH &ch, AP arr, uint32_t alen, const dsr_dloop &L, span_t sp,
+                                            uint32_t lane, lane_acc &A)
 {
+    const uint32_t lo = uniform((uint32_t)sp.lo), hi = uniform((uint32_t)sp.hi);
+    if (lo >= hi) return;
     const GLB float *x = (const GLB float *)L.in;
     GLB double *y = (GLB double *)L.out;
-    const bool balanced = uniform(L.ni + L.nf) >= DSR_BALANCE_MIN;
-    if (alen)
-        for_spans(L, sp, lane, claim, A, [&](span_t q) { fma_rt_span<U, true>(sc, arr, alen, x, y, q, A); },
-                  balanced);
-    else
-        for_spans(L, sp, lane, claim, A, [&](span_t q) { fma_rt_span<U, false>(sc, arr, alen, x, y, q, A); },
-                  balanced);
+    const uint32_t p0 = (lo + 1) >> 1, p1 = max(p0, hi >> 1);
+    const bool edge = (sp.p == 0 && (lo & 1u)) || (sp.p == 1 && (hi & 1u));
+    const uint32_t ie = sp.p == 0 ? lo : hi - 1;
+    const float xe = edge ? x[ie] : 0.0f;
+    const uint32_t st = BLOCKS ? 64u : uniform(sp.P);
+    stream_t<U, ARR, AP, CH> S{ch, arr, alen, (const GLB char *)x + 8ull * p0, (GLB char *)y + 16ull * p0, p1 - p0,
+                               ARR != ARR_NONE ? (2u * p0) % alen : 0u,
+                               ARR != ARR_NONE ? 0xFFFFFFFFu / alen : 0u, st, ARR != ARR_NONE ? (2u * st) % alen : 0u,
+                               lane, A, {}};
+    uint32_t b = uniform(sp.p - lane), ahead = 0;
+    if (BLOCKS) {
+        b = uniform(claim_block(lane)) * (64u * U);
+        ahead = claim_block(lane);
+    }
+    S.run(b, [&](uint32_t q) {
+        if (!BLOCKS) return q + U * st;
+        const uint32_t n = uniform(ahead) * (64u * U);
+        ahead = claim_block(lane);
+        return n;
+    });
+    if (__any(edge)) {
+        const float xf[1] = {xe};
+        const double xd[1] = {(double)xe};
+        int32_t a[1] = {0};
+        if constexpr (ARR != ARR_NONE) a[0] = edge ? arr.p[ie % alen] : 0;
+        double acc[1] = {ARR != ARR_NONE ? (double)a[0] : 0.0};
+        const bool w = ch.template eval<ARR != ARR_NONE, 1>(acc, xd, xf, a);
+        if (edge) {
+            y[ie] = acc[0];
+            A.bad |= (uint32_t)w;
+            acc_add_f64(A, acc[0]);
+        }
+    }
 }
 
-/* Body entry for the run-time chain, frame in LDS (offset `off` in the
- * dynamic LDS) or in HBM (`fb`); the array follows the scalars at the next
- * 16-byte boundary.  U element pairs per lane and batch. */
-template <int U>
-__device__ __forceinline__ void body_fma_rt(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp,
-                                            lane_acc &A, uint32_t *claim, uint32_t lane)
+/* A chain over the team's part of the loop: its static range by blocks, or
+ * under the dynamic tail its static part and then the blocks its wave claims
+ * from the loop's device counter.  The lean instances run static ranges only,
+ * every wave its fixed per-lane share: 0.3-1.0 us faster there per
+ * 2^24-element region than blocks for 8 to 32 scalars, and the same below. */
+template <int U, int ARR, bool LEAN, class AP, class CH>
+__device__ __forceinline__ void chain_loop(const CH &ch, AP arr, uint32_t alen, const dsr_dloop &L, span_t sp,
+                                           uint32_t lane, uint32_t *claim, lane_acc &A)
+{
+    if constexpr (LEAN) {
+        chain_range<U, ARR, false>(ch, arr, alen, L, sp, lane, A);
+        return;
+    }
+    if (L.schedule == DSR_SCHED_STATIC) {
+        chain_range<U, ARR, true>(ch, arr, alen, L, sp, lane, A);
+        return;
+    }
+    uint32_t c = 0, since = 0;
+    for (bool tail = false;; tail = true) {
+        /* the next claim is issued before the current block runs, so its
+         * latency overlaps the work */
+        if (tail && lane == 0) c = atomicAdd(claim, 1u);
+        chain_range<U, ARR, false>(ch, arr, alen, L, sp, lane, A);
+        if (!tail && lane == 0) c = atomicAdd(claim, 1u);
+        /* a block adds at most 1024 values per lane: flush well before 2^16 */
+        if (++since == 16) { acc_flush(A); since = 0; }
+        const uint64_t lo = L.dyn_start + (uint64_t)uniform(c) * L.block;
+        if (lo >= L.n) return;
+        sp = span_t{lo, min(L.n, lo + (uint64_t)L.block), lane, 64u};
+    }
+}
+
+/* The chain's shared variables, published as a frame ([24 B exact sum][nf
+ * fp64][ni int32][pad to 16][array]) or, REFS, as the list of references of
+ * section 5.1: lane j reads reference 1 + j, then scalar j through it. */
+template <int U, bool LEAN>
+__device__ __forceinline__ void body_chain(const team_t &T, bool refs, frame_t f, const dsr_dloop &L, span_t sp,
+                                           lane_acc &A, uint32_t *claim, uint32_t lane)
 {
     const uint32_t ni = uniform(L.ni), nf = uniform(L.nf), alen = uniform(L.alen);
-    const uint32_t aoff = (24 + 8 * nf + 4 * ni + 15) & ~15u;
-    if (f.space == SPACE_LDS) {
+    double sv = 0.0;
+    uint32_t aspace = f.space, aoff = f.off + ((24 + 8 * nf + 4 * ni + 15) & ~15u);
+    if (refs) {
+        const uint32_t *lst = f.space == SPACE_LIST ? ref_list(T) : (const uint32_t *)frame_hbm(T, f);
+        if (uniform(L.deref) && alen == 0) {
+            const list_chain ch{lst, T.stack_lds, T.stack_hbm, ni, nf};
+            chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, lane, claim, A);
+            return;
+        }
+        if (lane < ni + nf) {
+            const uint32_t sp_ = lst[2 * (1 + lane)], off = lst[2 * (1 + lane) + 1];
+            const uint8_t *p = sp_ == SPACE_LDS ? T.stack_lds + off : T.stack_hbm + off;
+            sv = lane < ni ? (double)*(const int32_t *)p : *(const double *)p;
+        }
+        if (alen) {
+            aspace = uniform(lst[2 * (1 + ni + nf)]);
+            aoff = uniform(lst[2 * (1 + ni + nf) + 1]);
+        }
+    } else if (f.space == SPACE_LDS) {
         const LDSQ uint8_t *fb = (const LDSQ uint8_t *)(dsr_lds + cb_bytes(T.nw) + f.off);
-        const lds_scalars sc{(const LDSQ int32_t *)(fb + 24 + 8 * nf), (const LDSQ double *)(fb + 24), ni, nf};
-        rt_spans<U>(sc, (const LDSQ int32_t *)(fb + aoff), L, alen, sp, A, claim, lane);
+        if (lane < ni) sv = (double)*(const LDSQ int32_t *)(fb + 24 + 8 * nf + 4 * lane);
+        else if (lane < ni + nf) sv = *(const LDSQ double *)(fb + 24 + 8 * (lane - ni));
     } else {
         const GLB uint8_t *fb = (const GLB uint8_t *)frame_hbm(T, f);
-        double sv = 0.0;
         if (lane < ni) sv = (double)*(const GLB int32_t *)(fb + 24 + 8 * nf + 4 * lane);
         else if (lane < ni + nf) sv = *(const GLB double *)(fb + 24 + 8 * (lane - ni));
-        const lane_scalars sc{sv, ni + nf};
-        rt_spans<U>(sc, (const GLB int32_t *)(fb + aoff), L, alen, sp, A, claim, lane);
     }
+    const rt_chain ch = make_chain(sv, ni, nf, lane);
+    constexpr int UA = U > 4 ? 4 : U;
+    /* an array a list refers to may lie on a 4-byte boundary alone; in global
+     * memory arrays are read element by element as well (one body less) */
+    if (!alen)
+        chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, lane, claim, A);
+    else if (aspace != SPACE_LDS)
+        chain_loop<UA, ARR_ODD, LEAN>(ch, glb_array{(const GLB int32_t *)(T.stack_hbm + aoff)}, alen, L, sp, lane, claim, A);
+    else if ((alen & 1u) || (aoff & 7u))
+        chain_loop<UA, ARR_ODD, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, lane,
+                               claim, A);
+    else
+        chain_loop<UA, ARR_EVEN, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, lane,
+                                claim, A);
+}
+
+/* Shared scalars are wave-uniform: read once as uniform values, they live in
+ * scalar registers. */
+__device__ __forceinline__ uint32_t uniform_u32(const uint8_t *p)
+{
+    return uniform(*(const uint32_t *)p);
 }
 
 /* Shared-array gather; arrays at `arr` (LDS or global pointer), `len`
@@ -1147,18 +1108,15 @@ __device__ __forceinline__ const uint8_t *frame_ptr(const team_t &T, frame_t f)
     return f.space == SPACE_LDS ? frame_lds(T, f) : frame_hbm(T, f);
 }
 
-/* VARIANT selects which fixed-length fma chains are compiled into the
- * kernel: the worker code is specialised to the bodies a region can
- * publish, so a region of short chains does not pay the register budget
- * of the longest one.  0: chains up to 8+8 scalars (workgroups of up to
- * 512 threads); 1: adds 16+16; 2: adds 32+32; -1 (workgroups above 512
- * threads, 128 registers per lane): run-time chains only.  Other lengths
- * (at most 64 scalars) use the run-time chain, one pair per batch at -1. */
+/* The general instances run every body (fma chains with run-time counts).
+ * VARIANT -1 (workgroups above 512 threads, 128 registers per lane) takes
+ * fewer element pairs per batch. */
 template <int VARIANT>
 __device__ __forceinline__ void run_body(team_t &T, uint32_t body, frame_t f, const dsr_dloop &L, span_t sp,
                                          lane_acc &A, uint32_t *claim, uint32_t member,
                                          uint32_t members, uint32_t &inner_pushes, GLB uint32_t *tr)
 {
+    constexpr int U = VARIANT < 0 ? 1 : 8;
     const uint32_t lane = T.lane;
     switch (body) {
     case DSR_BODY_AFFINE_XOR: {
@@ -1171,62 +1129,10 @@ __device__ __forceinline__ void run_body(team_t &T, uint32_t body, frame_t f, co
         for_spans(L, sp, lane, claim, A, [&](span_t q) { affine_span(a, b, c, d, out, q, A); });
         break;
     }
-    case DSR_BODY_FMA_CHAIN: {
-        const uint32_t ni = L.ni, nf = L.nf;
-        if (VARIANT >= 0 && L.alen == 0) {
-            if (ni == 1 && nf == 0) { body_fma_fixed<1, 0>(T, f, L, sp, A, claim, lane); break; }
-            if (ni == 1 && nf == 1) { body_fma_fixed<1, 1>(T, f, L, sp, A, claim, lane); break; }
-            if (ni == 2 && nf == 2) { body_fma_fixed<2, 2>(T, f, L, sp, A, claim, lane); break; }
-            if (ni == 4 && nf == 4) { body_fma_fixed<4, 4>(T, f, L, sp, A, claim, lane); break; }
-            if (ni == 8 && nf == 8) { body_fma_fixed<8, 8>(T, f, L, sp, A, claim, lane); break; }
-            if constexpr (VARIANT >= 1)
-                if (ni == 16 && nf == 16) { body_fma_fixed<16, 16>(T, f, L, sp, A, claim, lane); break; }
-            if constexpr (VARIANT >= 2)
-                if (ni == 32 && nf == 32) { body_fma_fixed<32, 32>(T, f, L, sp, A, claim, lane); break; }
-        }
-        /* run-time chain (the host admits at most 64 scalars); workgroups
-         * above 512 threads have 128 registers per lane */
-        body_fma_rt<VARIANT < 0 ? 1 : DSR_RT_PAIRS>(T, f, L, sp, A, claim, lane);
+    case DSR_BODY_FMA_CHAIN:
+    case DSR_BODY_FMA_CHAIN_REFS:
+        body_chain<U, false>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, A, claim, lane);
         break;
-    }
-    case DSR_BODY_FMA_CHAIN_REFS: {
-        /* the wrapper of section 5.1 over a list of references: lane j
-         * reads reference 1 + j (scalar j), then the scalar through it; the
-         * array's reference is read by every lane */
-        const uint32_t ni = uniform(L.ni), nf = uniform(L.nf), alen = uniform(L.alen);
-        const uint32_t *lst = f.space == SPACE_LIST ? ref_list(T) : (const uint32_t *)frame_hbm(T, f);
-        double sv = 0.0;
-        if (lane < ni + nf) {
-            const uint32_t sp_ = lst[2 * (1 + lane)], off = lst[2 * (1 + lane) + 1];
-            const uint8_t *p = sp_ == SPACE_LDS ? T.stack_lds + off : T.stack_hbm + off;
-            sv = lane < ni ? (double)*(const int32_t *)p : *(const double *)p;
-        }
-        /* with the counts of a compiled fixed chain, run that chain */
-        if (VARIANT >= 0 && alen == 0 && !uniform(L.deref)) {
-            if (ni == 1 && nf == 0) { lanes_fma_fixed<1, 0>(sv, L, sp, A, claim, lane); break; }
-            if (ni == 1 && nf == 1) { lanes_fma_fixed<1, 1>(sv, L, sp, A, claim, lane); break; }
-            if (ni == 2 && nf == 2) { lanes_fma_fixed<2, 2>(sv, L, sp, A, claim, lane); break; }
-            if (ni == 4 && nf == 4) { lanes_fma_fixed<4, 4>(sv, L, sp, A, claim, lane); break; }
-            if (ni == 8 && nf == 8) { lanes_fma_fixed<8, 8>(sv, L, sp, A, claim, lane); break; }
-        }
-        constexpr int U = VARIANT < 0 ? 1 : DSR_RT_PAIRS;
-        if (uniform(L.deref) && alen == 0) {
-            const list_scalars ls{lst, T.stack_lds, T.stack_hbm, ni, nf};
-            rt_spans<U>(ls, (const GLB int32_t *)nullptr, L, 0, sp, A, claim, lane);
-            break;
-        }
-        const lane_scalars sc{sv, ni + nf};
-        if (alen) {
-            const uint32_t asp = uniform(lst[2 * (1 + ni + nf)]), aoff = uniform(lst[2 * (1 + ni + nf) + 1]);
-            if (asp == SPACE_LDS)
-                rt_spans<U>(sc, (const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff), L, alen, sp, A, claim, lane);
-            else
-                rt_spans<U>(sc, (const GLB int32_t *)(T.stack_hbm + aoff), L, alen, sp, A, claim, lane);
-        } else {
-            rt_spans<U>(sc, (const GLB int32_t *)nullptr, L, 0, sp, A, claim, lane);
-        }
-        break;
-    }
     case DSR_BODY_GATHER:
         for_spans(L, sp, lane, claim, A, [&](span_t q) { body_gather(T, f, L, q); });
         break;
@@ -1280,6 +1186,9 @@ __device__ __forceinline__ void participate(team_t &T, const dsr_dregion &R, con
                                             const dsr_dloop &L, uint32_t &inner_pushes)
 {
     const uint32_t nwork = C.master_joins ? T.nw : T.nw - 1;
+    /* keeps the compiler from computing every body's lane offsets ahead of the
+     * await loop and holding them in registers across all bodies */
+    asm volatile("" : "+v"(T.lane));
     lane_acc A = acc_zero();
     GLB uint32_t *tr = (C.trace && R.trace) ? (GLB uint32_t *)(R.trace + (uint64_t)team * DSR_TRACE_WORDS) : nullptr;
     if (tr && T.lane == 0) tr[96 + 2 * T.wave] = (uint32_t)wall_clock64();
@@ -1582,8 +1491,8 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
 }
 
 /* Sum `cnt` 192-bit partials (three words each, `stride` partials apart)
- * with the whole wave: each lane issues up to eight independent loads per
- * round, so up to 512 partials cost one memory round trip. */
+ * with the whole wave: each lane takes up to eight partials per round, so up
+ * to 512 cost one memory round trip. */
 __device__ __forceinline__ i192 sum_partials(const uint64_t *base, uint32_t cnt, uint32_t stride, uint32_t lane)
 {
     i192 s{0, 0, 0};
@@ -1595,10 +1504,11 @@ __device__ __forceinline__ i192 sum_partials(const uint64_t *base, uint32_t cnt,
         }
         return wave_sum192(s);
     }
-    for (uint32_t j0 = 0; j0 < cnt; j0 += 512) {
-        uint64_t w[8][3];
+    constexpr uint32_t PER = 8;
+    for (uint32_t j0 = 0; j0 < cnt; j0 += 64 * PER) {
+        uint64_t w[PER][3];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (uint32_t u = 0; u < PER; ++u) {
             const uint32_t j = j0 + 64u * u + lane;
             const uint64_t *pp = base + (uint64_t)DSR_PART_WORDS * j * stride;
             const bool in = j < cnt;
@@ -1607,7 +1517,7 @@ __device__ __forceinline__ i192 sum_partials(const uint64_t *base, uint32_t cnt,
             w[u][2] = in ? load_dev(pp + 2) : 0;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s = add192(s, i192{w[u][0], w[u][1], w[u][2]});
+        for (uint32_t u = 0; u < PER; ++u) s = add192(s, i192{w[u][0], w[u][1], w[u][2]});
     }
     return wave_sum192(s);
 }
@@ -2136,16 +2046,25 @@ __device__ __forceinline__ void lean_chain(const team_t &T, frame_t f, const dsr
                        : *(const GLB uint32_t *)(T.stack_hbm + f.off + 24 + 4 * k);
     }
     auto word = [&](int k) { return (uint32_t)__builtin_amdgcn_readlane(w[k >> 6], k & 63); };
-    double s[NI + NF];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) s[k] = (double)(int32_t)word(2 * NF + k);
+    fixed_chain<NI, NF> ch;
 #pragma unroll
     for (int k = 0; k < NF; ++k)
-        s[NI + k] = __longlong_as_double((long long)((uint64_t)word(2 * k) | ((uint64_t)word(2 * k + 1) << 32)));
-    /* every wave takes its fixed per-lane share of the team's range: 0.3-1.0 us
-     * faster per 2^24-element region than the balanced block split of the
-     * general instances for 8 to 32 scalars, and the same below */
-    fma_span<NI, NF>(s, (const GLB float *)L.in, (GLB double *)L.out, sp, A);
+        ch.s[k] = __longlong_as_double((long long)((uint64_t)word(2 * k) | ((uint64_t)word(2 * k + 1) << 32)));
+    /* all the scalars, one per lane, int32 ones first */
+    double sv = 0.0;
+    if constexpr (NI > 1) {
+        const uint32_t at = T.lane < NI ? 2 * NF + T.lane : 2 * ((T.lane - NI) & 31u);
+        auto pick = [&](uint32_t k) {
+            const uint32_t lo = (uint32_t)__shfl((int)w[0], k & 63u, 64), hi = (uint32_t)__shfl((int)w[1], k & 63u, 64);
+            return k < 64 ? lo : hi;
+        };
+        const uint32_t a = pick(at), b = pick(at + 1);
+        sv = T.lane < NI ? (double)(int32_t)a : __longlong_as_double((long long)((uint64_t)a | ((uint64_t)b << 32)));
+    } else {
+        sv = (double)(int32_t)word(2 * NF);
+    }
+    ch.all = make_chain(sv, NI, NF, T.lane);
+    chain_range<8, ARR_NONE, false>(ch, glb_array{nullptr}, 0, L, sp, T.lane, A);
 }
 
 __device__ __forceinline__ void lean_affine(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp, lane_acc &A)
@@ -2159,10 +2078,34 @@ __device__ __forceinline__ void lean_affine(const team_t &T, frame_t f, const ds
     affine_span(a, b, c, d, (GLB int32_t *)L.out, sp, A);
 }
 
+/* Master wave, section 5.2: resolve each (frame, offset) reference of `tab` to
+ * a stack address and write the list on chip, or to a list frame `lf` on the
+ * HBM stack when it is longer than the on-chip list or `global` is set.  What
+ * is published is the list's place; SPACE_NONE when it does not fit. */
+__device__ __forceinline__ frame_t post_list(const team_t &T, stack_t &S, const uint32_t *tab, uint32_t n, uint32_t global,
+                                             frame_t &lf)
+{
+    frame_t f{SPACE_LIST, 0, n};
+    uint32_t *dst = ref_list(T);
+    if (n > DSR_REF_LIST || global) {
+        lf = push(T, S, 8 * n, true);
+        if (lf.space == SPACE_NONE) return lf;
+        dst = (uint32_t *)frame_hbm(T, lf);
+        f = frame_t{SPACE_HBM, lf.off, n};
+    }
+    for (uint32_t q = T.lane; q < n; q += 64) {
+        const uint32_t *fte = frame_table(T) + 4 * tab[2 * q];
+        dst[2 * q] = fte[0];
+        dst[2 * q + 1] = fte[1] + tab[2 * q + 1];
+    }
+    return f;
+}
+
 template <int MAXWG, int VARIANT>
 __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
 {
     constexpr bool gather = VARIANT == DSR_LEAN_GATHER, affine = VARIANT == DSR_LEAN_AFFINE;
+    constexpr bool chains = VARIANT == DSR_LEAN_ANY_CHAIN;
     touch_args<offsetof(dsr_lean, image)>();
     const uint32_t team = blockIdx.x;
     team_t T = team_bind(dsr_lds, A.nw, A.lds_cap, A.threshold, A.hbm_base + (uint64_t)team * A.hbm_slot_bytes,
@@ -2186,7 +2129,7 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
     if (master && 16u * T.lane < A.inl_img) img = *(const i32x4 *)(A.image + 16u * T.lane);
     for (;;) {
         uint32_t body = DSR_BODY_TERMINATE, loop = 0, red = 0xffffffffu;
-        frame_t f{SPACE_NONE, 0, 0};
+        frame_t f{SPACE_NONE, 0, 0}, lf{SPACE_NONE, 0, 0};
         if (master) {
             while (k < A.n_ops && !err) {
                 const dsr_op op = A.inl_ops ? A.inl_op[k] : load_const(A.ops + k);
@@ -2222,7 +2165,17 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                                    op.nbytes);
                     }
                 } else if (op.kind == DSR_OP_PUBLISH) {
-                    f = frame_at(T, S, op.frame);
+                    if (chains && op.body == DSR_BODY_FMA_CHAIN_REFS) {
+                        f = post_list(T, S, (const uint32_t *)(A.init + op.init_off), op.nbytes, A.global_lists, lf);
+                        if (f.space == SPACE_NONE) { err = DSR_E_NOMEM; break; }
+                        if (tr && T.lane == 0) {
+                            tr[89] = f.space;
+                            tr[90] = f.off;
+                            tr[91] = op.nbytes;
+                        }
+                    } else {
+                        f = frame_at(T, S, op.frame);
+                    }
                     body = op.body;
                     loop = op.loop;
                     red = op.red;
@@ -2258,6 +2211,8 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                 else body_gather_nested(T, f, L, sp, T.wave, nwork, inner_pushes, tr);
             } else if constexpr (affine) {
                 lean_affine(T, f, L, sp, acc);
+            } else if constexpr (chains) {
+                body_chain<8, true>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, acc, nullptr, T.lane);
             } else {
                 lean_chain<DSR_LEAN_NI(VARIANT - DSR_LEAN_BASE), DSR_LEAN_NF(VARIANT - DSR_LEAN_BASE)>(T, f, L, sp, acc);
             }
@@ -2285,11 +2240,19 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
              * every outstanding memory operation of the wave, its loop stores
              * included */
             uint64_t *pp = A.partials + ((uint64_t)red * A.teams + team) * DSR_PART_WORDS;
+            if (chains && body == DSR_BODY_FMA_CHAIN_REFS) {
+                /* the shared sum is where reference 0 points */
+                const uint32_t *lst = f.space == SPACE_LIST ? ref_list(T) : (const uint32_t *)frame_hbm(T, f);
+                f.space = uniform(lst[0]);
+                f.off = uniform(lst[1]);
+            }
             if (f.space == SPACE_LDS)
                 store_partial(pp, update_sum((LDSQ uint64_t *)(dsr_lds + cb_bytes(T.nw) + f.off), tot, affine, T.lane),
                               T.lane);
             else
                 store_partial(pp, update_sum((GLB uint64_t *)(T.stack_hbm + f.off), tot, affine, T.lane), T.lane);
+            /* a global reference list dies with its parallel region */
+            if (chains && lf.space == SPACE_HBM) pop(T, S);
         }
     }
     if (master) {

@@ -1,0 +1,145 @@
+"""The fma chain's int32 steps taken as one step, and when they must not be:
+bit for bit against the oracle's step-by-step chain with scalars, inputs and
+array elements at and beyond the bounds where one step rounds differently
+(partial sums around 2^29, x off the 2^-24 grid, large elements), with
+denormal and non-finite inputs, at ragged sizes around a wave's batch."""
+import numpy as np
+import pytest
+
+from oracle import ref as R
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+from paper_1711_10413_amd import dsr as D  # noqa: E402
+
+I31 = (1 << 31) - 1
+
+
+def scalars(kind, ni, rs):
+    if kind == "small":
+        return rs.randint(-(1 << 20), (1 << 20) + 1, ni).astype(np.int32)
+    if kind == "at_bound":                    # partial sums reach 2^29 exactly
+        s = np.zeros(ni, np.int32)
+        s[0] = (1 << 29) - 1
+        s[1:2] = 1
+        s[2:] = np.tile([-3, 3], ni)[:max(0, ni - 2)]
+        return s
+    if kind == "over_bound":                  # one partial sum is 2^29 + 1
+        s = scalars("at_bound", ni, rs)
+        s[0] += 1
+        return s
+    if kind == "huge":                        # cancelling 31-bit scalars
+        return np.tile(np.array([I31, -I31, I31 - 7, -I31 + 3], np.int32), ni)[:ni]
+    return np.zeros(ni, np.int32)
+
+
+def inputs(kind, n, rs):
+    x = (rs.randint(-(1 << 23), 1 << 23, n) * 2.0 ** -23).astype(np.float32)
+    if kind == "grid24":                      # the finest grid the array bound allows
+        x = (rs.randint(-(1 << 24), 1 << 24, n) * 2.0 ** -24).astype(np.float32)
+    elif kind == "off_grid":
+        x[::5] = rs.standard_normal(len(x[::5])).astype(np.float32) * np.float32(2.0 ** -30)
+    elif kind == "denormal":
+        x[::3] = np.float32(1e-40)
+        x[1::3] = -np.float32(0.0)
+    elif kind == "wide":                      # large x on the grid
+        x *= np.float32(2.0 ** 9)
+    return x
+
+
+def chain_region(ctx, form, n, teams, s_i, s_f, arr, x, y):
+    img, size = D.fma_chain_frame(s_i, s_f, arr)
+    ni, nf, alen = len(s_i), len(s_f), 0 if arr is None else len(arr)
+    args = {"inp": x.data_ptr(), "out": y.data_ptr(), "ni": ni, "nf": nf, "alen": alen}
+    r = D.dsr_region_begin(ctx, teams)
+    f = D.dsr_push(r, size, img)
+    if form == "list":
+        refs = [(f, 0)] + [(f, 24 + 8 * nf + 4 * k) for k in range(ni)] + [(f, 24 + 8 * k) for k in range(nf)]
+        if alen:
+            refs.append((f, (24 + 8 * nf + 4 * ni + 15) // 16 * 16))
+        D.dsr_publish_list(r, refs, D.DSR_BODY_FMA_CHAIN_REFS, n, **args)
+    else:
+        D.dsr_publish(r, f, D.DSR_BODY_FMA_CHAIN, n, **args)
+    D.dsr_pop(r, f)
+    return r
+
+
+def exact_total(want):
+    """The sum in units of 2^-75, or None when a value lies outside the exact-sum
+    window (|y| < 2^32, a multiple of 2^-75)."""
+    if not (np.all(np.isfinite(want)) and np.all(np.abs(want) < 2.0 ** 32)):
+        return None
+    units = np.ldexp(want, 75)
+    if not np.array_equal(units, np.trunc(units)):
+        return None
+    return sum(int(v) for v in units)
+
+
+def check(form, wg, slab, n, teams, s_i, s_f, arr, x_np):
+    ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=slab, hbm_slab_bytes=65536, max_teams=max(8, teams))
+    x = torch.from_numpy(x_np).cuda()
+    y = torch.full((n,), 5.0, dtype=torch.float64, device="cuda")
+    r = chain_region(ctx, "frame" if form == "batch" else form, n, teams, s_i, s_f, arr, x, y)
+    stream = torch.cuda.current_stream().cuda_stream
+    want = R.fma_chain(x_np, s_i, s_f, arr)
+    if form == "batch":
+        b = D.dsr_batch_create(ctx, [r])
+        D.dsr_batch_launch(b, stream)
+        st = D.dsr_batch_sync(b)
+        fixed = D.dsr_batch_result(b, 0)[2]
+        D.dsr_batch_free(b)
+    else:
+        D.dsr_launch(r, stream)
+        st = D.dsr_region_sync(r)
+        fixed = D.dsr_region_reduction(r, 0)[2]
+    got = y.cpu().numpy()
+    assert np.array_equal(got, want, equal_nan=True)
+    assert np.array_equal(np.signbit(got), np.signbit(want)) or not np.all(np.isfinite(want))
+    total = exact_total(want)
+    assert st == (D.DSR_E_RANGE if total is None else 0)
+    if total is not None:
+        assert fixed == total
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("form,wg,slab", [("frame", 256, 40960), ("list", 256, 40960), ("frame", 512, 0),
+                                          ("frame", 1024, 40960), ("batch", 128, 40960), ("batch", 256, 0)])
+@pytest.mark.parametrize("sk", ["small", "at_bound", "over_bound", "huge", "zero"])
+@pytest.mark.parametrize("xk", ["plain", "grid24", "off_grid", "denormal", "wide"])
+@pytest.mark.parametrize("ni,nf,alen", [(4, 4, 0), (32, 0, 0), (2, 1, 6), (7, 3, 33), (32, 16, 1000)])
+def test_steps(form, wg, slab, sk, xk, ni, nf, alen):
+    rs = np.random.RandomState(ni * 100 + alen)
+    s_i = scalars(sk, ni, rs)
+    s_f = (rs.randint(0, 1 << 20, nf) * 2.0 ** -19 - 1.0)
+    arr = rs.randint(-(1 << 16), 1 << 16, alen).astype(np.int32) if alen else None
+    if alen and sk == "at_bound":
+        arr[::2] = I31
+    check(form, wg, slab, 4099, 2, s_i, s_f, arr, inputs(xk, 4099, rs))
+
+
+@pytest.mark.parametrize("ni,nf,alen", [(8, 8, 0), (5, 2, 0), (4, 2, 10)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_non_finite_inputs(ni, nf, alen, bad):
+    """A chain of mixed signs over an infinity is NaN, their sum over it is not:
+    the batches that hold one run every step, and the region reports RANGE."""
+    rs = np.random.RandomState(5)
+    s_i = scalars("small", ni, rs)
+    s_i[0], s_i[1] = 3, -1
+    arr = rs.randint(0, 100, alen).astype(np.int32) if alen else None
+    x = inputs("plain", 3001, rs)
+    x[[0, 700, 701, 2999, 3000]] = bad
+    for form, wg in (("frame", 256), ("list", 256), ("batch", 128)):
+        check(form, wg, 4096, 3001, 3, s_i, rs.randint(1, 9, nf).astype(np.float64), arr, x)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 127, 128, 129, 255, 511, 1023, 1024, 1025, 2047, 3071, 3073, 8191])
+@pytest.mark.parametrize("ni,nf,alen", [(1, 0, 0), (16, 16, 0), (3, 2, 0), (6, 3, 14), (6, 3, 1)])
+def test_ragged_sizes(n, ni, nf, alen):
+    rs = np.random.RandomState(n)
+    s_i = scalars("small", ni, rs)
+    s_f = rs.randint(0, 1 << 53, nf) * 2.0 ** -52 - 1.0
+    arr = rs.randint(0, 1 << 16, alen).astype(np.int32) if alen else None
+    for form, wg, slab in (("frame", 64, 4096), ("frame", 256, 4096), ("list", 192, 0), ("batch", 128, 4096),
+                           ("frame", 1024, 0)):
+        check(form, wg, slab, n, 1 + n // 1500, s_i, s_f, arr, inputs("plain", n, rs))
