@@ -44,23 +44,30 @@ struct dsr_dloop {
     uint32_t pad;
 };
 
-/* Per-launch result block (device memory, written by the last team).  The
- * fields the host reads come first: it copies only DSR_RESULT_HOST_BYTES. */
+/* What a launch leaves for the host, written by the last team: in pinned host
+ * memory for a region's own launches and a batch's, so that nothing is left to
+ * copy when the host waits for it, else in the region's result block. */
+struct dsr_hred {
+    uint64_t fixed[3];
+    double f64;
+    int64_t i64;
+};
+struct dsr_hres {
+    dsr_hred red[DSR_MAX_RED];
+    int32_t status;        /* the launch's error                             */
+    int32_t pad;
+};
+
+/* Per-launch counters and results in device memory. */
 struct dsr_dresult {
     int32_t error;         /* accumulating: first team error of this launch */
     uint32_t arrived;      /* teams that finished; reset by the last team   */
-    int32_t final_error;   /* the launch's error, written by the last team  */
-    uint32_t done;         /* launch counter, bumped by the last team       */
-    uint64_t fixed[DSR_MAX_RED][3];
-    double f64[DSR_MAX_RED];
-    int64_t i64[DSR_MAX_RED];
-    /* device-side counters from here on */
+    dsr_hres out;          /* where no host memory takes the results        */
     uint32_t claim[DSR_MAX_LOOPS]; /* dynamic-tail block counters; reset by the last team */
     /* arrival tree: teams count into DSR_ARRIVE_GROUPS group counters (64 B
      * apart), the last team of each group into `arrived` */
     uint32_t group[DSR_ARRIVE_GROUPS * 16];
 };
-#define DSR_RESULT_HOST_BYTES offsetof(dsr_dresult, claim)
 
 /* Everything one region needs on the device. */
 struct dsr_dregion {
@@ -69,6 +76,8 @@ struct dsr_dregion {
     const uint8_t *init;
     uint64_t *partials;    /* [n_red][teams][DSR_PART_WORDS] */
     dsr_dresult *result;
+    dsr_hred *out;         /* the reductions' values (host or device memory) */
+    int32_t *status;       /* the launch's error                             */
     uint32_t *trace;       /* [teams][DSR_TRACE_WORDS] or null */
     uint32_t n_ops;
     uint32_t teams;
@@ -175,6 +184,8 @@ struct dsr_lean {
     uint8_t *nest_base;
     uint64_t *partials;        /* the region, as in dsr_dregion             */
     dsr_dresult *result;
+    dsr_hred *out;
+    int32_t *status;
     uint32_t *trace;           /* null: not traced                          */
     const dsr_op *ops;
     const dsr_dloop *loops;

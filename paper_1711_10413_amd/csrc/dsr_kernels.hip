@@ -1299,6 +1299,8 @@ __device__ __forceinline__ dsr_op op_at(const op_lanes &o, uint32_t k)
 struct region_sums {
     uint64_t *partials;
     dsr_dresult *result;
+    dsr_hred *out;
+    int32_t *status;
     uint32_t teams, n_red, red_kind_mask;
 };
 
@@ -1307,6 +1309,8 @@ __device__ __forceinline__ region_sums sums_of(const dsr_dregion &R)
     region_sums S;
     S.partials = R.partials;
     S.result = R.result;
+    S.out = R.out;
+    S.status = R.status;
     S.teams = uniform(R.teams);
     S.n_red = uniform(R.n_red);
     S.red_kind_mask = uniform(R.red_kind_mask);
@@ -1530,15 +1534,14 @@ __device__ __forceinline__ void combine_teams(const region_sums &R, uint32_t cnt
     for (uint32_t r = 0; r < R.n_red; ++r) {
         const i192 s = sum_partials(R.partials + (uint64_t)r * R.teams * DSR_PART_WORDS, cnt, stride, lane);
         if (lane == 0) {
-            GLB dsr_dresult *res = (GLB dsr_dresult *)R.result;
+            GLB dsr_hred *out = (GLB dsr_hred *)R.out + r;
             const double f = ((R.red_kind_mask >> r) & 1u) ? fixed_to_double(s) : (double)(int64_t)s.w0;
-            res->fixed[r][0] = s.w0;
-            res->fixed[r][1] = s.w1;
-            res->fixed[r][2] = s.w2;
-            res->i64[r] = (int64_t)s.w0;
-            res->f64[r] = f;
-            /* served form: the completion record gets the same values
-             * directly, not read back from the result block */
+            out->fixed[0] = s.w0;
+            out->fixed[1] = s.w1;
+            out->fixed[2] = s.w2;
+            out->f64 = f;
+            out->i64 = (int64_t)s.w0;
+            /* served form: the completion record gets the same values */
             if (rec && r < DSR_MAX_RED) {
                 rec->fixed[r][0] = s.w0;
                 rec->fixed[r][1] = s.w1;
@@ -1629,8 +1632,7 @@ __device__ __forceinline__ void finish_team(const region_sums &R, uint32_t team,
         else combine_teams(R, R.teams, 1, lane, rec);
     }
     if (lane == 0) {
-        res->final_error = err;
-        __hip_atomic_fetch_add(&res->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *(GLB int32_t *)R.status = err;
         if (done_ts) *done_ts = wall_clock64();
         if (tr) tr[95] = (uint32_t)wall_clock64();
     }
@@ -2116,7 +2118,7 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
     const bool master = T.wave == A.nw - 1;
     const uint32_t nwork = A.master_joins ? A.nw : A.nw - 1;
     GLB uint32_t *tr = A.trace ? (GLB uint32_t *)(A.trace + (uint64_t)team * DSR_TRACE_WORDS) : nullptr;
-    const region_sums RS{A.partials, A.result, A.teams, A.n_red, affine ? 0u : 0xffu};
+    const region_sums RS{A.partials, A.result, A.out, A.status, A.teams, A.n_red, affine ? 0u : 0xffu};
     uint32_t barriers = 0, inner_pushes = 0;
     /* the master's place in the program, and its stack */
     stack_t S = stack_empty();

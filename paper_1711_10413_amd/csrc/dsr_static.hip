@@ -37,13 +37,14 @@ __global__ void copy_result(const dsr_dresult *src, uint32_t n_red, dsr_result_r
 {
     const uint32_t t = threadIdx.x;
     if (t == 0) {
-        dst->status = src->final_error;
+        dst->status = src->out.status;
         dst->n_red = (int32_t)n_red;
     }
     if (t < DSR_MAX_RED) {
-        dst->f64[t] = t < n_red ? src->f64[t] : 0.0;
-        dst->i64[t] = t < n_red ? src->i64[t] : 0;
-        for (int w = 0; w < 3; ++w) dst->fixed[t][w] = t < n_red ? src->fixed[t][w] : 0;
+        const dsr_hred &r = src->out.red[t];
+        dst->f64[t] = t < n_red ? r.f64 : 0.0;
+        dst->i64[t] = t < n_red ? r.i64 : 0;
+        for (int w = 0; w < 3; ++w) dst->fixed[t][w] = t < n_red ? r.fixed[w] : 0;
     }
 }
 
