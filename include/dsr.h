@@ -332,9 +332,9 @@ int dsr_region_freeze(dsr_region *r);
  * stacks, the cross-team partials and the result block -- lies in one fixed
  * device workspace of DSR_STATIC_SCRATCH_BYTES that the library holds on
  * each GPU it runs on until the process ends.  It calls no hipMalloc,
- * hipFree or other allocating routine: the program is copied in with
- * hipMemcpyAsync, the result block is cleared by a fill kernel, and the
- * result is written by a kernel to `result`, a device pointer to one
+ * hipFree or other allocating routine: what of the program does not travel in
+ * the kernel arguments is copied in with hipMemcpyAsync, and the region kernel
+ * itself writes the result to `result`, a device pointer to one
  * dsr_result_rec owned by the caller.  The region's context may be
  * host-only (device < 0: the current device is used) or a device context
  * (its own slab is not used).  Every call on one GPU uses the same

@@ -167,6 +167,7 @@ struct dsr_dlaunch {
     uint32_t *relays;          /* host-coherent: [0] requests whose images team 0
                                   relayed, [1] teams that gave up waiting */
     uint64_t *start_ts;        /* if set, block 0 stamps its start time here */
+    struct dsr_result_rec *pub; /* launch without allocation: the caller's record */
     uint64_t idle_limit;       /* close after a waiting workgroup saw the
                                   published count unchanged for this many
                                   ticks of its own clock                    */
@@ -186,6 +187,7 @@ struct dsr_lean {
     dsr_dresult *result;
     dsr_hred *out;
     int32_t *status;
+    struct dsr_result_rec *pub; /* the caller's record, or null              */
     uint32_t *trace;           /* null: not traced                          */
     const dsr_op *ops;
     const dsr_dloop *loops;
@@ -268,11 +270,8 @@ struct dsr_dconfig {
 #ifdef __cplusplus
 extern "C" {
 #endif
-/* The fixed device workspace (dsr_static.hip): its address on `device`,
- * a word fill kernel and the result-record copy kernel. */
+/* The fixed device workspace (dsr_static.hip): its address on `device`. */
 int dsr_static_workspace(int device, uint8_t **out);
-int dsr_static_fill(void *p, uint32_t words, uint32_t value, void *stream);
-int dsr_static_copy_result(const void *result_block, uint32_t n_red, void *dst, void *stream);
 /* Kernel launchers (dsr_dispatch.cpp). Return hipError_t as int. */
 /* `args` is a dsr_dlaunch, or a dsr_lean for a lean variant (cfg unused). */
 int dsr_launch_region_kernel(const void *args, const dsr_dconfig *cfg, uint32_t grid,

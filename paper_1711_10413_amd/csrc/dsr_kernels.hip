@@ -1529,7 +1529,7 @@ __device__ __forceinline__ i192 sum_partials(const uint64_t *base, uint32_t cnt,
 /* Last team: the region's reductions from the (group) partials, exact in
  * 192-bit integers, rounded once for fp64. */
 __device__ __forceinline__ void combine_teams(const region_sums &R, uint32_t cnt, uint32_t stride, uint32_t lane,
-                                              dsr_drec *rec)
+                                              dsr_drec *rec, dsr_result_rec *pub)
 {
     for (uint32_t r = 0; r < R.n_red; ++r) {
         const i192 s = sum_partials(R.partials + (uint64_t)r * R.teams * DSR_PART_WORDS, cnt, stride, lane);
@@ -1549,6 +1549,14 @@ __device__ __forceinline__ void combine_teams(const region_sums &R, uint32_t cnt
                 rec->i64[r] = (int64_t)s.w0;
                 rec->f64[r] = f;
             }
+            if (pub && r < DSR_MAX_RED) {
+                GLB dsr_result_rec *p = (GLB dsr_result_rec *)pub;
+                p->fixed[r][0] = s.w0;
+                p->fixed[r][1] = s.w1;
+                p->fixed[r][2] = s.w2;
+                p->i64[r] = (int64_t)s.w0;
+                p->f64[r] = f;
+            }
         }
     }
 }
@@ -1565,15 +1573,30 @@ __device__ __forceinline__ void publish_record(uint32_t n_red, uint64_t tag, dsr
     __hip_atomic_store(&rec->seq, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+/* Launch without allocation: the rest of the caller's public record. */
+__device__ __forceinline__ void public_record(dsr_result_rec *pub, uint32_t n_red, int32_t err, uint32_t lane)
+{
+    GLB dsr_result_rec *p = (GLB dsr_result_rec *)pub;
+    if (lane == 0) {
+        p->status = err;
+        p->n_red = (int32_t)n_red;
+    }
+    if (lane >= n_red && lane < DSR_MAX_RED) {
+        p->f64[lane] = 0.0;
+        p->i64[lane] = 0;
+        for (int w = 0; w < 3; ++w) p->fixed[lane][w] = 0;
+    }
+}
+
 /* A team's arrival after its program.  Arrivals go through a two-level
  * tree (groups of teams, then groups) so that no counter sees more than a
  * few dozen simultaneous atomics.  With up to 512 teams the last team
  * reads every partial in one round; with more, the last team of each group
  * first adds up its group's partials and leaves the sum in the group's
  * first partial slot, and the last team overall adds the group sums. */
-template <bool REDUCES>
 __device__ __forceinline__ void finish_team(const region_sums &R, uint32_t team, uint32_t lane, uint64_t *done_ts,
-                                            dsr_drec *rec, const dsr_dregion *served, GLB uint32_t *tr)
+                                            dsr_drec *rec, const dsr_dregion *served, dsr_result_rec *pub,
+                                            GLB uint32_t *tr)
 {
     uint32_t gsize = R.teams, ngroups = 1, g = 0, in_group = R.teams;
     if (R.teams > DSR_FLAT_TEAMS) {
@@ -1582,7 +1605,7 @@ __device__ __forceinline__ void finish_team(const region_sums &R, uint32_t team,
         g = team / gsize;
         in_group = min(gsize, R.teams - g * gsize);
     }
-    const bool group_sums = REDUCES && R.teams > 512;
+    const bool group_sums = R.teams > 512;
     drain_memory();                      /* this team's partials are stored */
     if (tr && lane == 0) tr[92] = (uint32_t)wall_clock64();
     GLB dsr_dresult *res = (GLB dsr_dresult *)R.result;
@@ -1627,15 +1650,14 @@ __device__ __forceinline__ void finish_team(const region_sums &R, uint32_t team,
     int32_t err = 0;
     if (lane == 0) err = __hip_atomic_exchange(&res->error, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (lane < DSR_MAX_LOOPS) __hip_atomic_store(&res->claim[lane], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if constexpr (REDUCES) {
-        if (ngroups > 1 && group_sums) combine_teams(R, ngroups, gsize, lane, rec);
-        else combine_teams(R, R.teams, 1, lane, rec);
-    }
+    if (ngroups > 1 && group_sums) combine_teams(R, ngroups, gsize, lane, rec, pub);
+    else combine_teams(R, R.teams, 1, lane, rec, pub);
     if (lane == 0) {
         *(GLB int32_t *)R.status = err;
         if (done_ts) *done_ts = wall_clock64();
         if (tr) tr[95] = (uint32_t)wall_clock64();
     }
+    if (pub) public_record(pub, R.n_red, err, lane);
     if (rec) publish_record(R.n_red, served->tag, rec, err, lane);
 }
 
@@ -1948,8 +1970,8 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_dlaunch LP, dsr_d
              * has its completion record's system-scope release do it */
             if (C.serve && R.teams > 1) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             /* the 1024-thread instance reads fewer partials per round */
-            finish_team<true>(sums_of(R), team, T.lane, (LP.done_ts && !LP.published) ? LP.done_ts + region : nullptr,
-                              LP.recs ? LP.recs + region : nullptr, &R, tr);
+            finish_team(sums_of(R), team, T.lane, (LP.done_ts && !LP.published) ? LP.done_ts + region : nullptr,
+                        LP.recs ? LP.recs + region : nullptr, &R, LP.pub, tr);
             if (tr && T.lane == 0) tr[88] = (uint32_t)wall_clock64();
         }
         if (LP.wg_exited && T.lane == 0)
@@ -2258,8 +2280,22 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
         }
     }
     if (master) {
-        if (err && T.lane == 0) atomicCAS(&A.result->error, 0, err);
-        finish_team<!gather>(RS, team, T.lane, nullptr, nullptr, nullptr, tr);
+        if constexpr (gather) {
+            /* nothing to combine, and every team meets the same error or none:
+             * where a frame goes depends on sizes alone.  The first team tells
+             * it; the others leave without arriving (a store, an atomic and a
+             * fence less, about 1 us of each team's time) */
+            if (tr && T.lane == 0) tr[92] = tr[93] = (uint32_t)wall_clock64();
+            if (team == 0) {
+                if (tr && T.lane == 0) tr[94] = (uint32_t)wall_clock64();
+                if (T.lane == 0) *(GLB int32_t *)A.status = err;
+                if (A.pub) public_record(A.pub, 0, err, T.lane);
+                if (tr && T.lane == 0) tr[95] = (uint32_t)wall_clock64();
+            }
+        } else {
+            if (err && T.lane == 0) atomicCAS(&A.result->error, 0, err);
+            finish_team(RS, team, T.lane, nullptr, nullptr, nullptr, A.pub, tr);
+        }
         if (tr && T.lane == 0) tr[88] = (uint32_t)wall_clock64();
     }
     if (tr && T.lane == 0) {
