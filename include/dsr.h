@@ -137,9 +137,12 @@ typedef struct dsr_config {
 /* One published parallel loop.  Pointers are device pointers. */
 typedef struct dsr_loop {
     uint64_t n;        /* iterations of the worksharing loop                   */
-    uint64_t chunk;    /* iterations per team (0: ceil(n/teams) rounded up to 64,
-                          or to 1024 when that is at least 16384);
-                          team t runs [t*chunk, min(n, (t+1)*chunk))            */
+    uint64_t chunk;    /* iterations per team: team t runs
+                          [t*chunk, min(n, (t+1)*chunk)).  0: the runtime's choice,
+                          ceil(n/teams) rounded up to 64, or to 1024 when that is
+                          at least 16384; long fma chains whose frames are the
+                          same in every team may be dealt to the teams in blocks
+                          instead (the results do not depend on it)             */
     const void *in;    /* FMA_CHAIN: float x[n]                                */
     void *out;         /* int32 out[n] or double y[n]                           */
     uint32_t ni, nf;   /* FMA_CHAIN: int32 and fp64 scalar counts (ni+nf <= 64) */
@@ -160,8 +163,8 @@ typedef struct dsr_loop {
 } dsr_loop;
 
 /* Loop schedules.
- * STATIC: team t runs [t*chunk, min(n, (t+1)*chunk)); its worker lanes take
- *   the iterations cyclically.
+ * STATIC: team t runs [t*chunk, min(n, (t+1)*chunk)) (see dsr_loop's chunk);
+ *   its worker lanes take the iterations cyclically.
  * DYNAMIC_TAIL: the first (100 - tail_pct)% of the iterations are split
  *   statically as above (chunk is computed by the runtime and must be 0 on
  *   input); the rest is cut into blocks of `block` iterations that worker

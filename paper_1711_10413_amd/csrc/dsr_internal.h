@@ -41,7 +41,8 @@ struct dsr_dloop {
     uint32_t len, schedule, block, depth;   /* depth: nested levels (nested body) */
     uint64_t dyn_start;    /* first iteration of the dynamic tail (= n if none) */
     uint32_t deref;        /* list body: re-read the references every batch  */
-    uint32_t pad;
+    uint32_t deal;         /* lean chains: 1 = the batches of all teams' waves are
+                              dealt in turn instead of a range per team      */
 };
 
 /* What a launch leaves for the host, written by the last team: in pinned host

@@ -626,9 +626,10 @@ struct stream_t {
         compute<N, true>(B, b);
     }
 
-    /* next(b): the wave's batch after the one at b. */
+    /* next(b): the wave's batch after the one at b.  Returns the first batch
+     * that was not a full one. */
     template <class NEXT>
-    __device__ __forceinline__ void run(uint32_t b, NEXT &&next)
+    __device__ __forceinline__ uint32_t run(uint32_t b, NEXT &&next)
     {
         auto full = [&](uint32_t q) { return (uint64_t)q + 63u + (uint64_t)(U - 1) * st < nv; };
         Ac[0] = Ac[1] = acc_zero();
@@ -664,6 +665,7 @@ struct stream_t {
         }
         acc_merge(A, Ac[0]);
         acc_merge(A, Ac[1]);
+        return b;
     }
 };
 
@@ -694,16 +696,22 @@ __device__ __forceinline__ uint32_t claim_block(uint32_t lane)
  * a claim is taken one batch ahead.  Else lane sp.p of sp.P takes every
  * sp.P-th pair.  An odd first element and an odd last one go to lanes 0 and 1
  * of the range. */
+/* A loop dealt to the waves of all teams, a batch at a time in turn: this wave
+ * is number `wave` of `waves` (0: not dealt). */
+struct deal_t {
+    uint32_t wave, waves;
+};
+
 template <int U, int ARR, bool BLOCKS, class AP, class CH>
 __device__ __forceinline__ void chain_range(const CH &ch, AP arr, uint32_t alen, const dsr_dloop &L, span_t sp,
-                                            uint32_t lane, lane_acc &A)
+                                            deal_t deal, uint32_t lane, lane_acc &A)
 {
     const uint32_t lo = uniform((uint32_t)sp.lo), hi = uniform((uint32_t)sp.hi);
     if (lo >= hi) return;
     const GLB float *x = (const GLB float *)L.in;
     GLB double *y = (GLB double *)L.out;
     const uint32_t p0 = (lo + 1) >> 1, p1 = max(p0, hi >> 1);
-    const bool edge = (sp.p == 0 && (lo & 1u)) || (sp.p == 1 && (hi & 1u));
+    bool edge = (sp.p == 0 && (lo & 1u)) || (sp.p == 1 && (hi & 1u));
     const uint32_t ie = sp.p == 0 ? lo : hi - 1;
     const float xe = edge ? x[ie] : 0.0f;
     const uint32_t st = BLOCKS ? 64u : uniform(sp.P);
@@ -711,17 +719,21 @@ __device__ __forceinline__ void chain_range(const CH &ch, AP arr, uint32_t alen,
                                ARR != ARR_NONE ? (2u * p0) % alen : 0u,
                                ARR != ARR_NONE ? 0xFFFFFFFFu / alen : 0u, st, ARR != ARR_NONE ? (2u * st) % alen : 0u,
                                lane, A, {}};
-    uint32_t b = uniform(sp.p - lane), ahead = 0;
+    constexpr uint32_t BATCH = 64u * U;
+    uint32_t b = deal.waves ? deal.wave * BATCH : uniform(sp.p - lane), ahead = 0;
+    const uint32_t step = deal.waves ? deal.waves * BATCH : U * st;
     if (BLOCKS) {
-        b = uniform(claim_block(lane)) * (64u * U);
+        b = uniform(claim_block(lane)) * BATCH;
         ahead = claim_block(lane);
     }
-    S.run(b, [&](uint32_t q) {
-        if (!BLOCKS) return q + U * st;
-        const uint32_t n = uniform(ahead) * (64u * U);
+    b = S.run(b, [&](uint32_t q) {
+        if (!BLOCKS) return q + step;
+        const uint32_t n = uniform(ahead) * BATCH;
         ahead = claim_block(lane);
         return n;
     });
+    /* a dealt loop's odd last element goes with the batch it would be in */
+    if (deal.waves) edge = edge && b == S.nv / BATCH * BATCH;
     if (__any(edge)) {
         const float xf[1] = {xe};
         const double xd[1] = {(double)xe};
@@ -744,14 +756,14 @@ __device__ __forceinline__ void chain_range(const CH &ch, AP arr, uint32_t alen,
  * 2^24-element region than blocks for 8 to 32 scalars, and the same below. */
 template <int U, int ARR, bool LEAN, class AP, class CH>
 __device__ __forceinline__ void chain_loop(const CH &ch, AP arr, uint32_t alen, const dsr_dloop &L, span_t sp,
-                                           uint32_t lane, uint32_t *claim, lane_acc &A)
+                                           deal_t deal, uint32_t lane, uint32_t *claim, lane_acc &A)
 {
     if constexpr (LEAN) {
-        chain_range<U, ARR, false>(ch, arr, alen, L, sp, lane, A);
+        chain_range<U, ARR, false>(ch, arr, alen, L, sp, deal, lane, A);
         return;
     }
     if (L.schedule == DSR_SCHED_STATIC) {
-        chain_range<U, ARR, true>(ch, arr, alen, L, sp, lane, A);
+        chain_range<U, ARR, true>(ch, arr, alen, L, sp, deal, lane, A);
         return;
     }
     uint32_t c = 0, since = 0;
@@ -759,7 +771,7 @@ __device__ __forceinline__ void chain_loop(const CH &ch, AP arr, uint32_t alen, 
         /* the next claim is issued before the current block runs, so its
          * latency overlaps the work */
         if (tail && lane == 0) c = atomicAdd(claim, 1u);
-        chain_range<U, ARR, false>(ch, arr, alen, L, sp, lane, A);
+        chain_range<U, ARR, false>(ch, arr, alen, L, sp, deal, lane, A);
         if (!tail && lane == 0) c = atomicAdd(claim, 1u);
         /* a block adds at most 1024 values per lane: flush well before 2^16 */
         if (++since == 16) { acc_flush(A); since = 0; }
@@ -774,7 +786,7 @@ __device__ __forceinline__ void chain_loop(const CH &ch, AP arr, uint32_t alen, 
  * section 5.1: lane j reads reference 1 + j, then scalar j through it. */
 template <int U, bool LEAN>
 __device__ __forceinline__ void body_chain(const team_t &T, bool refs, frame_t f, const dsr_dloop &L, span_t sp,
-                                           lane_acc &A, uint32_t *claim, uint32_t lane)
+                                           deal_t deal, lane_acc &A, uint32_t *claim, uint32_t lane)
 {
     const uint32_t ni = uniform(L.ni), nf = uniform(L.nf), alen = uniform(L.alen);
     double sv = 0.0;
@@ -783,7 +795,7 @@ __device__ __forceinline__ void body_chain(const team_t &T, bool refs, frame_t f
         const uint32_t *lst = f.space == SPACE_LIST ? ref_list(T) : (const uint32_t *)frame_hbm(T, f);
         if (uniform(L.deref) && alen == 0) {
             const list_chain ch{lst, T.stack_lds, T.stack_hbm, ni, nf};
-            chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, lane, claim, A);
+            chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, deal, lane, claim, A);
             return;
         }
         if (lane < ni + nf) {
@@ -809,14 +821,14 @@ __device__ __forceinline__ void body_chain(const team_t &T, bool refs, frame_t f
     /* an array a list refers to may lie on a 4-byte boundary alone; in global
      * memory arrays are read element by element as well (one body less) */
     if (!alen)
-        chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, lane, claim, A);
+        chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, deal, lane, claim, A);
     else if (aspace != SPACE_LDS)
-        chain_loop<UA, ARR_ODD, LEAN>(ch, glb_array{(const GLB int32_t *)(T.stack_hbm + aoff)}, alen, L, sp, lane, claim, A);
+        chain_loop<UA, ARR_ODD, LEAN>(ch, glb_array{(const GLB int32_t *)(T.stack_hbm + aoff)}, alen, L, sp, deal, lane, claim, A);
     else if ((alen & 1u) || (aoff & 7u))
-        chain_loop<UA, ARR_ODD, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, lane,
+        chain_loop<UA, ARR_ODD, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, deal, lane,
                                claim, A);
     else
-        chain_loop<UA, ARR_EVEN, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, lane,
+        chain_loop<UA, ARR_EVEN, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, deal, lane,
                                 claim, A);
 }
 
@@ -1131,7 +1143,7 @@ __device__ __forceinline__ void run_body(team_t &T, uint32_t body, frame_t f, co
     }
     case DSR_BODY_FMA_CHAIN:
     case DSR_BODY_FMA_CHAIN_REFS:
-        body_chain<U, false>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, A, claim, lane);
+        body_chain<U, false>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, deal_t{0, 0}, A, claim, lane);
         break;
     case DSR_BODY_GATHER:
         for_spans(L, sp, lane, claim, A, [&](span_t q) { body_gather(T, f, L, q); });
@@ -2057,7 +2069,8 @@ __device__ __forceinline__ V load_const(const V *p)
 /* Fixed fma chain of a lean instance: the frame's scalars are read one word
  * per lane in one round and handed out with readlanes. */
 template <int NI, int NF>
-__device__ __forceinline__ void lean_chain(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp, lane_acc &A)
+__device__ __forceinline__ void lean_chain(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp, deal_t deal,
+                                           lane_acc &A)
 {
     constexpr uint32_t NWORDS = 2 * NF + NI;
     uint32_t w[2] = {0, 0};
@@ -2088,7 +2101,7 @@ __device__ __forceinline__ void lean_chain(const team_t &T, frame_t f, const dsr
         sv = (double)(int32_t)word(2 * NF);
     }
     ch.all = make_chain(sv, NI, NF, T.lane);
-    chain_range<8, ARR_NONE, false>(ch, glb_array{nullptr}, 0, L, sp, T.lane, A);
+    chain_range<8, ARR_NONE, false>(ch, glb_array{nullptr}, 0, L, sp, deal, T.lane, A);
 }
 
 __device__ __forceinline__ void lean_affine(const team_t &T, frame_t f, const dsr_dloop &L, span_t sp, lane_acc &A)
@@ -2227,7 +2240,12 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
         stamped = true;
         if (!master || A.master_joins) {
             const dsr_dloop L = loop == 0 ? A.loop0 : load_const(A.loops + loop);
-            const span_t sp = team_span(L, team, T.wave * 64 + T.lane, nwork * 64);
+            span_t sp = team_span(L, team, T.wave * 64 + T.lane, nwork * 64);
+            deal_t deal{0, 0};
+            if (!gather && !affine && L.deal) {
+                sp = span_t{0, L.n, T.lane, 64u};
+                deal = deal_t{team * nwork + T.wave, A.teams * nwork};
+            }
             if (tr && T.lane == 0) tr[96 + 2 * T.wave] = (uint32_t)wall_clock64();
             lane_acc acc = acc_zero();
             if constexpr (gather) {
@@ -2236,9 +2254,10 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
             } else if constexpr (affine) {
                 lean_affine(T, f, L, sp, acc);
             } else if constexpr (chains) {
-                body_chain<8, true>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, acc, nullptr, T.lane);
+                body_chain<8, true>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, deal, acc, nullptr, T.lane);
             } else {
-                lean_chain<DSR_LEAN_NI(VARIANT - DSR_LEAN_BASE), DSR_LEAN_NF(VARIANT - DSR_LEAN_BASE)>(T, f, L, sp, acc);
+                lean_chain<DSR_LEAN_NI(VARIANT - DSR_LEAN_BASE), DSR_LEAN_NF(VARIANT - DSR_LEAN_BASE)>(T, f, L, sp, deal,
+                                                                                                    acc);
             }
             if (tr && T.lane == 0) tr[97 + 2 * T.wave] = (uint32_t)wall_clock64();
             if constexpr (affine) {

@@ -143,3 +143,50 @@ def test_ragged_sizes(n, ni, nf, alen):
     for form, wg, slab in (("frame", 64, 4096), ("frame", 256, 4096), ("list", 192, 0), ("batch", 128, 4096),
                            ("frame", 1024, 0)):
         check(form, wg, slab, n, 1 + n // 1500, s_i, s_f, arr, inputs("plain", n, rs))
+
+
+@pytest.mark.parametrize("wg,teams,joins", [(64, 1, 1), (64, 5, 1), (256, 2, 0), (256, 3, 1), (512, 2, 0)])
+@pytest.mark.parametrize("extra", [-1, 0, 1, 2, 511, 1023, 1024, 1025, 5000, 12345])
+@pytest.mark.parametrize("ni,nf,alen", [(2, 2, 0), (5, 4, 0), (6, 3, 14), (6, 3, 33)])
+def test_dealt_batches(wg, teams, joins, extra, ni, nf, alen):
+    """Loops around the length from which their batches are dealt to all teams:
+    every element once, ragged ends included; not with frames of their own."""
+    waves = teams * (wg // 64 - (0 if joins else 1))
+    n = 3 * 1024 * waves + extra
+    rs = np.random.RandomState(n)
+    s_i = scalars("small", ni, rs)
+    s_f = rs.randint(0, 1 << 53, nf) * 2.0 ** -52 - 1.0
+    arr = rs.randint(0, 1 << 16, alen).astype(np.int32) if alen else None
+    x_np = inputs("plain", n, rs)
+    ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=4096, hbm_slab_bytes=4096, max_teams=teams, master_joins=joins)
+    x = torch.from_numpy(x_np).cuda()
+    want = R.fma_chain(x_np, s_i, s_f, arr)
+    for form in ("frame", "list"):
+        y = torch.full((n + 1,), 5.0, dtype=torch.float64, device="cuda")
+        r = chain_region(ctx, form, n, teams, s_i, s_f, arr, x, y)
+        D.dsr_launch(r, torch.cuda.current_stream().cuda_stream)
+        assert D.dsr_region_sync(r) == 0
+        got = y.cpu().numpy()
+        assert np.array_equal(got[:n], want) and got[n] == 5.0
+        assert D.dsr_region_reduction(r, 0)[2] == exact_total(want)
+        D.dsr_region_free(r)
+    # a frame per team keeps team t on its own range
+    img, size = D.fma_chain_frame(s_i, s_f, arr)
+    stride = (size + 15) // 16 * 16
+    images, parts = b"", []
+    chunk = -(-n // teams)
+    chunk = -(-chunk // (1024 if chunk >= 16384 else 64)) * (1024 if chunk >= 16384 else 64)
+    for t in range(teams):
+        images += D.fma_chain_frame(s_i + t, s_f, arr)[0].ljust(stride, b"\0")
+        lo, hi = min(n, t * chunk), min(n, (t + 1) * chunk)
+        parts.append(R.fma_chain(x_np[lo:hi], s_i + t, s_f, arr, i0=lo))
+    y = torch.full((n,), 5.0, dtype=torch.float64, device="cuda")
+    r = D.dsr_region_begin(ctx, teams)
+    f = D.dsr_push(r, size, images, init_stride=stride, init_bytes=size)
+    D.dsr_publish(r, f, D.DSR_BODY_FMA_CHAIN, n, inp=x.data_ptr(), out=y.data_ptr(), ni=ni, nf=nf, alen=alen)
+    D.dsr_pop(r, f)
+    D.dsr_launch(r, torch.cuda.current_stream().cuda_stream)
+    assert D.dsr_region_sync(r) == 0
+    assert np.array_equal(y.cpu().numpy(), np.concatenate(parts))
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
