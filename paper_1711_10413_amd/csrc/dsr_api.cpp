@@ -1868,7 +1868,7 @@ extern "C" int dsr_serve_submit(dsr_server *S, dsr_region *r, void *const *outs,
     uint64_t *ring = (uint64_t *)K.items;
     for (int32_t t = 0; t < r->teams; ++t) {
         const uint32_t seq = K.pub + (uint32_t)t;
-        ring[seq & (S->cfg.ring_items - 1)] = ((uint64_t)seq << 32) | ((uint64_t)k << 16) | (uint32_t)t;
+        ring[seq & (S->cfg.ring_items - 1)] = ((uint64_t)(seq + 1u) << 32) | ((uint64_t)k << 16) | (uint32_t)t;
     }
     sl.busy = true;
     sl.tmpl = dev_img ? r : nullptr;

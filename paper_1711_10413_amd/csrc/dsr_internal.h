@@ -105,8 +105,9 @@ struct dsr_dregion {
  * DSR_SERVE_SLOT_HEAD on, so a team copies the head and the images' first
  * bytes in one round of loads.
  * A ring item is one 64-bit word: the item's position in the ring's
- * sequence (upper 32 bits), the slot (bits 16-31) and the team (bits 0-15),
- * so a reader can tell a stale word from the item it waits for. */
+ * sequence, counted from 1 (upper 32 bits), the slot (bits 16-31) and the team
+ * (bits 0-15), so a reader can tell a stale word, or a ring word never
+ * written, from the item it waits for. */
 #define DSR_SERVE_MAX_OPS 16
 #define DSR_SERVE_MAX_LOOPS 4
 #define DSR_SERVE_OPS_AT 128

@@ -1811,8 +1811,9 @@ __device__ __forceinline__ bool wait_item(const dsr_dlaunch &LP, uint32_t it, ui
     if (ok && lane == 0) {
         /* published before the count that was seen: a word still holding an
          * older sequence is read again (bounded, so a broken ring cannot
-         * hold the workgroup) */
-        for (uint32_t k = 0; (uint32_t)(item >> 32) != it && k < (1u << 22); ++k)
+         * hold the workgroup).  Sequences start at 1: a word of the cleared
+         * ring is no item, whichever item this workgroup waits for */
+        for (uint32_t k = 0; (uint32_t)(item >> 32) != it + 1u && k < (1u << 22); ++k)
             item = __hip_atomic_load(ring + (it & LP.ring_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     return ok != 0;
