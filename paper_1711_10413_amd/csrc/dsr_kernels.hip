@@ -817,18 +817,21 @@ __device__ __forceinline__ void body_chain(const team_t &T, bool refs, frame_t f
         else if (lane < ni + nf) sv = *(const GLB double *)(fb + 24 + 8 * (lane - ni));
     }
     const rt_chain ch = make_chain(sv, ni, nf, lane);
-    constexpr int UA = U > 4 ? 4 : U;
+    /* batches of U pairs with an array too: half as many computed for less time
+     * than memory takes to return the next batch's x (2^20 elements, 48 scalars,
+     * 16 teams, per launch 63.0 -> 51.5 us; two such batches ahead 63.0); a second
+     * full one ahead costs the general instances their registers */
     /* an array a list refers to may lie on a 4-byte boundary alone; in global
      * memory arrays are read element by element as well (one body less) */
     if (!alen)
         chain_loop<U, ARR_NONE, LEAN>(ch, glb_array{nullptr}, 0, L, sp, deal, lane, claim, A);
     else if (aspace != SPACE_LDS)
-        chain_loop<UA, ARR_ODD, LEAN>(ch, glb_array{(const GLB int32_t *)(T.stack_hbm + aoff)}, alen, L, sp, deal, lane, claim, A);
+        chain_loop<U, ARR_ODD, LEAN>(ch, glb_array{(const GLB int32_t *)(T.stack_hbm + aoff)}, alen, L, sp, deal, lane, claim, A);
     else if ((alen & 1u) || (aoff & 7u))
-        chain_loop<UA, ARR_ODD, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, deal, lane,
+        chain_loop<U, ARR_ODD, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, deal, lane,
                                claim, A);
     else
-        chain_loop<UA, ARR_EVEN, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, deal, lane,
+        chain_loop<U, ARR_EVEN, LEAN>(ch, lds_array{(const LDSQ int32_t *)(dsr_lds + cb_bytes(T.nw) + aoff)}, alen, L, sp, deal, lane,
                                 claim, A);
 }
 
