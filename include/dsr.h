@@ -669,8 +669,9 @@ int dsr_occupancy_model(const dsr_hw_model *hw, uint32_t threads_per_team,
  * (1,1) (2,2) (4,4) (8,8) (16,16) (32,32), which a single-region launch of
  * workgroups up to 256 threads runs when every publish of the region is that
  * chain; 17 and 18 for those of regions that publish only gathers or only
- * affine loops, of any workgroup size; 19, up to 512 threads, for any other
- * mix of fma chains; all with a static schedule), the team's LDS
+ * affine loops, of any workgroup size; 19 and 20, up to 512 threads, for any
+ * other mix of fma chains and for any mix of bodies; all with a static
+ * schedule), the team's LDS
  * (control block plus stack slab) and the device's parameters. */
 int dsr_region_occupancy(dsr_ctx *ctx, uint32_t variant, dsr_occupancy *out);
 

@@ -99,8 +99,8 @@ struct dsr_region {
     uint32_t n_red;
     uint32_t red_kind_mask;
     int32_t lean;                       /* lean instance every publish runs on: its variant
-                                           less DSR_LEAN_BASE (-1 none yet, -2 mixed or
-                                           other bodies) */
+                                           less DSR_LEAN_BASE (-1 none yet, -2 a dynamic
+                                           schedule among them) */
     bool frozen;                        /* uploaded; program can't change   */
     /* device side */
     dsr_op *d_ops;
@@ -385,10 +385,11 @@ static int32_t lean_of(int32_t body, const dsr_loop &L)
 
 static void note_lean(dsr_region *r, int32_t k)
 {
-    const int32_t any = DSR_LEAN_ANY_CHAIN - DSR_LEAN_BASE;
+    const int32_t any = DSR_LEAN_ANY_CHAIN - DSR_LEAN_BASE, mixed = DSR_LEAN_MIXED - DSR_LEAN_BASE;
     const auto chain = [any](int32_t v) { return v == any || (v >= 0 && v < DSR_LEAN_CHAINS); };
     if (r->lean == -1) r->lean = k;
-    else if (r->lean != k) r->lean = chain(r->lean) && chain(k) ? any : -2;
+    else if (r->lean < 0 || k < 0) r->lean = -2;
+    else if (r->lean != k) r->lean = chain(r->lean) && chain(k) ? any : mixed;
 }
 
 /* Kernel variant for a single-region launch of r with workgroups of wg: the
@@ -400,7 +401,7 @@ static uint32_t single_variant(const dsr_region *r, uint32_t wg)
     const uint32_t lean = (uint32_t)(DSR_LEAN_BASE + r->lean);
     if (lean == DSR_LEAN_GATHER || lean == DSR_LEAN_AFFINE) return lean;
     if (wg > 512) return 0;
-    return wg > 256 ? (uint32_t)DSR_LEAN_ANY_CHAIN : lean;
+    return wg > 256 && lean < DSR_LEAN_GATHER ? (uint32_t)DSR_LEAN_ANY_CHAIN : lean;
 }
 
 extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr_loop *loop)
@@ -698,6 +699,8 @@ static int launch_single(const dsr_region *r, const dsr_dregion &R, const dsr_dr
     A.inl_img = 0;
     A.init_in_place = r->init.size() <= 0xFFFFFFFFull ? 1u : 0u;
     A.global_lists = C.global_lists;
+    A.red_kind_mask = R.red_kind_mask;
+    A.pad = 0;
     const dsr_op &op = r->ops[0];
     if (inline_image(op)) {
         const uint32_t padded = (op.init_bytes + 15u) & ~15u;
@@ -2121,7 +2124,7 @@ extern "C" int dsr_region_occupancy(dsr_ctx *ctx, uint32_t variant, dsr_occupanc
     if (!ctx || !out) return DSR_E_INVAL;
     if (variant > 2) {
         const uint32_t most = variant < DSR_LEAN_BASE ? 0u : variant < DSR_LEAN_GATHER ? 256u
-                              : variant <= DSR_LEAN_AFFINE ? 1024u : variant == DSR_LEAN_ANY_CHAIN ? 512u : 0u;
+                              : variant <= DSR_LEAN_AFFINE ? 1024u : variant <= DSR_LEAN_MIXED ? 512u : 0u;
         if (ctx->cfg.wg_size > most) return DSR_E_INVAL;
     }
     if (ctx->device < 0) return DSR_E_STATE;

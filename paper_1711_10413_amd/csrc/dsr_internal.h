@@ -201,6 +201,8 @@ struct dsr_lean {
                                   16, zero-padded; 0: none)                 */
     uint32_t init_in_place;    /* 1: the images lie within 2^32 bytes of `init` */
     uint32_t global_lists;
+    uint32_t red_kind_mask;
+    uint32_t pad;
     dsr_dloop loop0;
     dsr_op inl_op[DSR_INLINE_OPS];
     uint8_t image[DSR_INLINE_IMG];
@@ -251,7 +253,8 @@ struct dsr_dconfig {
     X(256_l6, 256, 16)   \
     X(1024_g, 1024, 17)  \
     X(1024_a, 1024, 18)  \
-    X(512_c, 512, 19)
+    X(512_c, 512, 19)    \
+    X(512_m, 512, 20)
 
 /* Lean instances: variant DSR_LEAN_BASE + k runs single-region launches of
  * workgroups up to 256 threads whose publishes are all the fixed fma chain
@@ -260,12 +263,14 @@ struct dsr_dconfig {
  * size whose publishes are all gathers (flat or nested) or all affine
  * loops, and DSR_LEAN_ANY_CHAIN those of workgroups up to 512 threads whose
  * publishes are all fma chains, of any counts, with or without an array,
- * through frames or lists; all with a static schedule. */
+ * through frames or lists, and DSR_LEAN_MIXED those of any mix of bodies; all
+ * with a static schedule. */
 #define DSR_LEAN_BASE 10
 #define DSR_LEAN_CHAINS 7
 #define DSR_LEAN_GATHER 17
 #define DSR_LEAN_AFFINE 18
 #define DSR_LEAN_ANY_CHAIN 19
+#define DSR_LEAN_MIXED 20
 #define DSR_LEAN_NI(k) ((k) == 0 ? 1 : (k) == 1 ? 1 : (k) == 2 ? 2 : (k) == 3 ? 4 : (k) == 4 ? 8 : (k) == 5 ? 16 : 32)
 #define DSR_LEAN_NF(k) ((k) == 0 ? 0 : DSR_LEAN_NI(k))
 

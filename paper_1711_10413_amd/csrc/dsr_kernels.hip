@@ -303,14 +303,26 @@ __device__ __forceinline__ void for_spans(const dsr_dloop &L, span_t sp, uint32_
     }
 }
 
+/* One lane's share of the affine loop: groups of four outputs (one 16-byte
+ * store) from the first multiple of four on, the ends one by one.  A loop has
+ * fewer than 2^31 iterations, so indices are 32 bits wide. */
 __device__ __forceinline__ void affine_span(uint32_t a, uint32_t b, uint32_t c, uint32_t d,
                                             GLB int32_t *out, span_t sp, lane_acc &A)
 {
+    const uint32_t lo = (uint32_t)sp.lo, hi = (uint32_t)sp.hi;
+    const uint32_t v0 = min(hi, (lo + 3u) & ~3u), v1 = max(v0, hi & ~3u);
     int64_t s = 0;
-    for (uint64_t i = sp.lo + sp.p; i < sp.hi; i += sp.P) {
-        const uint32_t ui = (uint32_t)i;
-        const int32_t o = (int32_t)(a * ui + b - (c ^ ui) + d);
-        out[i] = o;
+    auto value = [&](uint32_t i) { return (int32_t)(a * i + b - (c ^ i) + d); };
+    for (uint32_t i = v0 + 4 * sp.p; i < v1; i += 4 * sp.P) {
+        const i32x4 o = {value(i), value(i + 1), value(i + 2), value(i + 3)};
+        __builtin_nontemporal_store(o, (GLB i32x4 *)(out + i));
+        s += ((int64_t)o.x + o.y) + ((int64_t)o.z + o.w);
+    }
+    /* at most three elements before the groups and three after */
+    const uint32_t edge = sp.p < v0 - lo ? lo + sp.p : v1 + (sp.p - (v0 - lo));
+    if (sp.p < (v0 - lo) + (hi - v1)) {
+        const int32_t o = value(edge);
+        out[edge] = o;
         s += o;
     }
     acc_add_i64(A, s);
@@ -2146,7 +2158,7 @@ template <int MAXWG, int VARIANT>
 __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
 {
     constexpr bool gather = VARIANT == DSR_LEAN_GATHER, affine = VARIANT == DSR_LEAN_AFFINE;
-    constexpr bool chains = VARIANT == DSR_LEAN_ANY_CHAIN;
+    constexpr bool mixed = VARIANT == DSR_LEAN_MIXED, chains = VARIANT == DSR_LEAN_ANY_CHAIN || mixed;
     touch_args<offsetof(dsr_lean, image)>();
     const uint32_t team = blockIdx.x;
     team_t T = team_bind(dsr_lds, A.nw, A.lds_cap, A.threshold, A.hbm_base + (uint64_t)team * A.hbm_slot_bytes,
@@ -2157,7 +2169,7 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
     const bool master = T.wave == A.nw - 1;
     const uint32_t nwork = A.master_joins ? A.nw : A.nw - 1;
     GLB uint32_t *tr = A.trace ? (GLB uint32_t *)(A.trace + (uint64_t)team * DSR_TRACE_WORDS) : nullptr;
-    const region_sums RS{A.partials, A.result, A.out, A.status, A.teams, A.n_red, affine ? 0u : 0xffu};
+    const region_sums RS{A.partials, A.result, A.out, A.status, A.teams, A.n_red, A.red_kind_mask};
     uint32_t barriers = 0, inner_pushes = 0;
     /* the master's place in the program, and its stack */
     stack_t S = stack_empty();
@@ -2246,7 +2258,9 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
             const dsr_dloop L = loop == 0 ? A.loop0 : load_const(A.loops + loop);
             span_t sp = team_span(L, team, T.wave * 64 + T.lane, nwork * 64);
             deal_t deal{0, 0};
-            if (!gather && !affine && L.deal) {
+            const bool chain_body = !gather && !affine &&
+                                    (!mixed || body == DSR_BODY_FMA_CHAIN || body == DSR_BODY_FMA_CHAIN_REFS);
+            if (chain_body && L.deal) {
                 sp = span_t{0, L.n, T.lane, 64u};
                 deal = deal_t{team * nwork + T.wave, A.teams * nwork};
             }
@@ -2257,6 +2271,10 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                 else body_gather_nested(T, f, L, sp, T.wave, nwork, inner_pushes, tr);
             } else if constexpr (affine) {
                 lean_affine(T, f, L, sp, acc);
+            } else if (mixed && !chain_body) {
+                if (body == DSR_BODY_AFFINE_XOR) lean_affine(T, f, L, sp, acc);
+                else if (body == DSR_BODY_GATHER) body_gather(T, f, L, sp);
+                else body_gather_nested(T, f, L, sp, T.wave, nwork, inner_pushes, tr);
             } else if constexpr (chains) {
                 body_chain<8, true>(T, body == DSR_BODY_FMA_CHAIN_REFS, f, L, sp, deal, acc, nullptr, T.lane);
             } else {
@@ -2287,6 +2305,8 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
              * every outstanding memory operation of the wave, its loop stores
              * included */
             uint64_t *pp = A.partials + ((uint64_t)red * A.teams + team) * DSR_PART_WORDS;
+            const bool whole = affine || (mixed && body == DSR_BODY_AFFINE_XOR);
+            if (mixed && red == 0xffffffffu) continue;       /* a gather */
             if (chains && body == DSR_BODY_FMA_CHAIN_REFS) {
                 /* the shared sum is where reference 0 points */
                 const uint32_t *lst = f.space == SPACE_LIST ? ref_list(T) : (const uint32_t *)frame_hbm(T, f);
@@ -2294,10 +2314,10 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                 f.off = uniform(lst[1]);
             }
             if (f.space == SPACE_LDS)
-                store_partial(pp, update_sum((LDSQ uint64_t *)(dsr_lds + cb_bytes(T.nw) + f.off), tot, affine, T.lane),
+                store_partial(pp, update_sum((LDSQ uint64_t *)(dsr_lds + cb_bytes(T.nw) + f.off), tot, whole, T.lane),
                               T.lane);
             else
-                store_partial(pp, update_sum((GLB uint64_t *)(T.stack_hbm + f.off), tot, affine, T.lane), T.lane);
+                store_partial(pp, update_sum((GLB uint64_t *)(T.stack_hbm + f.off), tot, whole, T.lane), T.lane);
             /* a global reference list dies with its parallel region */
             if (chains && lf.space == SPACE_HBM) pop(T, S);
         }

@@ -180,3 +180,58 @@ def test_gather_frames_read_in_place(depth, A, length):
     assert D.dsr_region_trace(r, 1)["placements"] == [("hbm", k * stride, stride) for k in range(3)]
     D.dsr_region_free(r)
     D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("wg,joins", [(64, 1), (256, 0), (256, 1), (512, 1), (1024, 0)])
+@pytest.mark.parametrize("slab", [0, 16384])
+@pytest.mark.parametrize("n,chunk", [(0, 0), (1, 0), (4099, 1026), (50001, 0)])
+def test_programs_of_mixed_bodies(wg, joins, slab, n, chunk):
+    """One program with every body: chains (fixed, with an array, through a
+    list), an affine loop, flat and nested gathers, over nested frames; sums
+    added to a frame from several publishes."""
+    teams = 4 if chunk == 0 else -(-n // chunk)
+    cf, x_np = W.cfg2_inputs(7, seed=3, n=max(n, 1))
+    x_np = x_np[:n]
+    x = torch.from_numpy(np.ascontiguousarray(np.resize(x_np, max(n, 1)))).cuda()
+    arr = (np.arange(33) * 5 - 40).astype(np.int32)
+    arrs = W.cfg3_arrays(2, 100)
+    img, size = D.fma_chain_frame(cf.s_i32, cf.s_f64, arr)
+    img2, size2 = D.fma_chain_frame(cf.s_i32[:2], cf.s_f64[:2])
+    ni, nf = len(cf.s_i32), len(cf.s_f64)
+    ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=slab, hbm_slab_bytes=16384, max_teams=max(teams, 1), master_joins=joins)
+    ys = [torch.full((n + 1,), 9.0, dtype=torch.float64, device="cuda") for _ in range(4)]
+    outs = [torch.full((n + 1,), 9, dtype=torch.int32, device="cuda") for _ in range(3)]
+    r = D.dsr_region_begin(ctx, max(teams, 1))
+    a = {"inp": x.data_ptr(), "chunk": chunk}
+    f0 = D.dsr_push(r, size, img)
+    D.dsr_publish(r, f0, D.DSR_BODY_FMA_CHAIN, n, out=ys[0].data_ptr(), ni=ni, nf=nf, alen=33, **a)
+    f1 = D.dsr_push(r, 24, D.affine_xor_frame(7, -3, 11, 5))
+    D.dsr_publish(r, f1, D.DSR_BODY_AFFINE_XOR, n, out=outs[0].data_ptr(), chunk=chunk)
+    f2 = D.dsr_push(r, 800, D.gather_frame(arrs))
+    D.dsr_publish(r, f2, D.DSR_BODY_GATHER_NESTED, n, out=outs[1].data_ptr(), arrays=2, length=100, depth=3, chunk=chunk)
+    D.dsr_publish(r, f2, D.DSR_BODY_GATHER, n, out=outs[2].data_ptr(), arrays=2, length=100, chunk=chunk)
+    D.dsr_pop(r, f2)
+    D.dsr_pop(r, f1)
+    refs = [(f0, 0)] + [(f0, 24 + 8 * nf + 4 * k) for k in range(ni)] + [(f0, 24 + 8 * k) for k in range(nf)]
+    for y, deref in ((ys[1], 0), (ys[2], 1)):
+        D.dsr_publish_list(r, refs, D.DSR_BODY_FMA_CHAIN_REFS, n, out=y.data_ptr(), ni=ni, nf=nf, deref=deref, **a)
+    f3 = D.dsr_push(r, size2, img2)
+    D.dsr_publish(r, f3, D.DSR_BODY_FMA_CHAIN, n, out=ys[3].data_ptr(), ni=2, nf=2, **a)
+    D.dsr_pop(r, f3)
+    D.dsr_pop(r, f0)
+    assert run_region(r) == 0
+    want = [R.fma_chain(x_np, cf.s_i32, cf.s_f64, arr), R.fma_chain(x_np, cf.s_i32, cf.s_f64)]
+    want += [want[1], R.fma_chain(x_np, cf.s_i32[:2], cf.s_f64[:2])]
+    for y, w in zip(ys, want):
+        got = y.cpu().numpy()
+        assert np.array_equal(got[:n], w) and got[n] == 9.0
+    wa, total = R.affine_xor(7, -3, 11, 5, 0, n)
+    wg_ = R.gather(arrs, 0, n)
+    for o, w in zip(outs, (wa, wg_, wg_)):
+        got = o.cpu().numpy()
+        assert np.array_equal(got[:n], w) and got[n] == 9
+    t = [R.fixed75_sum(w) for w in want]
+    assert D.dsr_region_reduction(r, 1)[0] == total
+    assert [D.dsr_region_reduction(r, k)[2] for k in (0, 2, 3, 4)] == [t[0], t[0] + t[1], t[0] + 2 * t[1], t[3]]
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
