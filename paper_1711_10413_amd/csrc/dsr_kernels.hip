@@ -1240,13 +1240,18 @@ __device__ __forceinline__ uint32_t ragged_word(const uint8_t *src, uint32_t o, 
     return w;
 }
 
-/* Copy a frame's initial bytes (or zeros) with the whole master wave.  The
- * 16-byte vectors that lie wholly inside the initial bytes go in rounds of
- * eight per lane, all loads of a round in flight together (a 32 KiB frame
- * is four round trips, not thirty-two); the rest is zeros or a ragged
- * edge. */
+/* Copy a frame's initial bytes (or zeros) with the whole master wave.  What
+ * bounds it is the latency of a round of loads, so from global memory to LDS
+ * the 16-byte vectors that lie wholly inside the initial bytes go by loads
+ * that write LDS themselves: they hold no registers, and all those of a
+ * 32 KiB frame are in flight together, where four rounds through registers
+ * had followed each other (launch and wait of a chain over 2^20 outputs with
+ * a 32 KiB frame 67.5 -> 65.7 us; of nested gathers over 2^26 outputs, 2048
+ * teams with 32 KiB each, 63.3 -> 61.2 us).  To HBM, and from a served request's
+ * copy in LDS (global = false), they go through registers in rounds of eight
+ * per lane.  The rest is zeros or a ragged edge. */
 __device__ __forceinline__ void init_frame(team_t &T, frame_t f, const uint8_t *src, uint32_t init_bytes,
-                                           uint32_t nbytes)
+                                           uint32_t nbytes, bool global)
 {
     uint8_t *dst = (uint8_t *)frame_ptr(T, f);
     const uint32_t nvec = nbytes >> 4;
@@ -1254,7 +1259,18 @@ __device__ __forceinline__ void init_frame(team_t &T, frame_t f, const uint8_t *
     const uint32_t full = src_aligned ? min(init_bytes, nbytes) >> 4 : 0;
     const uint4 *s4 = (const uint4 *)src;
     uint4 *d4 = (uint4 *)dst;
-    for (uint32_t k0 = T.lane; k0 < full; k0 += 512) {
+    uint32_t direct = 0;
+    if (global && f.space == SPACE_LDS && full >= 64u) {
+        /* this wave's own writes to a popped frame here land first */
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        /* lane i's vector lands 16 i bytes after the wave's LDS address */
+        const GLB uint8_t *g = (const GLB uint8_t *)src + 16u * T.lane;
+        LDSQ uint8_t *l = (LDSQ uint8_t *)(dsr_lds + cb_bytes(T.nw) + f.off);
+        for (; direct + 64u <= full; direct += 64u)
+            __builtin_amdgcn_global_load_lds((const GLB uint32_t *)(g + 16u * direct), (LDSQ uint32_t *)(l + 16u * direct),
+                                             16, 0, 0);
+    }
+    for (uint32_t k0 = direct + T.lane; k0 < full; k0 += 512) {
         const uint32_t k1 = k0 + 64, k2 = k0 + 128, k3 = k0 + 192, k4 = k0 + 256, k5 = k0 + 320,
                        k6 = k0 + 384, k7 = k0 + 448;
         /* indices past the end reload the last vector (always in bounds);
@@ -1279,6 +1295,9 @@ __device__ __forceinline__ void init_frame(team_t &T, frame_t f, const uint8_t *
                            ragged_word(src, o + 8, init_bytes), ragged_word(src, o + 12, init_bytes));
     }
     for (uint32_t o = nvec * 16 + T.lane; o < nbytes; o += 64) dst[o] = o < init_bytes ? src[o] : 0;
+    /* the workers read the frame after the hand-over barrier, which waits for
+     * LDS operations but not for these loads */
+    if (direct) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 /* The region's program, one op per lane of the master wave: all ops are
@@ -1410,7 +1429,7 @@ __device__ __forceinline__ int32_t run_program(team_t &T, const dsr_dregion &R, 
                 tr[3 + 3 * npush] = f.size;
             }
             npush++;
-            init_frame(T, f, R.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes, op.nbytes);
+            init_frame(T, f, R.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes, op.nbytes, !C.serve);
         } else if (op.kind == DSR_OP_PUBLISH) {
             frame_t f, lf{SPACE_NONE, 0, 0};
             if (op.body == DSR_BODY_FMA_CHAIN_REFS) {
@@ -2215,7 +2234,7 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                         read_in_place(T, S, (uint32_t)(op.init_off + (uint64_t)team * op.init_stride));
                     } else {
                         init_frame(T, p, A.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes,
-                                   op.nbytes);
+                                   op.nbytes, true);
                     }
                 } else if (op.kind == DSR_OP_PUBLISH) {
                     if (chains && op.body == DSR_BODY_FMA_CHAIN_REFS) {

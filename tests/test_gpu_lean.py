@@ -235,3 +235,48 @@ def test_programs_of_mixed_bodies(wg, joins, slab, n, chunk):
     assert [D.dsr_region_reduction(r, k)[2] for k in (0, 2, 3, 4)] == [t[0], t[0] + t[1], t[0] + 2 * t[1], t[3]]
     D.dsr_region_free(r)
     D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("wg", [64, 256, 1024])
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("image", [1, 252, 255, 256, 257, 260, 515, 2303, 8191, 8192])
+def test_frames_copied_to_lds(wg, batch, image):
+    """Frames on chip of sizes around whole rounds of the wave's direct
+    copies, over bytes that a popped frame left there: one image for all
+    teams with zeros behind it, one for each team, above one another."""
+    n, teams, chunk, length = 3 * 8300, 3, 8300, 8300
+    dirty = np.full(2 * length, -1, np.int32)
+    vals = (np.arange(image) * 7 + 1).astype(np.int32)
+    stride = (4 * image + 15) // 16 * 16
+    own = [np.concatenate([vals + 100 * t, np.zeros(length - image, np.int32)]) for t in range(teams)]
+    ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=2 * (4 * length + 16), hbm_slab_bytes=0, max_teams=teams)
+    outs = [torch.full((n,), -9, dtype=torch.int32, device="cuda") for _ in range(3)]
+    r = D.dsr_region_begin(ctx, teams)
+    args = {"arrays": 1, "chunk": chunk}
+    f = D.dsr_push(r, 8 * length, dirty.tobytes())
+    D.dsr_publish(r, f, D.DSR_BODY_GATHER, n, out=outs[0].data_ptr(), length=2 * length, **args)
+    D.dsr_pop(r, f)
+    f0 = D.dsr_push(r, 4 * length, vals.tobytes())
+    f1 = D.dsr_push(r, 4 * length, b"".join((vals + 100 * t).astype(np.int32).tobytes().ljust(stride, b"\0")
+                                            for t in range(teams)), init_stride=stride, init_bytes=4 * image)
+    D.dsr_publish(r, f1, D.DSR_BODY_GATHER, n, out=outs[1].data_ptr(), length=length, **args)
+    D.dsr_pop(r, f1)
+    D.dsr_publish(r, f0, D.DSR_BODY_GATHER_NESTED, n, out=outs[2].data_ptr(), length=length, depth=2, **args)
+    D.dsr_pop(r, f0)
+    if batch:
+        b = D.dsr_batch_create(ctx, [r])
+        D.dsr_batch_tune(b, wg_size=wg, lds_slab_bytes=2 * (4 * length + 16))
+        for _ in range(2):
+            D.dsr_batch_launch(b, stream())
+            assert D.dsr_batch_sync(b) == 0
+    else:
+        assert run_region(r) == 0
+    plain = np.concatenate([vals, np.zeros(length - image, np.int32)])
+    want = [R.gather([dirty], 0, n), np.concatenate([R.gather([own[t]], t * chunk, (t + 1) * chunk) for t in range(teams)]),
+            R.gather([plain], 0, n)]
+    for o, w in zip(outs, want):
+        assert np.array_equal(o.cpu().numpy(), w)
+    if batch:
+        D.dsr_batch_free(b)
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
