@@ -566,34 +566,36 @@ struct stream_t {
     __device__ __forceinline__ void load(batch_t<U, ARR> &B, uint32_t b) const
     {
         uint32_t j = 0;
-        if constexpr (ARR != ARR_NONE) {
-            /* (first + 2 (b + lane)) mod alen; the quotient from the
-             * reciprocal is at most one short */
-            const uint32_t k = first + 2u * (b + lane);
-            j = k - __umulhi(k, inv) * alen;
-            j = j >= alen ? j - alen : j;
-        }
+        /* (first + 2 v) mod alen; the quotient from the reciprocal is at most
+         * one short */
+        auto index = [&](uint32_t v) {
+            const uint32_t k = first + 2u * v, m = k - __umulhi(k, inv) * alen;
+            return m >= alen ? m - alen : m;
+        };
+        if constexpr (ARR != ARR_NONE && !MASK) j = index(b + lane);
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const GLB char *base = xb + 8ull * (b + (uint32_t)u * st);
             uint32_t off = 8u * lane;
             if constexpr (MASK) {
-                /* pairs past the end load the last one (their results are
-                 * dropped) */
-                const uint32_t v = b + (uint32_t)u * st;
+                /* pairs past the end do the last one again, its array
+                 * elements too (their results are dropped, but not whether
+                 * they lie in the exact-sum window) */
+                const uint32_t v = min(b + (uint32_t)u * st + lane, nv - 1);
                 base = xb;
-                off = 8u * min(v + lane, nv - 1);
+                off = 8u * v;
+                if constexpr (ARR != ARR_NONE) j = index(v);
             }
             B.x[u] = __builtin_nontemporal_load((const GLB f32x2 *)(base + off));
             if constexpr (ARR == ARR_EVEN) {
                 const i32x2 q = *(const typename AP::pair)(arr.p + j);
                 B.a[2 * u] = q.x;
                 B.a[2 * u + 1] = q.y;
-                j = mod_step(j, dj, alen);
+                if constexpr (!MASK) j = mod_step(j, dj, alen);
             } else if constexpr (ARR == ARR_ODD) {
                 B.a[2 * u] = arr.p[j];
                 B.a[2 * u + 1] = arr.p[j + 1 == alen ? 0 : j + 1];
-                j = mod_step(j, dj, alen);
+                if constexpr (!MASK) j = mod_step(j, dj, alen);
             }
         }
     }

@@ -190,3 +190,27 @@ def test_dealt_batches(wg, teams, joins, extra, ni, nf, alen):
     assert np.array_equal(y.cpu().numpy(), np.concatenate(parts))
     D.dsr_region_free(r)
     D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("n", [1, 2, 6, 127, 1026])
+@pytest.mark.parametrize("alen", [200, 2001])
+def test_elements_past_the_end_are_not_judged(n, alen):
+    """Array elements that no iteration uses would take the last x out of the
+    exact-sum window; every value of the loop itself lies inside it."""
+    n = min(n, alen - 50)
+    x_np = np.full(n, 0.4375, np.float32)
+    arr = np.full(alen, I31, np.int32)
+    arr[:n] = 3
+    s_i, s_f = np.full(4, I31, np.int32), np.zeros(1)
+    x = torch.from_numpy(x_np).cuda()
+    y = torch.zeros(n, dtype=torch.float64, device="cuda")
+    want = R.fma_chain(x_np, s_i, s_f, arr)
+    assert np.abs(want).max() < 2.0 ** 32 < 4 * 0.4375 * I31 + I31
+    for wg in (256, 1024):
+        ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=16384, hbm_slab_bytes=4096, max_teams=1)
+        r = chain_region(ctx, "frame", n, 1, s_i, s_f, arr, x, y)
+        D.dsr_launch(r, torch.cuda.current_stream().cuda_stream)
+        assert D.dsr_region_sync(r) == 0
+        assert np.array_equal(y.cpu().numpy(), want)
+        D.dsr_region_free(r)
+        D.dsr_destroy(ctx)
