@@ -124,14 +124,60 @@ __device__ __forceinline__ void acc_add_f64(lane_acc &a, double y)
     a.b3 += r2;
 }
 
+/* The bins of a stream's values.  b1 and b2 start at the constants that
+ * round to their grids, so one add both rounds a value to the grid and adds
+ * it, and what was added is the bin's difference: seven adds per value
+ * instead of acc_add_f64's eleven, and no compare.  Exact while a bin stays in
+ * its constant's binade: fewer than 2^14 values below 2^32 each.  b3 takes
+ * what is left below 2^-41, which is on the 2^-75 grid if the value is. */
+struct bins_t {
+    double b1, b2, b3;
+};
+#define DSR_BIN1 0x1.8p47
+#define DSR_BIN2 0x1.8p12
+
+__device__ __forceinline__ bins_t bins_zero()
+{
+    return bins_t{DSR_BIN1, DSR_BIN2, 0.0};
+}
+
+/* Value e goes to bins e & 1.  One wave alone on its SIMD waits for each
+ * fp64 result it uses next, so the steps of G values go side by side: 2^21
+ * elements, one scalar, 16 teams of 3 workers 53.4 -> 45.1 us per launch,
+ * 2^20 with 48 scalars and an array 52.2 -> 46.9 us; 2^24 elements, 512
+ * teams, 0.3-0.9 us less for 1 to 64 scalars. */
+template <int G>
+__device__ __forceinline__ void bins_add(bins_t (&B)[2], const double *y)
+{
+    double n[G], r[G];
+#pragma unroll
+    for (int e = 0; e < G; ++e) n[e] = (e < 2 ? B[e & 1].b1 : n[e < 2 ? 0 : e - 2]) + y[e];
+#pragma unroll
+    for (int e = 0; e < G; ++e) r[e] = n[e] - (e < 2 ? B[e & 1].b1 : n[e < 2 ? 0 : e - 2]);
+#pragma unroll
+    for (int e = 0; e < G; ++e) r[e] = y[e] - r[e];
+    B[0].b1 = n[G - 2];
+    B[1].b1 = n[G - 1];
+#pragma unroll
+    for (int e = 0; e < G; ++e) n[e] = (e < 2 ? B[e & 1].b2 : n[e < 2 ? 0 : e - 2]) + r[e];
+    double t[G];
+#pragma unroll
+    for (int e = 0; e < G; ++e) t[e] = n[e] - (e < 2 ? B[e & 1].b2 : n[e < 2 ? 0 : e - 2]);
+#pragma unroll
+    for (int e = 0; e < G; ++e) r[e] -= t[e];
+    B[0].b2 = n[G - 2];
+    B[1].b2 = n[G - 1];
+#pragma unroll
+    for (int e = 0; e < G; ++e) B[e & 1].b3 += r[e];
+}
+
 /* Bins of the same grid add exactly while each holds fewer than 2^16
  * values. */
-__device__ __forceinline__ void acc_merge(lane_acc &a, const lane_acc &b)
+__device__ __forceinline__ void acc_merge(lane_acc &a, const bins_t &b)
 {
-    a.b1 += b.b1;
-    a.b2 += b.b2;
+    a.b1 += b.b1 - DSR_BIN1;
+    a.b2 += b.b2 - DSR_BIN2;
     a.b3 += b.b3;
-    a.bad |= b.bad;
 }
 
 /* A lane's bins as one integer of 2^-75 units (bin values are integers of
@@ -363,13 +409,39 @@ __device__ __forceinline__ void fma_all(double s, double (&acc)[E], const double
     for (int e = 0; e < E; ++e) acc[e] = __builtin_fma(s, xd[e], acc[e]);
 }
 
-/* Whether any of a lane's values lies outside the exact-sum window. */
+/* A double's exponent and leading bits: ordered as its magnitude, NaN above
+ * all. */
+__device__ __forceinline__ uint32_t magnitude(double y)
+{
+    return (uint32_t)((uint64_t)__double_as_longlong(y) >> 32) & 0x7FFFFFFFu;
+}
+
+/* Whether any of a lane's values lies outside the exact-sum window
+ * (|y| >= 2^32 or not finite). */
 template <int E>
 __device__ __forceinline__ bool outside(const double (&y)[E])
 {
-    bool w = false;
+    uint32_t m = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) w |= !(__builtin_fabs(y[e]) < 0x1p32);
+    for (int e = 0; e < E; ++e) m = max(m, magnitude(y[e]));
+    return m >= 0x41F00000u;
+}
+
+/* Whether any of a lane's values inside the window is not on the 2^-75 grid.
+ * All doubles of 2^-23 and more are on it; only a batch that holds a smaller
+ * one is looked at value by value. */
+template <int E>
+__device__ __forceinline__ bool off_grid(const double (&y)[E])
+{
+    uint32_t m = 0x3FF00000u;
+#pragma unroll
+    for (int e = 0; e < E; ++e) m = min(m, magnitude(y[e]));
+    bool w = false;
+    if (__any(m < 0x3E800000u)) {
+        asm volatile("");      /* keep the branch */
+#pragma unroll
+        for (int e = 0; e < E; ++e) w |= __builtin_rint(y[e] * 0x1p75) != y[e] * 0x1p75;
+    }
     return w;
 }
 
@@ -422,15 +494,16 @@ struct rt_chain {
             one = __all(frac == 0 && __builtin_fmaf(__uint_as_float(mx), M, ma) < 0x1p28f);
         }
         if (one) fma_all<E>(S, acc, xd);
-        for (uint32_t k = one ? ni : 0;; k = 0) {
-            steps<E>(acc, xd, k);
-            const bool w = outside<E>(acc);
-            if (ARR || !one || !__any(w)) return w;
+        steps<E>(acc, xd, one ? ni : 0u);
+        bool w = outside<E>(acc);
+        if (!ARR && one && __any(w)) {
             /* all the steps of a batch with a value outside the window */
-            one = false;
 #pragma unroll
             for (int e = 0; e < E; ++e) acc[e] = 0.0;
+            steps<E>(acc, xd, 0);
+            w = outside<E>(acc);
         }
+        return w;
     }
 };
 
@@ -560,10 +633,10 @@ struct stream_t {
     uint32_t st, dj;          /* pair stride of a lane, as an array step      */
     uint32_t lane;
     lane_acc &A;
-    lane_acc Ac[2];
+    bins_t B[2];
 
     template <int N, bool MASK>
-    __device__ __forceinline__ void load(batch_t<U, ARR> &B, uint32_t b) const
+    __device__ __forceinline__ void load(batch_t<U, ARR> &t, uint32_t b) const
     {
         uint32_t j = 0;
         /* (first + 2 v) mod alen; the quotient from the reciprocal is at most
@@ -586,58 +659,59 @@ struct stream_t {
                 off = 8u * v;
                 if constexpr (ARR != ARR_NONE) j = index(v);
             }
-            B.x[u] = __builtin_nontemporal_load((const GLB f32x2 *)(base + off));
+            t.x[u] = __builtin_nontemporal_load((const GLB f32x2 *)(base + off));
             if constexpr (ARR == ARR_EVEN) {
                 const i32x2 q = *(const typename AP::pair)(arr.p + j);
-                B.a[2 * u] = q.x;
-                B.a[2 * u + 1] = q.y;
+                t.a[2 * u] = q.x;
+                t.a[2 * u + 1] = q.y;
                 if constexpr (!MASK) j = mod_step(j, dj, alen);
             } else if constexpr (ARR == ARR_ODD) {
-                B.a[2 * u] = arr.p[j];
-                B.a[2 * u + 1] = arr.p[j + 1 == alen ? 0 : j + 1];
+                t.a[2 * u] = arr.p[j];
+                t.a[2 * u + 1] = arr.p[j + 1 == alen ? 0 : j + 1];
                 if constexpr (!MASK) j = mod_step(j, dj, alen);
             }
         }
     }
 
     template <int N, bool MASK>
-    __device__ __forceinline__ void compute(const batch_t<U, ARR> &B, uint32_t b)
+    __device__ __forceinline__ void compute(const batch_t<U, ARR> &t, uint32_t b)
     {
         double xd[2 * N], acc[2 * N];
         float xf[2 * N];
         int32_t a[2 * N];
 #pragma unroll
         for (int e = 0; e < 2 * N; ++e) {
-            xf[e] = (e & 1) ? B.x[e / 2].y : B.x[e / 2].x;
+            xf[e] = (e & 1) ? t.x[e / 2].y : t.x[e / 2].x;
             xd[e] = (double)xf[e];
-            a[e] = ARR != ARR_NONE ? B.a[e] : 0;
+            a[e] = ARR != ARR_NONE ? t.a[e] : 0;
             acc[e] = ARR != ARR_NONE ? (double)a[e] : 0.0;
         }
         const bool w = ch.template eval<ARR != ARR_NONE, 2 * N>(acc, xd, xf, a);
-        A.bad |= (uint32_t)w;
+        A.bad |= (uint32_t)(w || off_grid<2 * N>(acc));
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            f64x2 r = {acc[2 * u], acc[2 * u + 1]};
+            const f64x2 r = {acc[2 * u], acc[2 * u + 1]};
             const uint32_t v = b + (uint32_t)u * st;
             if constexpr (MASK) {
                 const bool in = v + lane < nv;
                 if (in) __builtin_nontemporal_store(r, (GLB f64x2 *)(yb + 16ull * (v + lane)));
-                r.x = in ? r.x : 0.0;
-                r.y = in ? r.y : 0.0;
+                acc[2 * u] = in ? r.x : 0.0;
+                acc[2 * u + 1] = in ? r.y : 0.0;
             } else {
                 __builtin_nontemporal_store(r, (GLB f64x2 *)(yb + 16ull * v + 16u * lane));
             }
-            acc_add_f64(Ac[0], r.x);
-            acc_add_f64(Ac[1], r.y);
         }
+        constexpr int G = N < 4 ? 2 * N : 8;
+#pragma unroll
+        for (int e = 0; e < 2 * N; e += G) bins_add<G>(B, acc + e);
     }
 
     template <int N>
     __device__ __forceinline__ void rest(uint32_t b)
     {
-        batch_t<U, ARR> B;
-        load<N, true>(B, b);
-        compute<N, true>(B, b);
+        batch_t<U, ARR> last;
+        load<N, true>(last, b);
+        compute<N, true>(last, b);
     }
 
     /* next(b): the wave's batch after the one at b.  Returns the first batch
@@ -646,7 +720,7 @@ struct stream_t {
     __device__ __forceinline__ uint32_t run(uint32_t b, NEXT &&next)
     {
         auto full = [&](uint32_t q) { return (uint64_t)q + 63u + (uint64_t)(U - 1) * st < nv; };
-        Ac[0] = Ac[1] = acc_zero();
+        B[0] = B[1] = bins_zero();
         bool have = full(b);
         if (have) {
             batch_t<U, ARR> cur;
@@ -658,12 +732,12 @@ struct stream_t {
                 batch_t<U, ARR> nxt;
                 if (more) load<U, false>(nxt, bn);
                 compute<U, false>(cur, b);
-                /* a batch adds U values to each bin: flush well before 2^16 */
-                if (++since == 2048) {
-                    acc_merge(A, Ac[0]);
-                    acc_merge(A, Ac[1]);
+                /* a batch adds U values to each bin: flush before 2^14 */
+                if (++since == 1024) {
+                    acc_merge(A, B[0]);
+                    acc_merge(A, B[1]);
                     acc_flush(A);
-                    Ac[0] = Ac[1] = acc_zero();
+                    B[0] = B[1] = bins_zero();
                     since = 0;
                 }
                 b = bn;
@@ -677,8 +751,8 @@ struct stream_t {
             else if (U >= 4 && left > 2) rest<U < 4 ? U : 4>(b);
             else rest<U < 2 ? U : 2>(b);
         }
-        acc_merge(A, Ac[0]);
-        acc_merge(A, Ac[1]);
+        acc_merge(A, B[0]);
+        acc_merge(A, B[1]);
         return b;
     }
 };

@@ -214,3 +214,54 @@ def test_elements_past_the_end_are_not_judged(n, alen):
         assert np.array_equal(y.cpu().numpy(), want)
         D.dsr_region_free(r)
         D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("alen", [0, 3, 4])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_bins_of_a_long_stream(sign, alen):
+    """The most values one lane may have, at the edge of the window: its bins
+    are emptied in time, and the sum stays exact."""
+    n = (1 << 21) - 3
+    x_np = np.full(n, 1 - 2.0 ** -24, np.float32)
+    x_np[::7] = np.float32(2.0 ** -20 + 2.0 ** -43)
+    s_i = np.full(4, sign * ((1 << 30) - 1), np.int32)
+    s_f = np.array([2.0 ** -52 + 2.0 ** -3])
+    arr = np.array([5, -7, 11, 2][:alen], np.int32) if alen else None
+    x = torch.from_numpy(x_np).cuda()
+    y = torch.zeros(n, dtype=torch.float64, device="cuda")
+    want = R.fma_chain(x_np, s_i, s_f, arr)
+    ctx = D.dsr_init(wg_size=64, lds_slab_bytes=4096, hbm_slab_bytes=4096, max_teams=1, master_joins=1)
+    r = chain_region(ctx, "frame", n, 1, s_i, s_f, arr, x, y)
+    D.dsr_launch(r, torch.cuda.current_stream().cuda_stream)
+    assert D.dsr_region_sync(r) == 0
+    assert np.array_equal(y.cpu().numpy(), want)
+    values, counts = np.unique(want, return_counts=True)
+    assert D.dsr_region_reduction(r, 0)[2] == sum(exact_total(v) * int(c) for v, c in zip(values.reshape(-1, 1), counts))
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("n", [1, 7, 64, 1026, 5000])
+@pytest.mark.parametrize("alen", [0, 8])
+@pytest.mark.parametrize("value,ok", [(0.0, True), (2.0 ** -23, True), (2.0 ** -75, True), (3 * 2.0 ** -75, True),
+                                      (2.0 ** -76, False), (2.0 ** -60 + 2.0 ** -80, False), (1e-300, False)])
+def test_grid_of_small_values(n, alen, value, ok):
+    """A value between others that is on the 2^-75 grid or off it: the last
+    one, or one inside."""
+    ctx = D.dsr_init(wg_size=128, lds_slab_bytes=4096, hbm_slab_bytes=4096, max_teams=1, master_joins=1)
+    arr = np.zeros(alen, np.int32) if alen else None
+    for at in {0, n // 2, n - 1}:
+        x_np = np.full(n, 1.0, np.float32)
+        x_np[at] = 2.0 ** -20
+        s_f = np.array([value * 2.0 ** 20])
+        y_at = R.fma_chain(x_np, np.zeros(1, np.int32), s_f, arr)
+        x = torch.from_numpy(x_np).cuda()
+        y = torch.zeros(n, dtype=torch.float64, device="cuda")
+        r = chain_region(ctx, "frame", n, 1, np.zeros(1, np.int32), s_f, arr, x, y)
+        D.dsr_launch(r, torch.cuda.current_stream().cuda_stream)
+        st = D.dsr_region_sync(r)
+        on = all(float(v * 2.0 ** 75).is_integer() for v in y_at)
+        assert ok <= on and st == (0 if on else D.DSR_E_RANGE)
+        assert np.array_equal(y.cpu().numpy(), y_at)
+        D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
