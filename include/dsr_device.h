@@ -13,7 +13,8 @@
  *                   Figure 2: hand a frame reference and a body to workers.
  *   await         ~ the worker's barrier + __kmpc_kernel_parallel of
  *                   Figure 3: false means terminate.
- *   end_parallel  ~ __kmpc_kernel_end_parallel + the second barrier.
+ * The join (~ __kmpc_kernel_end_parallel + the second barrier of Figure 3) is
+ * a plain barrier after the body.
  *
  * Roles (a wave64 rendering of section 4's warp-based split): the team's
  * last wave is the master wave and its lane 0 the OpenMP master; every

@@ -1385,6 +1385,21 @@ __device__ __forceinline__ uint32_t ragged_word(const uint8_t *src, uint32_t o, 
     return w;
 }
 
+/* The 16-byte vectors [first, full) of an LDS frame's image, in rounds of 64
+ * (one per lane) that lie `step` apart, by loads that write LDS themselves;
+ * the next round's first vector.  Lane i's vector lands 16 i bytes after the
+ * wave's LDS address. */
+__device__ __forceinline__ uint32_t direct_rounds(const team_t &T, uint32_t off, const uint8_t *src, uint32_t first,
+                                                  uint32_t full, uint32_t step)
+{
+    const GLB uint8_t *g = (const GLB uint8_t *)src + 16u * T.lane;
+    LDSQ uint8_t *l = (LDSQ uint8_t *)(dsr_lds + cb_bytes(T.nw) + off);
+    for (; first + 64u <= full; first += step)
+        __builtin_amdgcn_global_load_lds((const GLB uint32_t *)(g + 16u * first), (LDSQ uint32_t *)(l + 16u * first), 16, 0,
+                                         0);
+    return first;
+}
+
 /* Copy a frame's initial bytes (or zeros) with the whole master wave.  What
  * bounds it is the latency of a round of loads, so from global memory to LDS
  * the 16-byte vectors that lie wholly inside the initial bytes go by loads
@@ -1394,9 +1409,10 @@ __device__ __forceinline__ uint32_t ragged_word(const uint8_t *src, uint32_t o, 
  * a 32 KiB frame 67.5 -> 65.7 us; of nested gathers over 2^26 outputs, 2048
  * teams with 32 KiB each, 63.3 -> 61.2 us).  To HBM, and from a served request's
  * copy in LDS (global = false), they go through registers in rounds of eight
- * per lane.  The rest is zeros or a ragged edge. */
+ * per lane.  The first `under_way` vectors (whole rounds) are being copied
+ * already.  The rest is zeros or a ragged edge. */
 __device__ __forceinline__ void init_frame(team_t &T, frame_t f, const uint8_t *src, uint32_t init_bytes,
-                                           uint32_t nbytes, bool global)
+                                           uint32_t nbytes, bool global, uint32_t under_way = 0)
 {
     uint8_t *dst = (uint8_t *)frame_ptr(T, f);
     const uint32_t nvec = nbytes >> 4;
@@ -1404,16 +1420,11 @@ __device__ __forceinline__ void init_frame(team_t &T, frame_t f, const uint8_t *
     const uint32_t full = src_aligned ? min(init_bytes, nbytes) >> 4 : 0;
     const uint4 *s4 = (const uint4 *)src;
     uint4 *d4 = (uint4 *)dst;
-    uint32_t direct = 0;
+    uint32_t direct = under_way;
     if (global && f.space == SPACE_LDS && full >= 64u) {
         /* this wave's own writes to a popped frame here land first */
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        /* lane i's vector lands 16 i bytes after the wave's LDS address */
-        const GLB uint8_t *g = (const GLB uint8_t *)src + 16u * T.lane;
-        LDSQ uint8_t *l = (LDSQ uint8_t *)(dsr_lds + cb_bytes(T.nw) + f.off);
-        for (; direct + 64u <= full; direct += 64u)
-            __builtin_amdgcn_global_load_lds((const GLB uint32_t *)(g + 16u * direct), (LDSQ uint32_t *)(l + 16u * direct),
-                                             16, 0, 0);
+        direct = direct_rounds(T, f.off, src, direct, full, 64u);
     }
     for (uint32_t k0 = direct + T.lane; k0 < full; k0 += 512) {
         const uint32_t k1 = k0 + 64, k2 = k0 + 128, k3 = k0 + 192, k4 = k0 + 256, k5 = k0 + 320,
@@ -2343,6 +2354,24 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
     if (tr && master && T.lane == 0) tr[86] = (uint32_t)wall_clock64();
     /* the first frame's image, 16 bytes a lane */
     i32x4 img = {0, 0, 0, 0};
+    /* A first frame that goes to LDS is copied by all the team's waves, each
+     * every nw-th round, from before the master looks at its program: its
+     * place, at the bottom of the stack, is known.  One wave has 64 loads of
+     * 1 KiB in flight at most: 2^26 outputs of 2048 teams with 128 KiB each,
+     * one team per CU, 76.5 -> 59.5 us per launch; the 2^20-element chain with
+     * a 32 KiB frame 62.1 -> 61.2 us launch and wait. */
+    uint32_t under_way = 0;
+    if (A.inl_ops && A.n_ops && A.inl_op[0].kind == DSR_OP_PUSH && !A.inl_img) {
+        const dsr_op op = A.inl_op[0];
+        const uint32_t size = (op.nbytes + DSR_ALIGN - 1) & ~(DSR_ALIGN - 1);
+        const uint8_t *src = A.init + op.init_off + (uint64_t)team * op.init_stride;
+        if (size <= T.threshold && size <= T.lds_cap && ((uintptr_t)src & 15u) == 0) {
+            const uint32_t full = min(op.init_bytes, op.nbytes) >> 4;
+            (void)direct_rounds(T, 0, src, 64u * T.wave, full, 64u * A.nw);
+            under_way = full & ~63u;
+            if (!master) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+    }
     if (master && 16u * T.lane < A.inl_img) img = *(const i32x4 *)(A.image + 16u * T.lane);
     for (;;) {
         uint32_t body = DSR_BODY_TERMINATE, loop = 0, red = 0xffffffffu;
@@ -2379,7 +2408,7 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                         read_in_place(T, S, (uint32_t)(op.init_off + (uint64_t)team * op.init_stride));
                     } else {
                         init_frame(T, p, A.init + op.init_off + (uint64_t)team * op.init_stride, op.init_bytes,
-                                   op.nbytes, true);
+                                   op.nbytes, true, at == 0 ? under_way : 0u);
                     }
                 } else if (op.kind == DSR_OP_PUBLISH) {
                     if (chains && op.body == DSR_BODY_FMA_CHAIN_REFS) {

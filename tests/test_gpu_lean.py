@@ -280,3 +280,28 @@ def test_frames_copied_to_lds(wg, batch, image):
         D.dsr_batch_free(b)
     D.dsr_region_free(r)
     D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("wg,joins", [(64, 1), (192, 0), (512, 1), (1024, 0)])
+@pytest.mark.parametrize("image", [127, 255, 256, 300, 1025, 8192, 30011])
+@pytest.mark.parametrize("stride_pad", [0, 16])
+def test_first_frame_copied_by_all_waves(wg, joins, image, stride_pad):
+    """A program's first frame, an image for each team, zeros behind it."""
+    teams, chunk = 4, image + 10
+    length, n = image + 10, 4 * (image + 10) - 3
+    stride = (4 * image + 15) // 16 * 16 + stride_pad
+    own = [(np.arange(length) * 3 + 1000 * t).astype(np.int32) * (np.arange(length) < image) for t in range(teams)]
+    ctx = D.dsr_init(wg_size=wg, lds_slab_bytes=(4 * length + 15) // 16 * 16, hbm_slab_bytes=0, max_teams=teams,
+                     master_joins=joins, flags=D.DSR_F_TRACE)
+    out = torch.full((n,), -9, dtype=torch.int32, device="cuda")
+    r = D.dsr_region_begin(ctx, teams)
+    f = D.dsr_push(r, 4 * length, b"".join(o[:image].astype(np.int32).tobytes().ljust(stride, b"\1") for o in own),
+                   init_stride=stride, init_bytes=4 * image)
+    D.dsr_publish(r, f, D.DSR_BODY_GATHER, n, out=out.data_ptr(), arrays=1, length=length, chunk=chunk)
+    D.dsr_pop(r, f)
+    assert run_region(r) == 0
+    want = np.concatenate([R.gather([own[t].astype(np.int32)], t * chunk, min(n, (t + 1) * chunk)) for t in range(teams)])
+    assert np.array_equal(out.cpu().numpy(), want)
+    assert D.dsr_region_trace(r, 2)["placements"] == [("lds", 0, (4 * length + 15) // 16 * 16)]
+    D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
