@@ -667,10 +667,12 @@ struct stream_t {
             if constexpr (MASK) {
                 /* pairs past the end do the last one again, its array
                  * elements too (their results are dropped, but not whether
-                 * they lie in the exact-sum window) */
+                 * they lie in the exact-sum window).  A dealt loop's range
+                 * holds up to 2^30 pairs (8 GiB of x): a lane's 32-bit offset
+                 * counts from the batch */
                 const uint32_t v = min(b + (uint32_t)u * st + lane, nv - 1);
-                base = xb;
-                off = 8u * v;
+                base = xb + 8ull * b;
+                off = 8u * (v - b);
                 if constexpr (ARR != ARR_NONE) j = index(v);
             }
             t.x[u] = __builtin_nontemporal_load((const GLB f32x2 *)(base + off));
