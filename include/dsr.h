@@ -142,7 +142,8 @@ typedef struct dsr_loop {
                           ceil(n/teams) rounded up to 64, or to 1024 when that is
                           at least 16384; long fma chains whose frames are the
                           same in every team may be dealt to the teams in blocks
-                          instead (the results do not depend on it)             */
+                          instead, where no other loop of the region can tell
+                          (the results do not depend on it)                     */
     const void *in;    /* FMA_CHAIN: float x[n]                                */
     void *out;         /* int32 out[n] or double y[n]                           */
     uint32_t ni, nf;   /* FMA_CHAIN: int32 and fp64 scalar counts (ni+nf <= 64) */

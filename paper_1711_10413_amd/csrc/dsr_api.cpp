@@ -17,6 +17,7 @@
 #include <chrono>
 #include <memory>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "dsr.h"
@@ -87,11 +88,25 @@ struct dsr_ctx {
     std::shared_ptr<record_pool> records;
 };
 
+/* Bytes [lo, hi) of a live frame (by handle). */
+struct frame_bytes {
+    int32_t frame;
+    uint64_t lo, hi;
+};
+
+/* What one published loop reads and writes of the frames: the bytes its body
+ * reads, and the sum it leaves (frame -1: none). */
+struct loop_uses {
+    std::vector<frame_bytes> reads;
+    frame_bytes sum;
+};
+
 struct dsr_region {
     dsr_ctx *ctx;
     int32_t teams;
     std::vector<dsr_op> ops;
     std::vector<dsr_dloop> loops;
+    std::vector<loop_uses> uses;        /* per loop                         */
     std::vector<uint8_t> init;
     std::vector<int32_t> live;          /* live frame handles, bottom..top  */
     std::vector<uint32_t> nbytes;       /* declared bytes per handle        */
@@ -294,8 +309,8 @@ static bool same_frames(const dsr_region *r, const int32_t *frames, int nframes)
  * waves of all teams in turn.  A range per team has every team stream two
  * places of its own, spread over all of x and y; dealt, the teams move through
  * both together, which memory serves better.  Any team may run any batch only
- * if their frames are the same and the caller asked for no chunk.  From three
- * batches per wave on: 512 teams x 4 waves, 8 scalars, per launch, range ->
+ * if their frames are the same and the caller asked for no chunk (and see
+ * keep_ranges for regions of several loops).  From three batches per wave on: 512 teams x 4 waves, 8 scalars, per launch, range ->
  * dealt, for 1, 2, 3, 4, 8 and 12 batches: 14.9 -> 15.2, 17.3 -> 17.3, 21.7 -> 21.1,
  * 26.5 -> 25.2, 45.1 -> 41.4, 67.9 -> 58.1 us; 2048 teams, 3 and 8: 63.4 -> 60.5,
  * 159.4 -> 145.9 us. */
@@ -304,6 +319,30 @@ static bool deal_loop(const dsr_region *r, const dsr_loop &L, const int32_t *fra
     const dsr_ctx *c = r->ctx;
     const uint64_t waves = (uint64_t)r->teams * (c->cfg.master_joins ? c->nw : c->nw - 1);
     return L.schedule == DSR_SCHED_STATIC && L.chunk == 0 && L.n >= 3 * 1024 * waves && same_frames(r, frames, nframes);
+}
+
+static bool meet(const frame_bytes &a, const frame_bytes &b)
+{
+    return a.frame == b.frame && a.lo < b.hi && b.lo < a.hi;
+}
+
+/* The last loop published is not dealt, nor any loop before it, where it
+ * matters which team ran an element: a loop reads a frame's bytes where an
+ * earlier one left its team's sum, or its own sum starts from part of them.  The
+ * sum is that of the team's own range, and every team reads its own. */
+static void keep_ranges(dsr_region *r)
+{
+    const size_t q = r->loops.size() - 1;
+    const auto apart = [r](size_t a, size_t b) { r->loops[a].deal = r->loops[b].deal = 0; };
+    const frame_bytes &mine = r->uses[q].sum;
+    for (size_t j = 0; j < q; ++j) {
+        const frame_bytes &left = r->uses[j].sum;
+        if (left.frame < 0) continue;
+        for (const frame_bytes &f : r->uses[q].reads)
+            if (meet(left, f)) apart(j, q);
+        /* (a sum added to at the same place adds up over the teams) */
+        if (meet(left, mine) && (left.lo != mine.lo || left.hi != mine.hi)) apart(j, q);
+    }
 }
 
 /* The loop part of a publish: schedule, coverage of [0, n) by the teams,
@@ -419,9 +458,12 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
     if (rc) return rc;
     const uint64_t chunk = dl.chunk;
     bool reduces = false;
+    frame_bytes reads{frame, 0, 0}, sum{-1, 0, 0};
     switch (body) {
     case DSR_BODY_AFFINE_XOR:
         if (nb < 24) return DSR_E_INVAL;
+        reads = frame_bytes{frame, 8, 24};
+        sum = frame_bytes{frame, 0, 8};
         reduces = true;
         break;
     case DSR_BODY_FMA_CHAIN: {
@@ -431,6 +473,8 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
         if (L.alen) need = ((need + 15) & ~15ull) + 4ull * L.alen;
         if (nb < need) return DSR_E_INVAL;
         if (!lane_share_ok(r, chunk)) return DSR_E_INVAL;
+        reads = frame_bytes{frame, 24, need};
+        sum = frame_bytes{frame, 0, 24};
         reduces = true;
         break;
     }
@@ -443,6 +487,7 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
         }
         if (L.arrays < 1 || L.arrays > 16 || L.len < 1) return DSR_E_INVAL;
         if ((uint64_t)nb < 4ull * L.arrays * L.len) return DSR_E_INVAL;
+        reads.hi = 4ull * L.arrays * L.len;
         break;
     default:
         return DSR_E_INVAL;
@@ -460,11 +505,14 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
         r->n_red++;
     }
     try {
+        r->uses.push_back(loop_uses{{reads}, sum});
         r->loops.push_back(dl);
         r->ops.push_back(op);
     } catch (...) {
+        if (r->uses.size() > r->loops.size()) r->uses.pop_back();
         return DSR_E_NOMEM;
     }
+    keep_ranges(r);
     note_lean(r, lean_of(body, L));
     return DSR_OK;
 }
@@ -481,8 +529,16 @@ extern "C" int dsr_publish_list(dsr_region *r, const dsr_ref *refs, int32_t n, i
     if (L.deref && L.alen) return DSR_E_INVAL;      /* per-batch reads: scalars only */
     if (n != (int32_t)(1 + L.ni + L.nf + (L.alen ? 1 : 0))) return DSR_E_INVAL;
     if (L.n && !L.in) return DSR_E_INVAL;
-    std::vector<uint32_t> table(2 * (size_t)n);
-    std::vector<int32_t> handles(n);
+    std::vector<uint32_t> table;
+    std::vector<int32_t> handles;
+    loop_uses uses{};
+    try {
+        table.resize(2 * (size_t)n);
+        handles.resize(n);
+        uses.reads.reserve(n);
+    } catch (...) {
+        return DSR_E_NOMEM;
+    }
     for (int32_t k = 0; k < n; ++k) {
         const int depth = frame_depth(r, refs[k].frame);
         if (depth < 0) return DSR_E_STATE;
@@ -493,6 +549,9 @@ extern "C" int dsr_publish_list(dsr_region *r, const dsr_ref *refs, int32_t n, i
         table[2 * k] = (uint32_t)depth;
         table[2 * k + 1] = refs[k].offset;
         handles[k] = refs[k].frame;
+        const frame_bytes f{refs[k].frame, refs[k].offset, refs[k].offset + size};
+        if (k == 0) uses.sum = f;
+        else uses.reads.push_back(f);
     }
     dsr_dloop dl{};
     int rc = prepare_loop(r, L, handles.data(), n, &dl);
@@ -511,11 +570,14 @@ extern "C" int dsr_publish_list(dsr_region *r, const dsr_ref *refs, int32_t n, i
         r->init.resize(off + table.size() * 4, 0);
         std::memcpy(r->init.data() + off, table.data(), table.size() * 4);
         op.init_off = off;
+        r->uses.push_back(std::move(uses));
         r->loops.push_back(dl);
         r->ops.push_back(op);
     } catch (...) {
+        if (r->uses.size() > r->loops.size()) r->uses.pop_back();
         return DSR_E_NOMEM;
     }
+    keep_ranges(r);
     note_lean(r, lean_of(body, L));
     r->red_kind_mask |= 1u << r->n_red;
     r->n_red++;
