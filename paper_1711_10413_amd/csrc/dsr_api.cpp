@@ -94,11 +94,12 @@ struct frame_bytes {
     uint64_t lo, hi;
 };
 
-/* What one published loop reads and writes of the frames: the bytes its body
- * reads, and the sum it leaves (frame -1: none). */
+/* What one published loop reads and writes: the frame bytes its body reads, the
+ * sum it leaves in a frame (frame -1: none), and its element sizes. */
 struct loop_uses {
     std::vector<frame_bytes> reads;
     frame_bytes sum;
+    uint32_t in_size, out_size;
 };
 
 struct dsr_region {
@@ -326,10 +327,20 @@ static bool meet(const frame_bytes &a, const frame_bytes &b)
     return a.frame == b.frame && a.lo < b.hi && b.lo < a.hi;
 }
 
+/* Whether the n elements of `size` bytes at p meet the m of `msize` at q. */
+static bool meet(const void *p, uint64_t n, uint32_t size, const void *q, uint64_t m, uint32_t msize)
+{
+    return n && m && size && msize && (uintptr_t)p < (uintptr_t)q + m * msize && (uintptr_t)q < (uintptr_t)p + n * size;
+}
+
 /* The last loop published is not dealt, nor any loop before it, where it
- * matters which team ran an element: a loop reads a frame's bytes where an
- * earlier one left its team's sum, or its own sum starts from part of them.  The
- * sum is that of the team's own range, and every team reads its own. */
+ * matters which team ran an element:
+ *   - a loop reads a frame's bytes where an earlier one left its team's sum, or
+ *     its own sum starts from part of them: the sum is that of the team's own
+ *     range, and every team reads its own;
+ *   - two loops share a buffer one of them writes: nothing orders the teams
+ *     between two loops, so a team has to meet its own range's elements again,
+ *     unless both loops deal the same elements to the same waves. */
 static void keep_ranges(dsr_region *r)
 {
     const size_t q = r->loops.size() - 1;
@@ -342,6 +353,22 @@ static void keep_ranges(dsr_region *r)
             if (meet(left, f)) apart(j, q);
         /* (a sum added to at the same place adds up over the teams) */
         if (meet(left, mine) && (left.lo != mine.lo || left.hi != mine.hi)) apart(j, q);
+    }
+    for (bool again = true; again;) {
+        again = false;
+        for (size_t b = 1; b <= q; ++b)
+            for (size_t a = 0; a < b; ++a) {
+                const dsr_dloop &A = r->loops[a], &B = r->loops[b];
+                if (!A.deal && !B.deal) continue;
+                const loop_uses &ua = r->uses[a], &ub = r->uses[b];
+                const bool outs = meet(A.out, A.n, ua.out_size, B.out, B.n, ub.out_size);
+                const bool same = A.deal && B.deal && A.out == B.out && A.n == B.n;
+                if ((outs && !same) || meet(A.out, A.n, ua.out_size, B.in, B.n, ub.in_size) ||
+                    meet(A.in, A.n, ua.in_size, B.out, B.n, ub.out_size)) {
+                    apart(a, b);
+                    again = true;
+                }
+            }
     }
 }
 
@@ -504,8 +531,9 @@ extern "C" int dsr_publish(dsr_region *r, int32_t frame, int32_t body, const dsr
         if (body == DSR_BODY_FMA_CHAIN) r->red_kind_mask |= 1u << r->n_red;
         r->n_red++;
     }
+    const bool chain = body == DSR_BODY_FMA_CHAIN;
     try {
-        r->uses.push_back(loop_uses{{reads}, sum});
+        r->uses.push_back(loop_uses{{reads}, sum, chain ? 4u : 0u, chain ? 8u : 4u});
         r->loops.push_back(dl);
         r->ops.push_back(op);
     } catch (...) {
@@ -531,7 +559,7 @@ extern "C" int dsr_publish_list(dsr_region *r, const dsr_ref *refs, int32_t n, i
     if (L.n && !L.in) return DSR_E_INVAL;
     std::vector<uint32_t> table;
     std::vector<int32_t> handles;
-    loop_uses uses{};
+    loop_uses uses{{}, {}, 4u, 8u};
     try {
         table.resize(2 * (size_t)n);
         handles.resize(n);
