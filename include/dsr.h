@@ -344,7 +344,10 @@ int dsr_region_freeze(dsr_region *r);
  * (its own slab is not used).  Every call on one GPU uses the same
  * workspace and leaves its contents behind: calls whose launches overlap
  * on one GPU (other streams, or other threads) race and must be
- * serialised by the caller; one stream serialises them.
+ * serialised by the caller; one stream serialises them.  The results of
+ * launches that overlap are undefined, those of later ones are not: once a
+ * second stream has used the workspace, or a graph holds such a launch, each
+ * launch clears the workspace's counters first, with a kernel of its own.
  * Errors: DSR_E_INVAL (null argument, or more teams than the context's
  * max_teams), DSR_E_LIVE (a frame still live), DSR_E_NOMEM (the launch
  * needs more than DSR_STATIC_SCRATCH_BYTES: teams x hbm_slab_bytes plus

@@ -965,6 +965,17 @@ extern "C" uint64_t dsr_static_bytes(const dsr_region *r)
     return r ? (uint64_t)static_plan(r).total : 0;
 }
 
+/* Whether calls on `s` are recorded into a graph (or may be). */
+static bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 extern "C" int dsr_launch_static(dsr_region *r, dsr_result_rec *result, void *stream)
 {
     static_assert(DSR_MAX_RED == 8, "dsr_result_rec holds eight reductions");
@@ -1005,7 +1016,8 @@ extern "C" int dsr_launch_static(dsr_region *r, dsr_result_rec *result, void *st
      * kernel around the region's own, a launch of a 64-team region takes 7.6 us
      * in a row of them instead of 26.1, and 24 us from a new state instead of
      * 42.5. */
-    const bool lean = single_variant(r, c->cfg.wg_size) >= DSR_LEAN_BASE;
+    const uint32_t variant = single_variant(r, c->cfg.wg_size);
+    const bool lean = variant >= DSR_LEAN_BASE;
     const auto put = [&](size_t at, const void *src, size_t bytes) {
         return !bytes || hipMemcpyAsync(ws + at, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
     };
@@ -1018,6 +1030,10 @@ extern "C" int dsr_launch_static(dsr_region *r, dsr_result_rec *result, void *st
                                  c->cfg.master_joins, 0u);
     C.hbm_base = ws + L.hbm;
     C.nest_base = L.nested ? ws + L.nest : nullptr;
+    /* (programs of gathers alone neither count nor report through the block) */
+    if (variant != DSR_LEAN_GATHER && dsr_static_counters_open(dev, stream, capturing(s)) &&
+        (rc = dsr_static_clear(R.result, sizeof(dsr_dresult) / 4, stream)))
+        return rc;
     return launch_single(r, R, (const dsr_dregion *)(ws + L.desc), C, result, stream) == 0 ? DSR_OK : DSR_E_HIP;
 }
 

@@ -277,8 +277,13 @@ struct dsr_dconfig {
 #ifdef __cplusplus
 extern "C" {
 #endif
-/* The fixed device workspace (dsr_static.hip): its address on `device`. */
+/* The fixed device workspace (dsr_static.hip): its address on `device`, and
+ * whether a launch on `stream` (recorded into a graph or not), the next on that
+ * device to use it, has to have its counters cleared. */
 int dsr_static_workspace(int device, uint8_t **out);
+int dsr_static_counters_open(int device, void *stream, int captured);
+/* Clear `words` 32-bit words at device address p on `stream`, with a kernel. */
+int dsr_static_clear(void *p, uint32_t words, void *stream);
 /* Kernel launchers (dsr_dispatch.cpp). Return hipError_t as int. */
 /* `args` is a dsr_dlaunch, or a dsr_lean for a lean variant (cfg unused). */
 int dsr_launch_region_kernel(const void *args, const dsr_dconfig *cfg, uint32_t grid,

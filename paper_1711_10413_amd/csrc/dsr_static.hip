@@ -12,11 +12,21 @@
  * share the array and race; the entry point that uses it says so.
  *
  * It starts out zero, and its first bytes are the result block of every
- * launch that uses it: each launch leaves the block's counters at zero for the
- * next one, so none has to clear them first.
+ * launch that uses it.  Each launch leaves the block's counters at zero for the
+ * next one, unless another ran beside it; then they may hold anything, and no
+ * later launch may rely on them.  Launches of one stream follow one another, so
+ * while one stream alone has used the workspace none has to clear the counters
+ * first.  From the first launch of another stream on (or one recorded into a
+ * graph, whose replays may run at any time), every launch clears them: nothing
+ * tells here when a launch of the other stream, which should have ended by then,
+ * does end.  64 teams, per launch in a row of them: 7.5 us without the clearing
+ * kernel, 9.2 us with it.  One launch in 256 of the one stream clears as well: a
+ * new stream may have the handle of one that was destroyed with work left.
  */
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <mutex>
 
 #include "dsr.h"
 #include "dsr_internal.h"
@@ -28,6 +38,20 @@ namespace {
 constexpr int kMaxDevices = 64;
 uint8_t *g_ptr[kMaxDevices];
 bool g_have[kMaxDevices];
+
+/* The streams that have used a device's workspace. */
+struct users {
+    void *stream;
+    bool several;
+    uint32_t calls;
+};
+users g_users[kMaxDevices];
+std::mutex g_users_lock;
+
+__global__ void clear_words(uint32_t *p, uint32_t words)
+{
+    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < words; k += gridDim.x * blockDim.x) p[k] = 0;
+}
 
 }  // namespace
 
@@ -50,4 +74,21 @@ extern "C" int dsr_static_workspace(int device, uint8_t **out)
     }
     *out = g_ptr[device];
     return DSR_OK;
+}
+
+extern "C" int dsr_static_counters_open(int device, void *stream, int captured)
+{
+    const std::lock_guard<std::mutex> hold(g_users_lock);
+    users &u = g_users[device];
+    /* (a per-thread stream has the same handle in every thread) */
+    if (captured || stream == (void *)hipStreamPerThread || (u.calls && stream != u.stream)) u.several = true;
+    u.stream = stream;
+    return u.calls++ % 256u == 0 || u.several;
+}
+
+extern "C" int dsr_static_clear(void *p, uint32_t words, void *stream)
+{
+    hipLaunchKernelGGL(clear_words, dim3((words + 255u) / 256u), dim3(256), 0, (hipStream_t)stream, (uint32_t *)p,
+                       words);
+    return hipGetLastError() == hipSuccess ? DSR_OK : DSR_E_HIP;
 }
