@@ -2158,6 +2158,16 @@ extern "C" int dsr_batch_replay_serial(dsr_batch *b, const int32_t *prog, const 
                                        double *latency_us)
 {
     if (!b || !prog || !arrival_s || n < 0 || !latency_us) return DSR_E_INVAL;
+    /* the regions write their results where the last launch's lie, which stay
+     * the batch's if the replay fails */
+    std::vector<uint8_t> kept;
+    if (b->have_results && b->h_out) {
+        try {
+            kept.assign(b->h_out, b->h_out + b->out_bytes);
+        } catch (...) {
+            return DSR_E_NOMEM;
+        }
+    }
     hipStream_t s = nullptr;
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) return DSR_E_HIP;
     const dsr_dconfig C = make_dconfig(b->ctx, b->tune.wg_size, b->tune.lds_slab_bytes,
@@ -2183,6 +2193,8 @@ extern "C" int dsr_batch_replay_serial(dsr_batch *b, const int32_t *prog, const 
     if (rc == DSR_OK) {
         if (fetch_batch_results(b) != DSR_OK) return DSR_E_HIP;
         b->have_results = true;
+    } else if (!kept.empty()) {
+        std::memcpy(b->h_out, kept.data(), kept.size());
     }
     return rc;
 }
