@@ -28,7 +28,8 @@
  *     order, live frames, state) are reported before any GPU work.
  *   - Device pointers are plain `void*` obtained from hipMalloc (or a
  *     framework such as PyTorch); the caller owns them and must keep them
- *     alive until the launch's stream has completed.  `stream` is a
+ *     alive until the launch's stream has completed.  A loop's buffers need
+ *     no more alignment than one of their elements.  `stream` is a
  *     hipStream_t passed as `void*` (NULL = the null stream).
  *   - A context belongs to one host thread at a time.
  */

@@ -41,6 +41,12 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 
+/* Elements of a caller's buffer, moved together: the buffer's address is a
+ * multiple of one element's size alone. */
+typedef float x_pair __attribute__((ext_vector_type(2), aligned(4)));
+typedef double y_pair __attribute__((ext_vector_type(2), aligned(8)));
+typedef int32_t out_quad __attribute__((ext_vector_type(4), aligned(4)));
+
 extern __shared__ __align__(16) uint8_t dsr_lds[];
 
 /* Address-space qualifiers: loop buffers are global memory; without the
@@ -361,7 +367,7 @@ __device__ __forceinline__ void affine_span(uint32_t a, uint32_t b, uint32_t c, 
     auto value = [&](uint32_t i) { return (int32_t)(a * i + b - (c ^ i) + d); };
     for (uint32_t i = v0 + 4 * sp.p; i < v1; i += 4 * sp.P) {
         const i32x4 o = {value(i), value(i + 1), value(i + 2), value(i + 3)};
-        __builtin_nontemporal_store(o, (GLB i32x4 *)(out + i));
+        __builtin_nontemporal_store(o, (GLB out_quad *)(out + i));
         s += ((int64_t)o.x + o.y) + ((int64_t)o.z + o.w);
     }
     /* at most three elements before the groups and three after */
@@ -675,7 +681,7 @@ struct stream_t {
                 off = 8u * (v - b);
                 if constexpr (ARR != ARR_NONE) j = index(v);
             }
-            t.x[u] = __builtin_nontemporal_load((const GLB f32x2 *)(base + off));
+            t.x[u] = __builtin_nontemporal_load((const GLB x_pair *)(base + off));
             if constexpr (ARR == ARR_EVEN) {
                 const i32x2 q = *(const typename AP::pair)(arr.p + j);
                 t.a[2 * u] = q.x;
@@ -739,7 +745,7 @@ struct stream_t {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const f64x2 r = {y[2 * u], y[2 * u + 1]};
-            __builtin_nontemporal_store(r, (GLB f64x2 *)(yb + 16ull * (b + (uint32_t)u * st) + 16u * lane));
+            __builtin_nontemporal_store(r, (GLB y_pair *)(yb + 16ull * (b + (uint32_t)u * st) + 16u * lane));
         }
     }
 
@@ -757,7 +763,7 @@ struct stream_t {
             const f64x2 r = {q.y[2 * u], q.y[2 * u + 1]};
             const uint32_t v = b + (uint32_t)u * st;
             const bool in = v + lane < nv;
-            if (in) __builtin_nontemporal_store(r, (GLB f64x2 *)(yb + 16ull * (v + lane)));
+            if (in) __builtin_nontemporal_store(r, (GLB y_pair *)(yb + 16ull * (v + lane)));
             q.y[2 * u] = in ? r.x : 0.0;
             q.y[2 * u + 1] = in ? r.y : 0.0;
         }
@@ -1047,7 +1053,7 @@ __device__ __forceinline__ void gather_store(GLB int32_t *out, uint32_t i, const
     if constexpr (V == 4) {
         const i32x4 r = {(int32_t)(s.e[0] + i), (int32_t)(s.e[1] + i + 1), (int32_t)(s.e[2] + i + 2),
                          (int32_t)(s.e[3] + i + 3)};
-        __builtin_nontemporal_store(r, (GLB i32x4 *)(out + i));
+        __builtin_nontemporal_store(r, (GLB out_quad *)(out + i));
     } else {
         __builtin_nontemporal_store((int32_t)(s.e[0] + i), out + i);
     }
