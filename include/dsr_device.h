@@ -13,8 +13,7 @@
  *                   Figure 2: hand a frame reference and a body to workers.
  *   await         ~ the worker's barrier + __kmpc_kernel_parallel of
  *                   Figure 3: false means terminate.
- * The join (~ __kmpc_kernel_end_parallel + the second barrier of Figure 3) is
- * a plain barrier after the body.
+ *   end_parallel  ~ __kmpc_kernel_end_parallel + the second barrier.
  *
  * Roles (a wave64 rendering of section 4's warp-based split): the team's
  * last wave is the master wave and its lane 0 the OpenMP master; every
@@ -91,7 +90,7 @@ struct cb_header {
     uint32_t sp_hbm;   /* HBM stack pointer                        */
     uint32_t nframes;  /* live frames                              */
     int32_t error;     /* team error (DSR_E_* or 0)                */
-    uint32_t pad0;
+    uint32_t bad;      /* OR of the flags passed to end_parallel   */
     uint32_t region;   /* launch-specific context published with the */
     uint32_t team;     /* body: which region and which of its teams  */
     uint32_t blocks;   /* blocks of the team's range claimed so far by its
@@ -140,6 +139,7 @@ __host__ __device__ constexpr uint32_t red_slot_at(uint32_t w)
 {
     return 64u + DSR_MAX_FRAMES * 16u + DSR_REF_LIST * 8u + w * 32u;
 }
+__device__ inline uint64_t *red_slot(const team_t &T, uint32_t w) { return (uint64_t *)(T.lds + red_slot_at(w)); }
 /* Base of the team's nested area (on chip). */
 __device__ inline uint8_t *nest_lds(const team_t &T)
 {
@@ -188,6 +188,7 @@ __device__ inline team_t team_init(uint8_t *lds, uint32_t nw, uint32_t lds_cap,
         h->sp_hbm = 0;
         h->nframes = 0;
         h->error = 0;
+        h->bad = 0;
     }
     return T;
 }
@@ -203,6 +204,7 @@ __device__ inline void team_reset(team_t &T)
         h->sp_hbm = 0;
         h->nframes = 0;
         h->error = 0;
+        h->bad = 0;
     }
     wave_sync();
 }
@@ -283,6 +285,21 @@ __device__ inline bool await(team_t &T, uint32_t *body, frame_t *f, uint32_t *lo
     f->size = uniform(h->size);
     *loop = uniform(h->loop);
     return *body != 0;
+}
+
+/* Every participating wave: deposit its reduction partial (a 192-bit
+ * integer, three 64-bit words, low first) and its range flag, then join
+ * (barrier 2).  Waves that did not run the body pass zeros.  (The region kernel
+ * leaves the flag in the slot's fourth word instead and adds the slots up
+ * across lanes.) */
+__device__ inline void end_parallel(team_t &T, uint64_t w0, uint64_t w1, uint64_t w2, uint32_t bad)
+{
+    if (T.lane == 0) {
+        uint64_t *r = red_slot(T, T.wave);
+        r[0] = w0; r[1] = w1; r[2] = w2;
+        if (bad) atomicOr(&header(T)->bad, 1u);
+    }
+    __syncthreads();
 }
 
 /* ---- the master's stack in registers: the same placement rule, frame table
