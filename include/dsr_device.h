@@ -338,6 +338,7 @@ __device__ inline void read_in_place(const team_t &T, stack_t &S, uint32_t off)
 {
     S.top_image = 1 + off / DSR_ALIGN;
     if (T.lane == 0) frame_table(T)[4 * (S.nframes - 1) + 3] = S.top_image;
+    wave_sync();
 }
 
 __device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes, bool global_only = false)
@@ -352,6 +353,7 @@ __device__ inline frame_t push(const team_t &T, stack_t &S, uint32_t nbytes, boo
         return f;
     }
     if (T.lane == 0) *(uint4 *)(frame_table(T) + 4 * S.nframes) = make_uint4(f.space, f.off, f.size, 0);
+    wave_sync();             /* the whole wave reads the table (frame_at, pop, lists) */
     S.nframes++;
     S.top = f;
     S.top_image = 0;
