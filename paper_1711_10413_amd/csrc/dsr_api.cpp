@@ -741,7 +741,8 @@ static bool reads_images(const dsr_region *r)
     for (size_t k = 0; k < r->ops.size(); ++k) {
         const dsr_op &op = r->ops[k];
         if (op.kind == DSR_OP_PUBLISH && op.body == DSR_BODY_FMA_CHAIN_REFS) return true;
-        if (op.kind == DSR_OP_PUSH && op.init_bytes && !(k == 0 && inline_image(op) && op.nbytes <= 1024)) return true;
+        if (op.kind == DSR_OP_PUSH && op.init_bytes && !(k == 0 && inline_image(op) && op.nbytes <= DSR_INLINE_FRAME))
+            return true;
     }
     return false;
 }

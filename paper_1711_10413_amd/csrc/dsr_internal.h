@@ -97,6 +97,10 @@ struct dsr_dregion {
 /* Program parts a single-region launch carries in its kernel arguments. */
 #define DSR_INLINE_OPS 4
 #define DSR_INLINE_IMG 512
+/* A first frame of up to this size (16 bytes a lane) whose image is in the
+ * arguments is written from registers, and its image in memory not read: a launch
+ * that copies images in leaves it out. */
+#define DSR_INLINE_FRAME 1024u
 
 /* Served form limits (a request's program is copied into LDS per item).  A
  * request slot in host memory has the layout of the LDS copy: its

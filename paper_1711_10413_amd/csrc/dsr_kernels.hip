@@ -2400,7 +2400,9 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
                         tr[3 + 3 * npush] = p.size;
                     }
                     npush++;
-                    if (at == 0 && A.inl_img && p.size <= 16u * 64u) {
+                    static_assert(DSR_INLINE_FRAME == 16u * 64u && DSR_INLINE_FRAME % DSR_ALIGN == 0,
+                                  "16 bytes a lane, whole after rounding");
+                    if (at == 0 && A.inl_img && p.size <= DSR_INLINE_FRAME) {
                         /* the image (zero-padded to a multiple of 16 bytes)
                          * from registers, zeros after it */
                         if (16u * T.lane < p.size) {

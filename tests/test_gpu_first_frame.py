@@ -45,3 +45,26 @@ def test_frame_in_a_popped_frames_place(pops, body, length, wg):
         assert np.array_equal(out.cpu().numpy(), want)
     D.dsr_region_free(r)
     D.dsr_destroy(ctx)
+
+
+@pytest.mark.parametrize("nbytes", [512, 1023, 1024, 1025, 1040, 2048])
+def test_small_image_in_a_larger_frame(nbytes):
+    """Launches without allocation, one after another, of frames around the size
+    that is written from the arguments, each with an image of its own."""
+    ctx = D.dsr_init(wg_size=128, lds_slab_bytes=4096, hbm_slab_bytes=4096, max_teams=4)
+    out = torch.zeros(1000, dtype=torch.int32, device="cuda")
+    rec = torch.zeros(D.RESULT_REC_BYTES, dtype=torch.uint8, device="cuda")
+    for k in (1, 1000, -5):
+        arr = (np.arange(100) * k).astype(np.int32)
+        r = D.dsr_region_begin(ctx, 3)
+        f = D.dsr_push(r, nbytes, arr.tobytes())
+        whole = np.zeros(nbytes // 4, np.int32)
+        whole[:100] = arr
+        D.dsr_publish(r, f, D.DSR_BODY_GATHER, 1000, out=out.data_ptr(), arrays=1, length=nbytes // 4)
+        D.dsr_pop(r, f)
+        D.dsr_launch_static(r, rec.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert D.result_rec(rec.cpu().numpy().tobytes())["status"] == 0
+        assert np.array_equal(out.cpu().numpy(), R.gather([whole], 0, 1000))
+        D.dsr_region_free(r)
+    D.dsr_destroy(ctx)
