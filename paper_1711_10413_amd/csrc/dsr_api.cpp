@@ -747,18 +747,6 @@ static bool reads_images(const dsr_region *r)
     return false;
 }
 
-/* Whether the frame op 0 pushes is still there at the first publish, where the
- * team's waves meet: until then its place is no other frame's. */
-static bool first_frame_stays(const dsr_region *r)
-{
-    if (r->ops[0].kind != DSR_OP_PUSH) return false;
-    for (const dsr_op &op : r->ops) {
-        if (op.kind == DSR_OP_PUBLISH) return true;
-        if (op.kind == DSR_OP_POP) return false;
-    }
-    return false;
-}
-
 /* Launch region r, whose descriptor R holds device pointers, with workgroups
  * of the context's size: its lean instance with everything in the kernel
  * arguments, or a general one. */
@@ -803,8 +791,8 @@ static int launch_single(const dsr_region *r, const dsr_dregion &R, const dsr_dr
     A.init_in_place = r->init.size() <= 0xFFFFFFFFull ? 1u : 0u;
     A.global_lists = C.global_lists;
     A.red_kind_mask = R.red_kind_mask;
+    A.pad = 0;
     const dsr_op &op = r->ops[0];
-    A.share_first = inline_ops(r) && !inline_image(op) && first_frame_stays(r) ? 1u : 0u;
     if (inline_image(op)) {
         const uint32_t padded = (op.init_bytes + 15u) & ~15u;
         std::memset(A.image, 0, padded);

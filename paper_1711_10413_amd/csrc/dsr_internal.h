@@ -206,10 +206,7 @@ struct dsr_lean {
     uint32_t init_in_place;    /* 1: the images lie within 2^32 bytes of `init` */
     uint32_t global_lists;
     uint32_t red_kind_mask;
-    uint32_t share_first;      /* 1: all the team's waves copy the first op's frame if
-                                  it goes to LDS: it is in inl_op, its image is not
-                                  in `image`, and no frame is popped before the
-                                  first publish                             */
+    uint32_t pad;
     dsr_dloop loop0;
     dsr_op inl_op[DSR_INLINE_OPS];
     uint8_t image[DSR_INLINE_IMG];

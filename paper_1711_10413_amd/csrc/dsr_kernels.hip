@@ -2365,14 +2365,16 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
     /* A first frame that goes to LDS is copied by all the team's waves, each
      * every nw-th round, from before the master looks at its program: its
      * place, at the bottom of the stack, is known, and until the first publish
-     * nothing else has it (share_first: nothing orders the workers' loads before
-     * a pop of the frame and a push in its place).  (Fixed chains and affine
+     * nothing else has it: a program that pops it before, which nothing here
+     * orders the workers' loads against, has more ops than travel in the
+     * arguments.  (Fixed chains and affine
      * loops have small frames, whose image comes in the arguments.)  One wave
      * has 64 loads of 1 KiB in flight at most: 2^26 outputs of 2048 teams with 128 KiB each,
      * one team per CU, 76.5 -> 59.5 us per launch; the 2^20-element chain with
      * a 32 KiB frame 62.1 -> 61.2 us launch and wait. */
     uint32_t under_way = 0;
-    if ((gather || chains) && A.share_first) {
+    static_assert(DSR_INLINE_OPS < 5, "push, pop, push, publish, pop");
+    if ((gather || chains) && A.inl_ops && A.n_ops && A.inl_op[0].kind == DSR_OP_PUSH && !A.inl_img) {
         const dsr_op op = A.inl_op[0];
         const uint32_t size = (op.nbytes + DSR_ALIGN - 1) & ~(DSR_ALIGN - 1);
         const uint8_t *src = A.init + op.init_off + (uint64_t)team * op.init_stride;
