@@ -674,11 +674,14 @@ struct stream_t {
                 /* pairs past the end do the last one again, its array
                  * elements too (their results are dropped, but not whether
                  * they lie in the exact-sum window).  A dealt loop's range
-                 * holds up to 2^30 pairs (8 GiB of x): a lane's 32-bit offset
-                 * counts from the batch */
+                 * holds up to 2^30 pairs, 8 GiB of x: its batches start at
+                 * multiples of 64 U pairs, so a batch never crosses 4 GiB, and a
+                 * lane's 32-bit offset counts from the last multiple of those.
+                 * (Counted from the batch, the code of the array chains' loop
+                 * came to lie so that it took 1.5% longer.) */
                 const uint32_t v = min(b + (uint32_t)u * st + lane, nv - 1);
-                base = xb + 8ull * b;
-                off = 8u * (v - b);
+                base = xb + ((uint64_t)(b >> 29) << 32);
+                off = 8u * v;
                 if constexpr (ARR != ARR_NONE) j = index(v);
             }
             t.x[u] = __builtin_nontemporal_load((const GLB x_pair *)(base + off));
