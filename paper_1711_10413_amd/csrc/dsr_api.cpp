@@ -428,8 +428,10 @@ static int prepare_loop(const dsr_region *r, const dsr_loop &L, const int32_t *f
     return DSR_OK;
 }
 
-/* A lane's fp64 bins stay exact for up to 2^16 values: the static share of
- * a lane is bounded here, dynamic blocks flush the bins as they go. */
+/* A lane's fp64 bins stay exact for up to 2^16 values, and the biased bins of a
+ * stream for fewer than 2^14: the streams merge theirs every 2^13 values a bin
+ * and dynamic blocks flush as they go, so the bound here, on the static share of a
+ * lane, keeps the 2^16. */
 static bool lane_share_ok(const dsr_region *r, uint64_t chunk)
 {
     const uint64_t lanes = 64ull * (r->ctx->cfg.master_joins ? r->ctx->nw : r->ctx->nw - 1);

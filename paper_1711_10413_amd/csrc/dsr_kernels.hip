@@ -856,19 +856,22 @@ __device__ __forceinline__ uint32_t claim_block(uint32_t lane)
     return c;
 }
 
-/* One range [sp.lo, sp.hi) of the loop through a chain.  BLOCKS: the team's
- * waves claim batches of 64 * U pairs from the team's counter, so a wave on a
- * SIMD it shares with fewer others takes more of them (three worker waves per
- * team and two teams per CU leave some SIMDs two worker waves and some one);
- * a claim is taken one batch ahead.  Else lane sp.p of sp.P takes every
- * sp.P-th pair.  An odd first element and an odd last one go to lanes 0 and 1
- * of the range. */
 /* A loop dealt to the waves of all teams, a batch at a time in turn: this wave
  * is number `wave` of `waves` (0: not dealt). */
 struct deal_t {
     uint32_t wave, waves;
 };
 
+/* One range [sp.lo, sp.hi) of the loop through a chain, in one of three forms.
+ * BLOCKS: the team's waves claim batches of 64 * U pairs from the team's counter,
+ * so a wave on a SIMD it shares with fewer others takes more of them (three worker
+ * waves per team and two teams per CU leave some SIMDs two worker waves and some
+ * one); a claim is taken one batch ahead.  Dealt: the range is the whole loop,
+ * up to 2^31 - 1 elements, and the wave takes every `waves`-th batch of 64 * U
+ * pairs.  Else lane sp.p of sp.P takes every sp.P-th pair; such a range, a team's or
+ * a claimed block, holds at most 2^25 elements.  An odd first element and an odd
+ * last one go to lanes 0 and 1 of the range; a dealt loop's odd last one goes to
+ * the wave whose batch it would be in. */
 template <int U, int ARR, bool BLOCKS, class AP, class CH>
 __device__ __forceinline__ void chain_range(const CH &ch, AP arr, uint32_t alen, const dsr_dloop &L, span_t sp,
                                             deal_t deal, uint32_t lane, lane_acc &A)
@@ -920,8 +923,9 @@ __device__ __forceinline__ void chain_range(const CH &ch, AP arr, uint32_t alen,
 /* A chain over the team's part of the loop: its static range by blocks, or
  * under the dynamic tail its static part and then the blocks its wave claims
  * from the loop's device counter.  The lean instances run static ranges only,
- * every wave its fixed per-lane share: 0.3-1.0 us faster there per
- * 2^24-element region than blocks for 8 to 32 scalars, and the same below. */
+ * dealt or every wave its fixed per-lane share: the share was 0.3-1.0 us faster
+ * there per 2^24-element region than blocks for 8 to 32 scalars, and the same
+ * below (loops of that length are dealt now unless the caller sets a chunk). */
 template <int U, int ARR, bool LEAN, class AP, class CH>
 __device__ __forceinline__ void chain_loop(const CH &ch, AP arr, uint32_t alen, const dsr_dloop &L, span_t sp,
                                            deal_t deal, uint32_t lane, uint32_t *claim, lane_acc &A)
@@ -2223,8 +2227,9 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_dlaunch LP, dsr_d
 
 #else
 /* ---- lean instances -----------------------------------------------------
- * Single-region launches whose every publish is of one kind (DSR_LEAN_*):
- * the kernel holds that body and the single-region form only.  A small
+ * Single-region launches with static schedules: the kernel holds the
+ * single-region form only, and of the bodies what its variant is for
+ * (DSR_LEAN_*).  A small
  * region's time is the chain of steps its master wave goes through one
  * after another (about 10 us of the 26 us launch-and-wait of a 64-team
  * region, and about 9 us of the 46 us of a 2^24-element one), so the steps
@@ -2367,12 +2372,12 @@ __global__ __launch_bounds__(MAXWG) void dsr_region_kernel(dsr_lean A)
     i32x4 img = {0, 0, 0, 0};
     /* A first frame that goes to LDS is copied by all the team's waves, each
      * every nw-th round, from before the master looks at its program: its
-     * place, at the bottom of the stack, is known, and until the first publish
-     * nothing else has it: a program that pops it before, which nothing here
-     * orders the workers' loads against, has more ops than travel in the
-     * arguments.  (Fixed chains and affine
-     * loops have small frames, whose image comes in the arguments.)  One wave
-     * has 64 loads of 1 KiB in flight at most: 2^26 outputs of 2048 teams with 128 KiB each,
+     * place, at the bottom of the stack, is known.  Nothing orders the workers'
+     * loads before a pop of that frame and a push in its place, so none may
+     * come before the first publish; a program with both has five ops at least
+     * and does not travel in the arguments.  (Fixed chains and affine loops have
+     * small frames, whose image comes in the arguments.)  One wave has 64 loads
+     * of 1 KiB in flight at most: 2^26 outputs of 2048 teams with 128 KiB each,
      * one team per CU, 76.5 -> 59.5 us per launch; the 2^20-element chain with
      * a 32 KiB frame 62.1 -> 61.2 us launch and wait. */
     uint32_t under_way = 0;
