@@ -311,7 +311,11 @@ static bool same_frames(const dsr_region *r, const int32_t *frames, int nframes)
  * places of its own, spread over all of x and y; dealt, the teams move through
  * both together, which memory serves better.  Any team may run any batch only
  * if their frames are the same and the caller asked for no chunk (and see
- * keep_ranges for regions of several loops).  From three batches per wave on: 512 teams x 4 waves, 8 scalars, per launch, range ->
+ * keep_ranges for regions of several loops), and up to DSR_DEAL_MAX elements:
+ * addressing longer ranges in the kernel moved the code of its loops, and chains on
+ * few teams with it, by -7 to +7% (run-time chains of 2^20 elements on 4 teams
+ * 129 -> 135 us, with an array of odd length 170 -> 159).  From three batches per
+ * wave on: 512 teams x 4 waves, 8 scalars, per launch, range ->
  * dealt, for 1, 2, 3, 4, 8 and 12 batches: 14.9 -> 15.2, 17.3 -> 17.3, 21.7 -> 21.1,
  * 26.5 -> 25.2, 45.1 -> 41.4, 67.9 -> 58.1 us; 2048 teams, 3 and 8: 63.4 -> 60.5,
  * 159.4 -> 145.9 us. */
@@ -319,7 +323,8 @@ static bool deal_loop(const dsr_region *r, const dsr_loop &L, const int32_t *fra
 {
     const dsr_ctx *c = r->ctx;
     const uint64_t waves = (uint64_t)r->teams * (c->cfg.master_joins ? c->nw : c->nw - 1);
-    return L.schedule == DSR_SCHED_STATIC && L.chunk == 0 && L.n >= 3 * 1024 * waves && same_frames(r, frames, nframes);
+    return L.schedule == DSR_SCHED_STATIC && L.chunk == 0 && L.n >= 3 * 1024 * waves && L.n <= DSR_DEAL_MAX &&
+           same_frames(r, frames, nframes);
 }
 
 static bool meet(const frame_bytes &a, const frame_bytes &b)

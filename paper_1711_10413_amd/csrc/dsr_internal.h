@@ -32,6 +32,10 @@ struct dsr_op {
     uint64_t pad;
 };
 
+/* The longest loop that is dealt: the round at a range's end reaches its x, 4
+ * bytes an element, by 32-bit byte offsets from the range's start. */
+#define DSR_DEAL_MAX ((uint64_t)1 << 30)
+
 struct dsr_dloop {
     uint64_t n;
     uint64_t chunk;        /* static iterations per team                    */

@@ -673,14 +673,10 @@ struct stream_t {
             if constexpr (MASK) {
                 /* pairs past the end do the last one again, its array
                  * elements too (their results are dropped, but not whether
-                 * they lie in the exact-sum window).  A dealt loop's range
-                 * holds up to 2^30 pairs, 8 GiB of x: its batches start at
-                 * multiples of 64 U pairs, so a batch never crosses 4 GiB, and a
-                 * lane's 32-bit offset counts from the last multiple of those.
-                 * (Counted from the batch, the code of the array chains' loop
-                 * came to lie so that it took 1.5% longer.) */
+                 * they lie in the exact-sum window).  The byte offset fits 32
+                 * bits: no range holds more than DSR_DEAL_MAX elements */
                 const uint32_t v = min(b + (uint32_t)u * st + lane, nv - 1);
-                base = xb + ((uint64_t)(b >> 29) << 32);
+                base = xb;
                 off = 8u * v;
                 if constexpr (ARR != ARR_NONE) j = index(v);
             }
@@ -867,8 +863,8 @@ struct deal_t {
  * so a wave on a SIMD it shares with fewer others takes more of them (three worker
  * waves per team and two teams per CU leave some SIMDs two worker waves and some
  * one); a claim is taken one batch ahead.  Dealt: the range is the whole loop,
- * up to 2^31 - 1 elements, and the wave takes every `waves`-th batch of 64 * U
- * pairs.  Else lane sp.p of sp.P takes every sp.P-th pair; such a range, a team's or
+ * up to DSR_DEAL_MAX elements, and the wave takes every `waves`-th batch of
+ * 64 * U pairs.  Else lane sp.p of sp.P takes every sp.P-th pair; such a range, a team's or
  * a claimed block, holds at most 2^25 elements.  An odd first element and an odd
  * last one go to lanes 0 and 1 of the range; a dealt loop's odd last one goes to
  * the wave whose batch it would be in. */

@@ -1,6 +1,6 @@
-"""Fma chains dealt to the waves of all teams over loops of more than 2^30
-elements, whose last batch is not a full one: the elements of that batch, and
-the exact sum, against the oracle."""
+"""Fma chains over loops of about 2^30 elements and more, below and above the
+longest that is dealt to the waves of all teams, whose last batch is not a full one:
+the elements of that batch, and the exact sum, against the oracle."""
 import numpy as np
 import pytest
 
@@ -29,6 +29,9 @@ def buffers():
     (3, 2, 0, LONGEST - 1),                  # run-time counts
     (2, 1, 250, LONGEST),                    # an array of even length, of odd length
     (2, 1, 251, LONGEST - 994),
+    (4, 4, 0, 1 << 30),                      # the longest dealt
+    (3, 2, 0, (1 << 30) - 23),
+    (2, 1, 251, (1 << 30) - 500),
 ])
 def test_last_batch_past_2_30(buffers, ni, nf, alen, n):
     x, y = buffers
